@@ -221,144 +221,307 @@ __global__ void __launch_bounds__(256) sac_select_kernel(
 }
 
 // --------------------------------------------------------- Algorithms 4/5 --
-// Round j visits every node with more than j edges.  Node n's j-th edge
-// n -> nd (length L) is removed when HasPath finds c in N(G_p, n) with
-// nd in N(G_p, c) and len(c, nd) < L.  In Algorithm 4 nodes are visited in
-// ascending id and G_p changes immediately, so G_p at n's turn is the graph
-// at the start of round j plus the round-j edges kept by nodes c < n.  The
-// GPU evaluates the start-of-round graph for all nodes at once (Jacobi
-// kernel), then settles the remaining dependence — a node c < n in
-// N(G_p, n) whose own round-j edge also goes to nd, is shorter than L and was
-// kept — by repeated passes in which a node is decided as soon as all such
-// c are (the smallest undecided node always is).
+// Round j of Algorithm 4 visits every node with more than j edges in ascending
+// id; node v's j-th edge v -> nd (length L) is removed when HasPath finds
+// v -> c and c -> nd in G_p with len(c, nd) < L.  At v's turn G_p holds the
+// edges decided before (j, v) in lexicographic order, so with (v, i) the i-th
+// edge of v's list, to c, and (c, jc) an edge of c's list to nd:
+//   (v, j) is removed  iff  for some i < j and some (jc, c) < (j, v) with
+//   len(c, jc) < L both (v, i) and (c, jc) are kept.
+// Each decision depends on edges that precede it, so the decisions are the
+// unique fixpoint of that rule, whatever order they are found in.  Every edge
+// has a status (undecided, kept, removed) and a pass visits each node that
+// still has undecided edges: a pair of kept edges removes (v, j), no pair
+// without a removed member keeps it, anything else waits for the next pass.
+// Statuses only ever become decided and a stale read (another node's write of
+// the same pass not seen) reads "undecided", so the passes need no order
+// among nodes.  The first undecided edge in (j, v) order is decided by every
+// pass; in practice 6 to 9 passes decide all of them (200,003 x 100 cosine
+// rows: 13.5M edges, longest list 2,734).
+//
+// A group of waves takes a node: the undecided targets of its list go into a
+// hash table in LDS, and the lists of its own not yet removed neighbours
+// stream past it, coalesced, the next one's load in flight.  What bounds it is
+// that chain (one list per step, most lists one 64-lane load) times the waves
+// in flight, not the bytes.  The earlier form ran one round per rank (as many
+// as the longest list, each with a same-round settling pass and a host
+// synchronisation) with a binary search per kept neighbour.
 
 constexpr int8_t ST_UNDECIDED = 0, ST_KEPT = 1, ST_REMOVED = 2;
+constexpr int PA_CLASSES = 3;          // node classes by list length, below
+constexpr int64_t PA_MAX_DEGREE = (1 << 20) - 1;   // longer lists are refused
 
-// Witness test of the start-of-round graph: c in N(G_p, n) is a witness
-// when c's edge to nd exists, was kept in an earlier round (its rank in c's
-// list is below j) and is shorter than L.  The edge is found by binary
-// search in c's edges sorted by id (sid_nb, with their edge index sid_e),
-// instead of scanning c's kept edges by length.
-template <typename LenT>
-__global__ void pa_jacobi_kernel(const int64_t *off, const int32_t *nbrs, const LenT *lens,
-                                 const int32_t *active, int64_t n_active, int j,
-                                 const int32_t *gp_nb, const int32_t *gp_cnt,
-                                 const int32_t *sid_nb, const int32_t *sid_e, const int8_t *kept,
-                                 int8_t *status) {
-    int64_t w = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-    int lane = lane_id();
-    if (w >= n_active) return;
-    int32_t v = active[w];
-    int64_t e = off[v] + j;
-    int32_t nd = nbrs[e];
-    LenT L = lens[e];
-    int cn = gp_cnt[v];
-    bool found = false;
-    for (int c0 = 0; c0 < cn && !found; c0 += WAVE) {
-        bool hit = false;
-        if (c0 + lane < cn) {
-            const int32_t c = gp_nb[off[v] + c0 + lane];
-            const int64_t cb = off[c], ce = off[c + 1];
-            int64_t lo = cb, hi = ce;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (sid_nb[mid] < nd) lo = mid + 1;
-                else hi = mid;
+// Class 0 (lists of at most 128): one wave per node, four nodes per block;
+// class 1 (at most 512): four waves per node; class 2: sixteen.  A table
+// covers CAP targets of the list at a time (class 2 lists may be longer: the
+// targets are then taken CAP at a time, in rank order) in HSZ >= 4 CAP slots,
+// so that probe runs stay short.
+constexpr int PA_CAP0 = 128, PA_CAP1 = 512, PA_CAP2 = 2048;
+
+__host__ __device__ inline int pa_class(int64_t deg) {
+    return deg <= PA_CAP0 ? 0 : deg <= PA_CAP1 ? 1 : 2;
+}
+
+template <typename LenT, int CAP, int HSZ>
+struct PaTable {
+    int64_t cbeg[CAP];     // start and length of each target's own list
+    int32_t clen[CAP];
+    int32_t nb[CAP];
+    LenT len[CAP];
+    uint32_t hid[HSZ];     // open addressing; a repeated id takes several slots
+    uint16_t hrank[HSZ];
+    uint8_t st[CAP];       // status before this pass
+    uint8_t rem[CAP];      // a witness pair is kept
+    uint8_t pend[CAP];     // a witness pair is not yet decided
+    int32_t last;          // last undecided rank within the chunk
+    int32_t left, kept;    // undecided / kept edges of the node
+};
+
+constexpr uint32_t PA_EMPTY = 0xFFFFFFFFu;   // no node id (ids are below 2^31)
+
+template <int HSZ>
+__device__ __forceinline__ uint32_t pa_hash(uint32_t id) {
+    return (id * 2654435761u) >> (32 - __builtin_ctz(HSZ));
+}
+
+template <typename T>
+__device__ __forceinline__ T ld_relaxed(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One pass over the nodes of `list`.  With several waves per node the list's
+// neighbours are taken WAVES at a time: an edge decided "kept" only by this
+// pass then counts as undecided for its own pairs unless it is the first of
+// its group (the others' flags may still change while the group runs).
+template <typename LenT, int WAVES, int CAP, int HSZ>
+__global__ void __launch_bounds__(WAVES == 1 ? 256 : WAVES * WAVE)
+pa_pass_kernel(const int64_t *off, const int32_t *nbrs, const LenT *lens, int64_t n,
+               const int32_t *list, int64_t n_list, int8_t *st, int32_t *left, int64_t *kept_cnt) {
+    constexpr int GROUPS = WAVES == 1 ? 4 : 1;   // nodes per block
+    constexpr int NT = WAVES * WAVE;             // threads per node
+    __shared__ PaTable<LenT, CAP, HSZ> tables[GROUPS];
+    const int lane = lane_id();
+    const int wv = uni(threadIdx.x / WAVE);
+    PaTable<LenT, CAP, HSZ> &T = tables[GROUPS == 1 ? 0 : wv];
+    const int w = WAVES == 1 ? 0 : wv;           // wave within the node's group
+    const int tid = WAVES == 1 ? lane : (int)threadIdx.x;
+    auto sync = [&]() {
+        if constexpr (WAVES == 1) wave_sync();
+        else __syncthreads();
+    };
+    // consecutive nodes share neighbours: give each XCD (blocks go to the 8 XCDs
+    // in turn) one run of the list
+    const int64_t nblk = gridDim.x, per = nblk / 8, tail = nblk - per * 8;
+    const int64_t xcd = blockIdx.x % 8, at = blockIdx.x / 8;
+    const int64_t blk = xcd * per + min(xcd, tail) + at;
+    const int64_t gi = GROUPS == 1 ? blk : blk * GROUPS + wv;
+    if (gi >= n_list) return;   // (a whole wave, or a whole block, leaves)
+    const int32_t v = uni(list[gi]);
+    const int64_t b = off[v];
+    const int deg = (int)(off[v + 1] - b);
+    if (tid == 0) T.left = 0, T.kept = 0;
+    for (int t0 = 0; t0 < deg; t0 += CAP) {
+        const int m = min(CAP, deg - t0);
+        sync();
+        for (int i = tid; i < HSZ; i += NT) T.hid[i] = PA_EMPTY;
+        if (tid == 0) T.last = -1;
+        sync();
+        int my_last = -1;
+        for (int i = tid; i < m; i += NT) {
+            const int8_t s = ld_relaxed(&st[b + t0 + i]);
+            const int32_t c = nbrs[b + t0 + i];
+            T.st[i] = (uint8_t)s;
+            T.rem[i] = 0;
+            T.pend[i] = 0;
+            T.nb[i] = c;
+            T.len[i] = lens[b + t0 + i];
+            int64_t cb = 0;
+            int32_t cl = 0;
+            if (s != ST_REMOVED && (uint32_t)c < (uint64_t)n) {
+                cb = off[c];
+                cl = (int32_t)min<int64_t>(off[c + 1] - cb, PA_MAX_DEGREE);
             }
-            // (a list may hold nd more than once: every copy is a candidate)
-            for (; lo < ce && sid_nb[lo] == nd && !hit; lo++) {
-                const int64_t ec = sid_e[lo];
-                hit = ec - cb < j && kept[ec] && lens[ec] < L;
+            T.cbeg[i] = cb;
+            T.clen[i] = cl;
+            if (s == ST_UNDECIDED) {
+                my_last = i;
+                uint32_t h = pa_hash<HSZ>((uint32_t)c);
+                while (atomicCAS(&T.hid[h], PA_EMPTY, (uint32_t)c) != PA_EMPTY) h = (h + 1) & (HSZ - 1);
+                T.hrank[h] = (uint16_t)i;
             }
         }
-        found = ballot(hit) != 0;
+        if (my_last >= 0) atomicMax(&T.last, my_last);
+        sync();
+        const int last = uni(T.last);
+        const int lim = last < 0 ? 0 : t0 + last + 1;   // ranks that can matter below
+        // the first 64 entries of the next list, read one step ahead
+        auto beg_of = [&](int i, int64_t &cb, int &cl) {
+            if (i >= t0) {
+                cb = (int64_t)uni64((uint64_t)T.cbeg[i - t0]);
+                cl = uni(T.clen[i - t0]);
+            } else {
+                const int32_t c = uni(nbrs[b + i]);
+                cb = 0, cl = 0;
+                if ((uint32_t)c < (uint64_t)n) {
+                    cb = off[c];
+                    cl = (int)min<int64_t>(off[c + 1] - cb, PA_MAX_DEGREE);
+                }
+            }
+            cl = min(cl, lim);   // (c, jc) needs jc <= j < lim
+        };
+        int64_t cb = 0;
+        int cl = 0;
+        int32_t x = 0;
+        LenT lx = 0;
+        int8_t sx = ST_REMOVED;
+        auto fetch = [&](int64_t base, int cnt, int jc0) {
+            sx = ST_REMOVED;
+            if (jc0 + lane < cnt) {
+                x = nbrs[base + jc0 + lane];
+                lx = lens[base + jc0 + lane];
+                sx = ld_relaxed(&st[base + jc0 + lane]);
+            }
+        };
+        if (w < lim - 1) {
+            beg_of(w, cb, cl);
+            fetch(cb, cl, 0);
+        }
+        for (int i0 = 0; i0 < lim - 1; i0 += WAVES) {
+            const int i = i0 + w;
+            // this step's list and the next one's load
+            const int64_t mb = cb;
+            const int ml = cl;
+            int32_t y = x;
+            LenT ly = lx;
+            int8_t sy = sx;
+            cl = 0;
+            if (i + WAVES < lim - 1) {
+                beg_of(i + WAVES, cb, cl);
+                fetch(cb, cl, 0);
+            }
+            // status of (v, i)
+            int si = ST_REMOVED;
+            int32_t c = -1;
+            if (i < lim - 1) {
+                if (i >= t0) {
+                    const int k = i - t0;
+                    c = uni(T.nb[k]);
+                    si = uni((int)T.st[k]);
+                    if (si == ST_UNDECIDED) {
+                        if (uni((int)T.rem[k])) si = ST_REMOVED;
+                        else if (w == 0 && !uni((int)T.pend[k])) si = ST_KEPT;
+                    }
+                } else {
+                    c = uni(nbrs[b + i]);
+                    si = uni((int)ld_relaxed(&st[b + i]));
+                }
+            }
+            if (si != ST_REMOVED) {
+                for (int jc0 = 0; jc0 < ml; jc0 += WAVE) {
+                    if (jc0 > 0) {
+                        sy = ST_REMOVED;
+                        if (jc0 + lane < ml) {
+                            y = nbrs[mb + jc0 + lane];
+                            ly = lens[mb + jc0 + lane];
+                            sy = ld_relaxed(&st[mb + jc0 + lane]);
+                        }
+                    }
+                    if (sy == ST_REMOVED) continue;
+                    const int jc = jc0 + lane;
+                    const bool both = si == ST_KEPT && sy == ST_KEPT;
+                    uint32_t h = pa_hash<HSZ>((uint32_t)y);
+                    for (uint32_t id; (id = T.hid[h]) != PA_EMPTY; h = (h + 1) & (HSZ - 1)) {
+                        if (id != (uint32_t)y) continue;
+                        const int k = T.hrank[h];
+                        const int j = t0 + k;
+                        if (j > i && (jc < j || (jc == j && c < v)) && ly < T.len[k]) {
+                            if (both) T.rem[k] = 1;
+                            else T.pend[k] = 1;
+                        }
+                    }
+                }
+            }
+            sync();   // this step's flags before the next step's status
+        }
+        // decisions of this chunk
+        sync();
+        int nl = 0, nk = 0;
+        for (int i = tid; i < m; i += NT) {
+            int s = T.st[i];
+            if (s == ST_UNDECIDED) {
+                s = T.rem[i] ? ST_REMOVED : T.pend[i] ? ST_UNDECIDED : ST_KEPT;
+                if (s != ST_UNDECIDED)
+                    __hip_atomic_store(&st[b + t0 + i], (int8_t)s, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            nl += s == ST_UNDECIDED;
+            nk += s == ST_KEPT;
+        }
+        if (nl) atomicAdd(&T.left, nl);
+        if (nk) atomicAdd(&T.kept, nk);
     }
-    if (lane == 0) status[v] = found ? ST_REMOVED : ST_UNDECIDED;
-}
-
-// edge index of every edge (the values sorted along with the ids)
-__global__ void iota_kernel(int64_t n, int32_t *out) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (int32_t)i;
-}
-
-template <typename LenT>
-__global__ void pa_settle_kernel(const int64_t *off, const int32_t *nbrs, const LenT *lens,
-                                 const int32_t *active, int64_t n_active, int j,
-                                 const int32_t *gp_nb, const int32_t *gp_cnt, int8_t *status,
-                                 int32_t *undecided) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_active) return;
-    int32_t v = active[i];
-    if (status[v] != ST_UNDECIDED) return;
-    int64_t e = off[v] + j;
-    int32_t nd = nbrs[e];
-    LenT L = lens[e];
-    int cn = gp_cnt[v];
-    bool kept_witness = false, pending = false;
-    for (int t = 0; t < cn; t++) {
-        int32_t c = gp_nb[off[v] + t];
-        if (c >= v) continue;
-        int64_t cdeg = off[c + 1] - off[c];
-        if (cdeg <= j) continue;
-        int64_t ce = off[c] + j;
-        if (nbrs[ce] != nd || !(lens[ce] < L)) continue;
-        int8_t sc = __atomic_load_n(&status[c], __ATOMIC_RELAXED);
-        if (sc == ST_KEPT) { kept_witness = true; break; }
-        if (sc == ST_UNDECIDED) pending = true;
+    sync();
+    if (tid == 0) {
+        left[v] = T.left;
+        kept_cnt[v] = T.kept;
     }
-    if (kept_witness) status[v] = ST_REMOVED;
-    else if (!pending) status[v] = ST_KEPT;
-    else atomicAdd(undecided, 1);
 }
 
+// The lists of nodes that still have undecided edges, per class (counters[0..2]
+// their lengths, counters[3] the edges left).  FIRST: from all nodes, with
+// left = the list length; counters[3] then counts lists that are too long.
+template <bool FIRST>
+__global__ void __launch_bounds__(256) pa_list_kernel(const int64_t *off, const int32_t *from,
+                                                      int64_t count, int32_t *left,
+                                                      int32_t *l0, int32_t *l1, int32_t *l2,
+                                                      unsigned long long *counters) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = lane_id();
+    int cls = -1;
+    int32_t v = 0;
+    int64_t todo = 0;
+    if (i < count) {
+        v = FIRST ? (int32_t)i : from[i];
+        const int64_t deg = off[v + 1] - off[v];
+        todo = FIRST ? deg : left[v];
+        if (todo > 0) cls = pa_class(deg);
+        if (FIRST && deg >= PA_MAX_DEGREE) atomicAdd(&counters[3], 1ull);
+    }
+#pragma unroll
+    for (int c = 0; c < PA_CLASSES; c++) {
+        const uint64_t m = ballot(cls == c);
+        if (!m) continue;
+        unsigned long long at = 0;
+        if (lane == (int)__builtin_ctzll(m)) at = atomicAdd(&counters[c], (unsigned long long)__popcll(m));
+        at = (unsigned long long)shfl64(at, (int)__builtin_ctzll(m));
+        if (cls == c) (c == 0 ? l0 : c == 1 ? l1 : l2)[at + mbcnt(m)] = v;
+    }
+    if (!FIRST) {
+        int t = (int)todo;
+        for (int s = 32; s >= 1; s >>= 1) t += __shfl_xor(t, s);
+        if (lane == 0 && t) atomicAdd(&counters[3], (unsigned long long)t);
+    }
+}
+
+// kept edges of every node, in list order (one wave per node)
 template <typename LenT>
-__global__ void pa_apply_kernel(const int64_t *off, const int32_t *nbrs, const LenT *lens,
-                                const int32_t *active, int64_t n_active, int j,
-                                int32_t *gp_nb, LenT *gp_len, int32_t *gp_cnt,
-                                const int8_t *status, int8_t *kept) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_active) return;
-    int32_t v = active[i];
-    if (status[v] != ST_KEPT) return;
-    int64_t e = off[v] + j;
-    kept[e] = 1;
-    int c = gp_cnt[v];
-    gp_nb[off[v] + c] = nbrs[e];
-    gp_len[off[v] + c] = lens[e];
-    gp_cnt[v] = c + 1;
-}
-
-__global__ void degree_hist_kernel(const int64_t *off, int64_t n, int32_t *deg,
-                                   unsigned long long *hist) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) pa_compact_kernel(const int64_t *off, const int64_t *out_off,
+                                                         int64_t n, const int32_t *nbrs,
+                                                         const LenT *lens, const int8_t *st,
+                                                         int32_t *out_nb, LenT *out_len) {
+    const int64_t v = (int64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+    const int lane = lane_id();
     if (v >= n) return;
-    int64_t d64 = off[v + 1] - off[v];
-    int d = d64 < (1 << 20) - 1 ? (int)d64 : (1 << 20) - 1;   // last bin flags overflow
-    deg[v] = d;
-    atomicAdd(&hist[d], 1ull);
-}
-
-// nodes by degree, descending: position = (#nodes with larger degree) + slot
-__global__ void order_by_degree_kernel(const int32_t *deg, int64_t n, const int64_t *start,
-                                       int32_t *cursor, int32_t *order) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    int d = deg[v];
-    int slot = atomicAdd(&cursor[d], 1);
-    order[start[d] + slot] = (int32_t)v;
-}
-
-template <typename LenT>
-__global__ void pa_compact_kernel(const int64_t *off, const int64_t *out_off, int64_t n,
-                                  const int32_t *gp_nb, const LenT *gp_len,
-                                  int32_t *out_nb, LenT *out_len) {
-    int64_t v = blockIdx.x;
-    if (v >= n) return;
-    int64_t b = off[v], ob = out_off[v], m = out_off[v + 1] - ob;
-    for (int64_t t = threadIdx.x; t < m; t += blockDim.x) {
-        out_nb[ob + t] = gp_nb[b + t];
-        out_len[ob + t] = gp_len[b + t];
+    const int64_t b = off[v], e = off[v + 1];
+    int64_t o = out_off[v];
+    for (int64_t t = b; t < e; t += WAVE) {
+        const bool keep = t + lane < e && st[t + lane] == ST_KEPT;
+        const uint64_t m = ballot(keep);
+        if (keep) {
+            out_nb[o + mbcnt(m)] = nbrs[t + lane];
+            out_len[o + mbcnt(m)] = lens[t + lane];
+        }
+        o += __popcll(m);
     }
 }
 
@@ -369,14 +532,6 @@ __global__ void cnt_to_i64_kernel(const int32_t *c, int64_t n, int64_t *o) {
 }
 
 inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
-
-size_t segsort_temp_bytes(int64_t nnz, int64_t n) {
-    size_t bytes = 0;
-    (void)hipcub::DeviceSegmentedRadixSort::SortPairs(
-        nullptr, bytes, (const int32_t *)nullptr, (int32_t *)nullptr, (const int32_t *)nullptr,
-        (int32_t *)nullptr, (int)nnz, (int)n, (const int64_t *)nullptr, (const int64_t *)nullptr);
-    return bytes;
-}
 
 size_t scan_temp_bytes(int64_t n) {
     size_t bytes = 0;
@@ -842,23 +997,12 @@ onng_status add_edges_launch(const onng_graph *g, const int32_t *src, const int3
 
 size_t adjust_path_ws(int64_t n, int64_t nnz) {
     Carver c(nullptr);
-    c.take<int32_t>(nnz);          // gp_nb
-    c.take<int32_t>(nnz);          // gp_len (4-byte lengths)
-    c.take<int32_t>(n);            // gp_cnt
-    c.take<int8_t>(n);             // status
-    c.take<int32_t>(n);            // degrees
-    c.take<int32_t>(n);            // order
-    c.take<int32_t>(4);            // undecided counter
-    c.take<unsigned long long>(1 << 20);   // degree histogram (max degree < 2^20)
-    c.take<int64_t>(1 << 20);      // start per degree
-    c.take<int32_t>(1 << 20);      // cursor per degree
-    c.take<int64_t>(n + 1);        // out counts
+    c.take<int8_t>(nnz);                // status per edge
+    c.take<int32_t>(n);                 // undecided edges per node
+    for (int i = 0; i < 2 * PA_CLASSES; i++) c.take<int32_t>(n);   // node lists, this and next pass
+    c.take<unsigned long long>(4);      // list lengths, edges left
+    c.take<int64_t>(n + 1);             // kept edges per node
     c.take<char>(scan_temp_bytes(n + 1));
-    c.take<int32_t>(nnz);          // edge index
-    c.take<int32_t>(nnz);          // ids sorted per node
-    c.take<int32_t>(nnz);          // their edge index
-    c.take<int8_t>(nnz);           // kept flag per edge
-    c.take<char>(segsort_temp_bytes(nnz, n));
     return c.size() + 256;
 }
 
@@ -867,93 +1011,66 @@ static onng_status adjust_path_impl(const onng_graph *g, int64_t *out_off, int32
                                     LenT *out_len, int64_t *nnz_out, void *ws, hipStream_t st) {
     const int64_t n = g->n, nnz = g->nnz;
     const LenT *lens = static_cast<const LenT *>(g->lens);
-    constexpr int MAXD = 1 << 20;
     Carver c(ws);
-    int32_t *gp_nb = c.take<int32_t>(nnz);
-    LenT *gp_len = reinterpret_cast<LenT *>(c.take<int32_t>(nnz));
-    int32_t *gp_cnt = c.take<int32_t>(n);
-    int8_t *status = c.take<int8_t>(n);
-    int32_t *deg = c.take<int32_t>(n);
-    int32_t *order = c.take<int32_t>(n);
-    int32_t *undecided = c.take<int32_t>(4);
-    unsigned long long *hist = c.take<unsigned long long>(MAXD);
-    int64_t *start = c.take<int64_t>(MAXD);
-    int32_t *cursor = c.take<int32_t>(MAXD);
-    int64_t *ocnt = c.take<int64_t>(n + 1);
+    int8_t *status = c.take<int8_t>(nnz);
+    int32_t *left = c.take<int32_t>(n);
+    int32_t *lists[2][PA_CLASSES];
+    for (auto &side : lists)
+        for (int32_t *&l : side) l = c.take<int32_t>(n);
+    unsigned long long *counters = c.take<unsigned long long>(4);
+    int64_t *kept = c.take<int64_t>(n + 1);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
-    int32_t *eidx = c.take<int32_t>(nnz);
-    int32_t *sid_nb = c.take<int32_t>(nnz);
-    int32_t *sid_e = c.take<int32_t>(nnz);
-    int8_t *kept = c.take<int8_t>(nnz);
-    size_t sb = segsort_temp_bytes(nnz, n);
-    void *stmp = c.take<char>(sb);
-    // every node's edges sorted by id, for the witness lookups
-    ONNG_HIP(hipMemsetAsync(kept, 0, (size_t)nnz, st));
-    if (nnz > 0) {
-        hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(nnz, 256)), dim3(256), 0, st, nnz, eidx);
-        ONNG_HIP(hipcub::DeviceSegmentedRadixSort::SortPairs(
-            stmp, sb, g->nbrs, sid_nb, eidx, sid_e, (int)nnz, (int)n, g->offsets, g->offsets + 1,
-            0, 32, st));
+    ONNG_HIP(hipMemsetAsync(status, ST_UNDECIDED, (size_t)nnz, st));
+    ONNG_HIP(hipMemsetAsync(kept, 0, sizeof(int64_t) * (n + 1), st));
+    ONNG_HIP(hipMemsetAsync(counters, 0, sizeof(unsigned long long) * 4, st));
+    unsigned long long h[4] = {0, 0, 0, 0};
+    if (n > 0) {
+        hipLaunchKernelGGL((pa_list_kernel<true>), dim3(blocks_for(n, 256)), dim3(256), 0, st,
+                           g->offsets, nullptr, n, left, lists[0][0], lists[0][1], lists[0][2],
+                           counters);
+        ONNG_HIP(hipMemcpyAsync(h, counters, sizeof(h), hipMemcpyDeviceToHost, st));
+        ONNG_HIP(hipStreamSynchronize(st));
     }
-
-    ONNG_HIP(hipMemsetAsync(gp_cnt, 0, sizeof(int32_t) * n, st));
-    ONNG_HIP(hipMemsetAsync(hist, 0, sizeof(unsigned long long) * MAXD, st));
-    ONNG_HIP(hipMemsetAsync(cursor, 0, sizeof(int32_t) * MAXD, st));
-    hipLaunchKernelGGL(degree_hist_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, g->offsets,
-                       n, deg, hist);
-    std::vector<unsigned long long> h(MAXD);
-    ONNG_HIP(hipMemcpyAsync(h.data(), hist, sizeof(unsigned long long) * MAXD,
-                            hipMemcpyDeviceToHost, st));
-    ONNG_HIP(hipStreamSynchronize(st));
-    if (h[MAXD - 1]) {
+    if (h[3]) {
         set_error("onng_adjust_path: a node has 2^20 - 1 or more edges");
         return ONNG_ERR_UNSUPPORTED;
     }
-    int maxdeg = 0;
-    for (int d = 0; d < MAXD; d++)
-        if (h[d]) maxdeg = d;
-    // start[d] = number of nodes with degree > d; active(j) = start[j] nodes
-    std::vector<int64_t> s(MAXD, 0);
-    int64_t acc = 0;
-    for (int d = maxdeg; d >= 0; d--) {
-        s[d] = acc;
-        acc += (int64_t)h[d];
-    }
-    ONNG_HIP(hipMemcpyAsync(start, s.data(), sizeof(int64_t) * (maxdeg + 1), hipMemcpyHostToDevice,
-                            st));
-    hipLaunchKernelGGL(order_by_degree_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, deg, n,
-                       start, cursor, order);
-    for (int j = 0; j < maxdeg; j++) {
-        int64_t n_act = s[j];    // nodes with degree > j
-        if (n_act == 0) break;
-        hipLaunchKernelGGL((pa_jacobi_kernel<LenT>), dim3(blocks_for(n_act * WAVE, 256)),
-                           dim3(256), 0, st, g->offsets, g->nbrs, lens, order, n_act, j, gp_nb,
-                           gp_cnt, sid_nb, sid_e, kept, status);
-        for (int it = 0;; it++) {
-            ONNG_HIP(hipMemsetAsync(undecided, 0, sizeof(int32_t), st));
-            hipLaunchKernelGGL((pa_settle_kernel<LenT>), dim3(blocks_for(n_act, 256)), dim3(256),
-                               0, st, g->offsets, g->nbrs, lens, order, n_act, j, gp_nb, gp_cnt,
-                               status, undecided);
-            int32_t und = 0;
-            ONNG_HIP(hipMemcpyAsync(&und, undecided, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-            ONNG_HIP(hipStreamSynchronize(st));
-            if (und == 0) break;
-            if (it > n_act + 2) {
-                set_error("onng_adjust_path: same-round dependences did not settle");
-                return ONNG_ERR_DEVICE;
-            }
+    unsigned long long before = (unsigned long long)nnz + 1;
+    for (int side = 0; h[0] + h[1] + h[2] > 0; side ^= 1) {
+        ONNG_HIP(hipMemsetAsync(counters, 0, sizeof(unsigned long long) * 4, st));
+        // the longest lists first: their blocks run longest
+        if (h[2])
+            hipLaunchKernelGGL((pa_pass_kernel<LenT, 16, PA_CAP2, 4 * PA_CAP2>),
+                               dim3((unsigned)h[2]), dim3(1024), 0, st, g->offsets, g->nbrs, lens,
+                               n, lists[side][2], (int64_t)h[2], status, left, kept);
+        if (h[1])
+            hipLaunchKernelGGL((pa_pass_kernel<LenT, 4, PA_CAP1, 4 * PA_CAP1>),
+                               dim3((unsigned)h[1]), dim3(256), 0, st, g->offsets, g->nbrs, lens,
+                               n, lists[side][1], (int64_t)h[1], status, left, kept);
+        if (h[0])
+            hipLaunchKernelGGL((pa_pass_kernel<LenT, 1, PA_CAP0, 4 * PA_CAP0>),
+                               dim3(blocks_for((int64_t)h[0], 4)), dim3(256), 0, st, g->offsets,
+                               g->nbrs, lens, n, lists[side][0], (int64_t)h[0], status, left, kept);
+        for (int k = 0; k < PA_CLASSES; k++)
+            if (h[k])
+                hipLaunchKernelGGL((pa_list_kernel<false>), dim3(blocks_for((int64_t)h[k], 256)),
+                                   dim3(256), 0, st, g->offsets, lists[side][k], (int64_t)h[k],
+                                   left, lists[side ^ 1][0], lists[side ^ 1][1],
+                                   lists[side ^ 1][2], counters);
+        ONNG_HIP(hipGetLastError());
+        ONNG_HIP(hipMemcpyAsync(h, counters, sizeof(h), hipMemcpyDeviceToHost, st));
+        ONNG_HIP(hipStreamSynchronize(st));
+        if (h[3] >= before) {
+            set_error("onng_adjust_path: a pass decided no edge");
+            return ONNG_ERR_DEVICE;
         }
-        hipLaunchKernelGGL((pa_apply_kernel<LenT>), dim3(blocks_for(n_act, 256)), dim3(256), 0, st,
-                           g->offsets, g->nbrs, lens, order, n_act, j, gp_nb, gp_len, gp_cnt,
-                           status, kept);
+        before = h[3];
     }
-    hipLaunchKernelGGL(cnt_to_i64_kernel, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, gp_cnt,
-                       n, ocnt);
-    ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, ocnt, out_off, (int)(n + 1), st));
+    ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, kept, out_off, (int)(n + 1), st));
     if (n > 0)
-        hipLaunchKernelGGL((pa_compact_kernel<LenT>), dim3((unsigned)n), dim3(64), 0, st,
-                           g->offsets, out_off, n, gp_nb, gp_len, out_nb, out_len);
+        hipLaunchKernelGGL((pa_compact_kernel<LenT>), dim3(blocks_for(n, 4)), dim3(256), 0, st,
+                           g->offsets, out_off, n, g->nbrs, lens, status, out_nb, out_len);
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipMemcpyAsync(nnz_out, out_off + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     ONNG_HIP(hipStreamSynchronize(st));
