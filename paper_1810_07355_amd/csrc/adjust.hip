@@ -236,271 +236,283 @@ __global__ void __launch_bounds__(256) sac_select_kernel(
 // Statuses only ever become decided and a stale read (another node's write of
 // the same pass not seen) reads "undecided", so the passes need no order
 // among nodes.  The first undecided edge in (j, v) order is decided by every
-// pass; in practice 6 to 9 passes decide all of them (200,003 x 100 cosine
+// pass; in practice about ten passes decide all of them (200,003 x 100 cosine
 // rows: 13.5M edges, longest list 2,734).
 //
-// A group of waves takes a node: the undecided targets of its list go into a
-// hash table in LDS, and the lists of its own not yet removed neighbours
-// stream past it, coalesced, the next one's load in flight.  What bounds it is
-// that chain (one list per step, most lists one 64-lane load) times the waves
-// in flight, not the bytes.  The earlier form ran one round per rank (as many
-// as the longest list, each with a same-round settling pass and a host
-// synchronisation) with a binary search per kept neighbour.
+// A work item is up to CAP consecutive targets of one node's list: its
+// undecided targets go into a hash table in LDS, and the lists of the node's
+// not yet removed neighbours stream past it, coalesced, the next one's load in
+// flight.  Lists of at most 128 are one item of one wave, in rank order, so an
+// edge kept by this very pass already serves as a witness; longer lists are
+// cut into items of 512 targets, each taken by four waves in no order, which
+// count only edges decided before.  What bounds it is the LDS probing and the
+// chain of one list per step, not the bytes (those 13.5M edges: 11.7 ms; with
+// one table and one block size per class of list length, in three launches
+// a pass, 15.2 ms).  The earlier form ran one round per rank (as many as the
+// longest list, each with a same-round settling pass and a host
+// synchronisation) with a binary search per kept neighbour: 458 ms.
 
 constexpr int8_t ST_UNDECIDED = 0, ST_KEPT = 1, ST_REMOVED = 2;
-constexpr int PA_CLASSES = 3;          // node classes by list length, below
 constexpr int64_t PA_MAX_DEGREE = (1 << 20) - 1;   // longer lists are refused
+constexpr int PA_SMALL = 128;          // longest list that one wave takes
+constexpr int PA_CHUNK = 512;          // targets per item of a longer list
+constexpr uint32_t PA_EMPTY = 0xFFFFFFFFu;   // no node id (ids are below 2^31)
 
-// Class 0 (lists of at most 128): one wave per node, four nodes per block;
-// class 1 (at most 512): four waves per node; class 2: sixteen.  A table
-// covers CAP targets of the list at a time (class 2 lists may be longer: the
-// targets are then taken CAP at a time, in rank order) in HSZ >= 4 CAP slots,
-// so that probe runs stay short.
-constexpr int PA_CAP0 = 128, PA_CAP1 = 512, PA_CAP2 = 2048;
-
-__host__ __device__ inline int pa_class(int64_t deg) {
-    return deg <= PA_CAP0 ? 0 : deg <= PA_CAP1 ? 1 : 2;
-}
-
-template <typename LenT, int CAP, int HSZ>
+// The hash table has four slots per target, so that probe runs stay short; a
+// repeated id takes several slots, and only then (dup) a lookup goes on past
+// its first match.
+template <typename LenT, int CAP, typename RankT>
 struct PaTable {
-    int64_t cbeg[CAP];     // start and length of each target's own list
-    int32_t clen[CAP];
-    int32_t nb[CAP];
+    static constexpr int HSZ = 4 * CAP;
+    uint32_t hid[HSZ];
+    RankT hrank[HSZ];
     LenT len[CAP];
-    uint32_t hid[HSZ];     // open addressing; a repeated id takes several slots
-    uint16_t hrank[HSZ];
     uint8_t st[CAP];       // status before this pass
     uint8_t rem[CAP];      // a witness pair is kept
     uint8_t pend[CAP];     // a witness pair is not yet decided
-    int32_t last;          // last undecided rank within the chunk
-    int32_t left, kept;    // undecided / kept edges of the node
+    int32_t last;          // last undecided rank within the item
+    int32_t dup;
+    int32_t left, kept;    // targets still undecided, targets kept by this pass
+    static __device__ uint32_t slot(uint32_t id) { return (id * 2654435761u) >> (32 - __builtin_ctz(HSZ)); }
+    static __device__ uint32_t next(uint32_t h) { return (h + 1) & (HSZ - 1); }
 };
-
-constexpr uint32_t PA_EMPTY = 0xFFFFFFFFu;   // no node id (ids are below 2^31)
-
-template <int HSZ>
-__device__ __forceinline__ uint32_t pa_hash(uint32_t id) {
-    return (id * 2654435761u) >> (32 - __builtin_ctz(HSZ));
-}
 
 template <typename T>
 __device__ __forceinline__ T ld_relaxed(const T *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// One pass over the nodes of `list`.  With several waves per node the list's
-// neighbours are taken WAVES at a time: an edge decided "kept" only by this
-// pass then counts as undecided for its own pairs unless it is the first of
-// its group (the others' flags may still change while the group runs).
-template <typename LenT, int WAVES, int CAP, int HSZ>
-__global__ void __launch_bounds__(WAVES == 1 ? 256 : WAVES * WAVE)
-pa_pass_kernel(const int64_t *off, const int32_t *nbrs, const LenT *lens, int64_t n,
-               const int32_t *list, int64_t n_list, int8_t *st, int32_t *left, int64_t *kept_cnt) {
-    constexpr int GROUPS = WAVES == 1 ? 4 : 1;   // nodes per block
-    constexpr int NT = WAVES * WAVE;             // threads per node
-    __shared__ PaTable<LenT, CAP, HSZ> tables[GROUPS];
+template <typename LenT>
+struct PaGraph {
+    const int64_t *off;
+    const int32_t *nbrs;
+    const LenT *lens;
+    int64_t n;
+    int8_t *st;            // status per edge
+    int64_t *kept;         // kept edges per node
+};
+
+// One item: targets [t0, t0 + m) of node v, by WAVES waves (this one is w).
+template <typename LenT, int CAP, typename RankT, int WAVES>
+__device__ void pa_item(const PaGraph<LenT> &g, PaTable<LenT, CAP, RankT> &T, int32_t v, int t0,
+                        int w, int32_t *left_at) {
+    typedef PaTable<LenT, CAP, RankT> Table;
+    constexpr int NT = WAVES * WAVE;
     const int lane = lane_id();
-    const int wv = uni(threadIdx.x / WAVE);
-    PaTable<LenT, CAP, HSZ> &T = tables[GROUPS == 1 ? 0 : wv];
-    const int w = WAVES == 1 ? 0 : wv;           // wave within the node's group
-    const int tid = WAVES == 1 ? lane : (int)threadIdx.x;
+    const int tid = w * WAVE + lane;
     auto sync = [&]() {
         if constexpr (WAVES == 1) wave_sync();
         else __syncthreads();
     };
-    // consecutive nodes share neighbours: give each XCD (blocks go to the 8 XCDs
-    // in turn) one run of the list
-    const int64_t nblk = gridDim.x, per = nblk / 8, tail = nblk - per * 8;
-    const int64_t xcd = blockIdx.x % 8, at = blockIdx.x / 8;
-    const int64_t blk = xcd * per + min(xcd, tail) + at;
-    const int64_t gi = GROUPS == 1 ? blk : blk * GROUPS + wv;
-    if (gi >= n_list) return;   // (a whole wave, or a whole block, leaves)
-    const int32_t v = uni(list[gi]);
-    const int64_t b = off[v];
-    const int deg = (int)(off[v + 1] - b);
-    if (tid == 0) T.left = 0, T.kept = 0;
-    for (int t0 = 0; t0 < deg; t0 += CAP) {
-        const int m = min(CAP, deg - t0);
-        sync();
-        for (int i = tid; i < HSZ; i += NT) T.hid[i] = PA_EMPTY;
-        if (tid == 0) T.last = -1;
-        sync();
-        int my_last = -1;
-        for (int i = tid; i < m; i += NT) {
-            const int8_t s = ld_relaxed(&st[b + t0 + i]);
-            const int32_t c = nbrs[b + t0 + i];
-            T.st[i] = (uint8_t)s;
-            T.rem[i] = 0;
-            T.pend[i] = 0;
-            T.nb[i] = c;
-            T.len[i] = lens[b + t0 + i];
-            int64_t cb = 0;
-            int32_t cl = 0;
-            if (s != ST_REMOVED && (uint32_t)c < (uint64_t)n) {
-                cb = off[c];
-                cl = (int32_t)min<int64_t>(off[c + 1] - cb, PA_MAX_DEGREE);
+    const int64_t b = g.off[v];
+    const int m = (int)min<int64_t>(CAP, g.off[v + 1] - b - t0);
+    for (int i = tid; i < Table::HSZ; i += NT) T.hid[i] = PA_EMPTY;
+    if (tid == 0) T.last = -1, T.dup = 0, T.left = 0, T.kept = 0;
+    sync();
+    int my_last = -1;
+    for (int i = tid; i < m; i += NT) {
+        const int8_t s = ld_relaxed(&g.st[b + t0 + i]);
+        T.st[i] = (uint8_t)s;
+        T.rem[i] = 0;
+        T.pend[i] = 0;
+        if (s == ST_UNDECIDED) {
+            const uint32_t c = (uint32_t)g.nbrs[b + t0 + i];
+            T.len[i] = g.lens[b + t0 + i];
+            my_last = i;
+            uint32_t h = Table::slot(c), was;
+            while ((was = atomicCAS(&T.hid[h], PA_EMPTY, c)) != PA_EMPTY) {
+                if (was == c) T.dup = 1;
+                h = Table::next(h);
             }
-            T.cbeg[i] = cb;
-            T.clen[i] = cl;
-            if (s == ST_UNDECIDED) {
-                my_last = i;
-                uint32_t h = pa_hash<HSZ>((uint32_t)c);
-                while (atomicCAS(&T.hid[h], PA_EMPTY, (uint32_t)c) != PA_EMPTY) h = (h + 1) & (HSZ - 1);
-                T.hrank[h] = (uint16_t)i;
+            T.hrank[h] = (RankT)i;
+        }
+    }
+    if (my_last >= 0) atomicMax(&T.last, my_last);
+    sync();
+    const int last = uni(T.last);
+    const bool dup = uni(T.dup) != 0;
+    const int lim = last < 0 ? 0 : t0 + last + 1;   // (c, jc) matters only for jc < lim
+    // ranks below the last undecided target, 64 at a time: their neighbours'
+    // lists are found by the lanes together, then taken one after another
+    for (int ib = w * WAVE; ib < lim - 1; ib += NT) {
+        const int il = ib + lane;
+        int sl = ST_REMOVED;
+        int32_t cl = -1;
+        int64_t cbl = 0;
+        int32_t cnl = 0;
+        if (il < lim - 1) {
+            sl = ld_relaxed(&g.st[b + il]);
+            cl = g.nbrs[b + il];
+            if (sl != ST_REMOVED && (uint32_t)cl < (uint64_t)g.n) {
+                cbl = g.off[cl];
+                cnl = (int32_t)min<int64_t>(g.off[cl + 1] - cbl, lim);
             }
         }
-        if (my_last >= 0) atomicMax(&T.last, my_last);
-        sync();
-        const int last = uni(T.last);
-        const int lim = last < 0 ? 0 : t0 + last + 1;   // ranks that can matter below
-        // the first 64 entries of the next list, read one step ahead
-        auto beg_of = [&](int i, int64_t &cb, int &cl) {
-            if (i >= t0) {
-                cb = (int64_t)uni64((uint64_t)T.cbeg[i - t0]);
-                cl = uni(T.clen[i - t0]);
-            } else {
-                const int32_t c = uni(nbrs[b + i]);
-                cb = 0, cl = 0;
-                if ((uint32_t)c < (uint64_t)n) {
-                    cb = off[c];
-                    cl = (int)min<int64_t>(off[c + 1] - cb, PA_MAX_DEGREE);
-                }
-            }
-            cl = min(cl, lim);   // (c, jc) needs jc <= j < lim
-        };
-        int64_t cb = 0;
-        int cl = 0;
+        uint64_t todo = ballot(cnl > 0);
         int32_t x = 0;
         LenT lx = 0;
-        int8_t sx = ST_REMOVED;
-        auto fetch = [&](int64_t base, int cnt, int jc0) {
+        int sx = ST_REMOVED;
+        auto fetch = [&](int64_t at, int cnt) {
             sx = ST_REMOVED;
-            if (jc0 + lane < cnt) {
-                x = nbrs[base + jc0 + lane];
-                lx = lens[base + jc0 + lane];
-                sx = ld_relaxed(&st[base + jc0 + lane]);
+            if (lane < cnt) {
+                x = g.nbrs[at + lane];
+                lx = g.lens[at + lane];
+                sx = ld_relaxed(&g.st[at + lane]);
             }
         };
-        if (w < lim - 1) {
-            beg_of(w, cb, cl);
-            fetch(cb, cl, 0);
+        if (todo) {
+            const int src = (int)__builtin_ctzll(todo);
+            fetch(readlane64(cbl, src), __builtin_amdgcn_readlane(cnl, src));
         }
-        for (int i0 = 0; i0 < lim - 1; i0 += WAVES) {
-            const int i = i0 + w;
-            // this step's list and the next one's load
-            const int64_t mb = cb;
-            const int ml = cl;
+        while (todo) {
+            const int src = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int i = ib + src;
+            int si = __builtin_amdgcn_readlane(sl, src);
+            const int32_t c = __builtin_amdgcn_readlane(cl, src);
+            const int64_t cb = readlane64(cbl, src);
+            const int cn = __builtin_amdgcn_readlane(cnl, src);
             int32_t y = x;
             LenT ly = lx;
-            int8_t sy = sx;
-            cl = 0;
-            if (i + WAVES < lim - 1) {
-                beg_of(i + WAVES, cb, cl);
-                fetch(cb, cl, 0);
+            int sy = sx;
+            if (todo) {
+                const int nx = (int)__builtin_ctzll(todo);
+                fetch(readlane64(cbl, nx), __builtin_amdgcn_readlane(cnl, nx));
             }
-            // status of (v, i)
-            int si = ST_REMOVED;
-            int32_t c = -1;
-            if (i < lim - 1) {
-                if (i >= t0) {
-                    const int k = i - t0;
-                    c = uni(T.nb[k]);
-                    si = uni((int)T.st[k]);
-                    if (si == ST_UNDECIDED) {
-                        if (uni((int)T.rem[k])) si = ST_REMOVED;
-                        else if (w == 0 && !uni((int)T.pend[k])) si = ST_KEPT;
-                    }
-                } else {
-                    c = uni(nbrs[b + i]);
-                    si = uni((int)ld_relaxed(&st[b + i]));
-                }
+            if (si == ST_UNDECIDED && i >= t0) {
+                if (uni((int)T.rem[i - t0])) continue;
+                // one wave, in rank order: all that could hold it back has run
+                if (WAVES == 1 && !uni((int)T.pend[i - t0])) si = ST_KEPT;
             }
-            if (si != ST_REMOVED) {
-                for (int jc0 = 0; jc0 < ml; jc0 += WAVE) {
-                    if (jc0 > 0) {
-                        sy = ST_REMOVED;
-                        if (jc0 + lane < ml) {
-                            y = nbrs[mb + jc0 + lane];
-                            ly = lens[mb + jc0 + lane];
-                            sy = ld_relaxed(&st[mb + jc0 + lane]);
-                        }
-                    }
-                    if (sy == ST_REMOVED) continue;
+            for (int jc0 = 0;;) {
+                if (sy != ST_REMOVED) {
                     const int jc = jc0 + lane;
-                    const bool both = si == ST_KEPT && sy == ST_KEPT;
-                    uint32_t h = pa_hash<HSZ>((uint32_t)y);
-                    for (uint32_t id; (id = T.hid[h]) != PA_EMPTY; h = (h + 1) & (HSZ - 1)) {
+                    uint32_t h = Table::slot((uint32_t)y);
+                    for (uint32_t id; (id = T.hid[h]) != PA_EMPTY; h = Table::next(h)) {
                         if (id != (uint32_t)y) continue;
                         const int k = T.hrank[h];
                         const int j = t0 + k;
                         if (j > i && (jc < j || (jc == j && c < v)) && ly < T.len[k]) {
-                            if (both) T.rem[k] = 1;
+                            if (si == ST_KEPT && sy == ST_KEPT) T.rem[k] = 1;
                             else T.pend[k] = 1;
                         }
+                        if (!dup) break;
                     }
                 }
+                jc0 += WAVE;
+                if (jc0 >= cn) break;
+                sy = ST_REMOVED;
+                if (jc0 + lane < cn) {
+                    y = g.nbrs[cb + jc0 + lane];
+                    ly = g.lens[cb + jc0 + lane];
+                    sy = ld_relaxed(&g.st[cb + jc0 + lane]);
+                }
             }
-            sync();   // this step's flags before the next step's status
+            if constexpr (WAVES == 1) wave_sync();   // this step's flags before the next status
         }
-        // decisions of this chunk
-        sync();
-        int nl = 0, nk = 0;
-        for (int i = tid; i < m; i += NT) {
-            int s = T.st[i];
-            if (s == ST_UNDECIDED) {
-                s = T.rem[i] ? ST_REMOVED : T.pend[i] ? ST_UNDECIDED : ST_KEPT;
-                if (s != ST_UNDECIDED)
-                    __hip_atomic_store(&st[b + t0 + i], (int8_t)s, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            nl += s == ST_UNDECIDED;
-            nk += s == ST_KEPT;
-        }
-        if (nl) atomicAdd(&T.left, nl);
-        if (nk) atomicAdd(&T.kept, nk);
     }
     sync();
+    int nl = 0, nk = 0;
+    for (int i = tid; i < m; i += NT) {
+        if (T.st[i] != ST_UNDECIDED) continue;
+        const int8_t s = T.rem[i] ? ST_REMOVED : T.pend[i] ? ST_UNDECIDED : ST_KEPT;
+        if (s != ST_UNDECIDED)
+            __hip_atomic_store(&g.st[b + t0 + i], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        nl += s == ST_UNDECIDED;
+        nk += s == ST_KEPT;
+    }
+    if (nl) atomicAdd(&T.left, nl);
+    if (nk) atomicAdd(&T.kept, nk);
+    sync();
     if (tid == 0) {
-        left[v] = T.left;
-        kept_cnt[v] = T.kept;
+        *left_at = T.left;
+        if (T.kept) atomicAdd((unsigned long long *)&g.kept[v], (unsigned long long)T.kept);
     }
 }
 
-// The lists of nodes that still have undecided edges, per class (counters[0..2]
-// their lengths, counters[3] the edges left).  FIRST: from all nodes, with
-// left = the list length; counters[3] then counts lists that are too long.
-template <bool FIRST>
-__global__ void __launch_bounds__(256) pa_list_kernel(const int64_t *off, const int32_t *from,
-                                                      int64_t count, int32_t *left,
-                                                      int32_t *l0, int32_t *l1, int32_t *l2,
+// One pass: the first n_big blocks take one item (node << 32 | chunk) of a
+// long list each (they run longest), the others four short lists.
+template <typename LenT>
+__global__ void __launch_bounds__(256) pa_pass_kernel(PaGraph<LenT> g, const int64_t *big,
+                                                      int64_t n_big, const int32_t *small,
+                                                      int64_t n_small, int32_t *left_big,
+                                                      int32_t *left_small) {
+    typedef PaTable<LenT, PA_SMALL, uint8_t> SmallT;
+    typedef PaTable<LenT, PA_CHUNK, uint16_t> BigT;
+    __shared__ union {
+        char small[4 * sizeof(SmallT)];
+        char big[sizeof(BigT)];
+    } lds;
+    static_assert(alignof(SmallT) == 4 && alignof(BigT) == 4 && sizeof(SmallT) % 4 == 0, "LDS layout");
+    const int wv = uni(threadIdx.x / WAVE);
+    if (blockIdx.x < n_big) {
+        const int64_t it = (int64_t)uni64((uint64_t)big[blockIdx.x]);
+        pa_item<LenT, PA_CHUNK, uint16_t, 4>(g, *reinterpret_cast<BigT *>(lds.big),
+                                             (int32_t)(it >> 32), (int)(uint32_t)it * PA_CHUNK, wv,
+                                             left_big + blockIdx.x);
+        return;
+    }
+    // consecutive nodes share neighbours: give each XCD (blocks go to the 8 XCDs
+    // in turn) one run of the list
+    const int64_t nblk = gridDim.x - n_big, per = nblk / 8, rest = nblk - per * 8;
+    const int64_t xcd = (blockIdx.x - n_big) % 8, at = (blockIdx.x - n_big) / 8;
+    const int64_t gi = (xcd * per + min(xcd, rest) + at) * 4 + wv;
+    if (gi >= n_small) return;
+    pa_item<LenT, PA_SMALL, uint8_t, 1>(g, reinterpret_cast<SmallT *>(lds.small)[wv],
+                                        uni(small[gi]), 0, 0, left_small + gi);
+}
+
+// The first pass's items, all lists: counters[0] short lists, counters[1]
+// items of longer ones, counters[3] lists that are too long.
+__global__ void __launch_bounds__(256) pa_items_kernel(const int64_t *off, int64_t n,
+                                                       int32_t *small, int64_t *big,
+                                                       unsigned long long *counters) {
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t deg = v < n ? off[v + 1] - off[v] : 0;
+    const bool sm = deg > 0 && deg <= PA_SMALL;
+    const uint64_t m = ballot(sm);
+    if (m) {
+        const int lead = (int)__builtin_ctzll(m);
+        uint64_t at = 0;
+        if (lane_id() == lead) at = atomicAdd(&counters[0], (unsigned long long)__popcll(m));
+        at = shfl64(at, lead);
+        if (sm) small[at + mbcnt(m)] = (int32_t)v;
+    }
+    if (deg > PA_SMALL) {
+        if (deg >= PA_MAX_DEGREE) {
+            atomicAdd(&counters[3], 1ull);
+            return;
+        }
+        const int nc = (int)((deg + PA_CHUNK - 1) / PA_CHUNK);
+        const unsigned long long at = atomicAdd(&counters[1], (unsigned long long)nc);
+        for (int c = 0; c < nc; c++) big[at + c] = v << 32 | c;
+    }
+}
+
+// The next pass's items: those with targets left; counters[2] the targets.
+// The first `sb` blocks take the short lists.
+__global__ void __launch_bounds__(256) pa_next_kernel(const int32_t *small, int64_t n_small,
+                                                      const int32_t *left_small, int64_t sb,
+                                                      const int64_t *big, int64_t n_big,
+                                                      const int32_t *left_big, int32_t *next_small,
+                                                      int64_t *next_big,
                                                       unsigned long long *counters) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = lane_id();
-    int cls = -1;
-    int32_t v = 0;
-    int64_t todo = 0;
-    if (i < count) {
-        v = FIRST ? (int32_t)i : from[i];
-        const int64_t deg = off[v + 1] - off[v];
-        todo = FIRST ? deg : left[v];
-        if (todo > 0) cls = pa_class(deg);
-        if (FIRST && deg >= PA_MAX_DEGREE) atomicAdd(&counters[3], 1ull);
+    const bool is_big = blockIdx.x >= sb;
+    const int64_t i = (int64_t)(blockIdx.x - (is_big ? sb : 0)) * blockDim.x + threadIdx.x;
+    const int64_t cnt = is_big ? n_big : n_small;
+    int left = i < cnt ? (is_big ? left_big : left_small)[i] : 0;
+    const uint64_t m = ballot(left > 0);
+    if (!m) return;
+    const int lead = (int)__builtin_ctzll(m);
+    uint64_t at = 0;
+    if (lane_id() == lead) at = atomicAdd(&counters[is_big], (unsigned long long)__popcll(m));
+    at = shfl64(at, lead);
+    if (left > 0) {
+        if (is_big) next_big[at + mbcnt(m)] = big[i];
+        else next_small[at + mbcnt(m)] = small[i];
     }
-#pragma unroll
-    for (int c = 0; c < PA_CLASSES; c++) {
-        const uint64_t m = ballot(cls == c);
-        if (!m) continue;
-        unsigned long long at = 0;
-        if (lane == (int)__builtin_ctzll(m)) at = atomicAdd(&counters[c], (unsigned long long)__popcll(m));
-        at = (unsigned long long)shfl64(at, (int)__builtin_ctzll(m));
-        if (cls == c) (c == 0 ? l0 : c == 1 ? l1 : l2)[at + mbcnt(m)] = v;
-    }
-    if (!FIRST) {
-        int t = (int)todo;
-        for (int s = 32; s >= 1; s >>= 1) t += __shfl_xor(t, s);
-        if (lane == 0 && t) atomicAdd(&counters[3], (unsigned long long)t);
-    }
+    for (int s = 32; s >= 1; s >>= 1) left += __shfl_xor(left, s);
+    if (lane_id() == lead) atomicAdd(&counters[2], (unsigned long long)left);
 }
 
 // kept edges of every node, in list order (one wave per node)
@@ -995,12 +1007,20 @@ onng_status add_edges_launch(const onng_graph *g, const int32_t *src, const int3
                                  static_cast<float *>(out_len), nnz_cap, nnz_out, ws, st);
 }
 
+// items of lists longer than PA_SMALL: ceil(deg / PA_CHUNK) of each
+static int64_t pa_big_cap(int64_t nnz) { return nnz / PA_SMALL + nnz / PA_CHUNK + 1; }
+
 size_t adjust_path_ws(int64_t n, int64_t nnz) {
+    const int64_t nb = pa_big_cap(nnz);
     Carver c(nullptr);
     c.take<int8_t>(nnz);                // status per edge
-    c.take<int32_t>(n);                 // undecided edges per node
-    for (int i = 0; i < 2 * PA_CLASSES; i++) c.take<int32_t>(n);   // node lists, this and next pass
-    c.take<unsigned long long>(4);      // list lengths, edges left
+    c.take<int32_t>(n);                 // short lists, this and the next pass
+    c.take<int32_t>(n);
+    c.take<int64_t>(nb);                // items of long lists, likewise
+    c.take<int64_t>(nb);
+    c.take<int32_t>(n);                 // undecided targets per short list
+    c.take<int32_t>(nb);                // ... per item of a long list
+    c.take<unsigned long long>(4);      // counters
     c.take<int64_t>(n + 1);             // kept edges per node
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
@@ -1009,26 +1029,28 @@ size_t adjust_path_ws(int64_t n, int64_t nnz) {
 template <typename LenT>
 static onng_status adjust_path_impl(const onng_graph *g, int64_t *out_off, int32_t *out_nb,
                                     LenT *out_len, int64_t *nnz_out, void *ws, hipStream_t st) {
-    const int64_t n = g->n, nnz = g->nnz;
+    const int64_t n = g->n, nnz = g->nnz, nb = pa_big_cap(nnz);
     const LenT *lens = static_cast<const LenT *>(g->lens);
     Carver c(ws);
     int8_t *status = c.take<int8_t>(nnz);
-    int32_t *left = c.take<int32_t>(n);
-    int32_t *lists[2][PA_CLASSES];
-    for (auto &side : lists)
-        for (int32_t *&l : side) l = c.take<int32_t>(n);
+    int32_t *small[2];
+    int64_t *big[2];
+    for (int32_t *&l : small) l = c.take<int32_t>(n);
+    for (int64_t *&l : big) l = c.take<int64_t>(nb);
+    int32_t *left_small = c.take<int32_t>(n);
+    int32_t *left_big = c.take<int32_t>(nb);
     unsigned long long *counters = c.take<unsigned long long>(4);
     int64_t *kept = c.take<int64_t>(n + 1);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
+    const PaGraph<LenT> pg{g->offsets, g->nbrs, lens, n, status, kept};
     ONNG_HIP(hipMemsetAsync(status, ST_UNDECIDED, (size_t)nnz, st));
     ONNG_HIP(hipMemsetAsync(kept, 0, sizeof(int64_t) * (n + 1), st));
     ONNG_HIP(hipMemsetAsync(counters, 0, sizeof(unsigned long long) * 4, st));
     unsigned long long h[4] = {0, 0, 0, 0};
     if (n > 0) {
-        hipLaunchKernelGGL((pa_list_kernel<true>), dim3(blocks_for(n, 256)), dim3(256), 0, st,
-                           g->offsets, nullptr, n, left, lists[0][0], lists[0][1], lists[0][2],
-                           counters);
+        hipLaunchKernelGGL(pa_items_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, g->offsets,
+                           n, small[0], big[0], counters);
         ONNG_HIP(hipMemcpyAsync(h, counters, sizeof(h), hipMemcpyDeviceToHost, st));
         ONNG_HIP(hipStreamSynchronize(st));
     }
@@ -1037,35 +1059,24 @@ static onng_status adjust_path_impl(const onng_graph *g, int64_t *out_off, int32
         return ONNG_ERR_UNSUPPORTED;
     }
     unsigned long long before = (unsigned long long)nnz + 1;
-    for (int side = 0; h[0] + h[1] + h[2] > 0; side ^= 1) {
+    for (int side = 0; h[0] + h[1] > 0; side ^= 1) {
+        const int64_t ns = (int64_t)h[0], nbig = (int64_t)h[1];
         ONNG_HIP(hipMemsetAsync(counters, 0, sizeof(unsigned long long) * 4, st));
-        // the longest lists first: their blocks run longest
-        if (h[2])
-            hipLaunchKernelGGL((pa_pass_kernel<LenT, 16, PA_CAP2, 4 * PA_CAP2>),
-                               dim3((unsigned)h[2]), dim3(1024), 0, st, g->offsets, g->nbrs, lens,
-                               n, lists[side][2], (int64_t)h[2], status, left, kept);
-        if (h[1])
-            hipLaunchKernelGGL((pa_pass_kernel<LenT, 4, PA_CAP1, 4 * PA_CAP1>),
-                               dim3((unsigned)h[1]), dim3(256), 0, st, g->offsets, g->nbrs, lens,
-                               n, lists[side][1], (int64_t)h[1], status, left, kept);
-        if (h[0])
-            hipLaunchKernelGGL((pa_pass_kernel<LenT, 1, PA_CAP0, 4 * PA_CAP0>),
-                               dim3(blocks_for((int64_t)h[0], 4)), dim3(256), 0, st, g->offsets,
-                               g->nbrs, lens, n, lists[side][0], (int64_t)h[0], status, left, kept);
-        for (int k = 0; k < PA_CLASSES; k++)
-            if (h[k])
-                hipLaunchKernelGGL((pa_list_kernel<false>), dim3(blocks_for((int64_t)h[k], 256)),
-                                   dim3(256), 0, st, g->offsets, lists[side][k], (int64_t)h[k],
-                                   left, lists[side ^ 1][0], lists[side ^ 1][1],
-                                   lists[side ^ 1][2], counters);
+        hipLaunchKernelGGL((pa_pass_kernel<LenT>), dim3((unsigned)nbig + blocks_for(ns, 4)),
+                           dim3(256), 0, st, pg, big[side], nbig, small[side], ns, left_big,
+                           left_small);
+        const unsigned sb = blocks_for(ns, 256);
+        hipLaunchKernelGGL(pa_next_kernel, dim3(sb + blocks_for(nbig, 256)), dim3(256), 0, st,
+                           small[side], ns, left_small, (int64_t)sb, big[side], nbig, left_big,
+                           small[side ^ 1], big[side ^ 1], counters);
         ONNG_HIP(hipGetLastError());
         ONNG_HIP(hipMemcpyAsync(h, counters, sizeof(h), hipMemcpyDeviceToHost, st));
         ONNG_HIP(hipStreamSynchronize(st));
-        if (h[3] >= before) {
+        if (h[2] >= before) {
             set_error("onng_adjust_path: a pass decided no edge");
             return ONNG_ERR_DEVICE;
         }
-        before = h[3];
+        before = h[2];
     }
     ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, kept, out_off, (int)(n + 1), st));
     if (n > 0)
