@@ -33,97 +33,303 @@ __device__ __forceinline__ uint32_t len_ord(LenT v) {
 // ascending, then p): the reverse copy when the far end has the smaller id,
 // and it keeps that copy's length.
 
+// Every reverse candidate (o, m) goes to o's segment first, m's forward edges
+// are its own row, and one wave per node then drops the reverse copies of its
+// forward edges.  Whether m -> o repeats a forward edge of o is thus decided
+// next to both lists; looked up instead in row o for every candidate, twice
+// (count, then scatter), one lane per row, it was 17 of the 19 ms that
+// 200,003 rows of 100 took (e_o = 20, e_i = 60; now 1.06 ms, of which the
+// scattered 8-byte keys are 0.23 and the merge 0.25).
+
 __device__ __forceinline__ int row_len(const int32_t *row, int k) {
     int l = 0;
     while (l < k && row[l] >= 0) l++;
     return l;
 }
 
-// position of `x` among the first `lim` ids of `row`, or -1
-__device__ __forceinline__ int find_in(const int32_t *row, int lim, int32_t x) {
-    for (int t = 0; t < lim; t++)
-        if (row[t] == x) return t;
-    return -1;
+// Node of a wave: blocks go to the 8 XCDs in turn, so each XCD takes one run of
+// consecutive nodes, whose rows share neighbours (and so segment lines).
+__device__ __forceinline__ int64_t xcd_node(int64_t n) {
+    const int64_t nblk = gridDim.x, per = nblk / 8, rest = nblk - per * 8;
+    const int64_t xcd = blockIdx.x % 8, at = blockIdx.x / 8;
+    const int64_t v = (xcd * per + min(xcd, rest) + at) * (blockDim.x / WAVE) + uni(threadIdx.x / WAVE);
+    return v < n ? v : -1;
 }
 
-__global__ void sa_count_kernel(const int32_t *knn, int64_t n, int k, int eo, int ei,
-                                int64_t *count) {
-    int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n) return;
-    const int32_t *row = knn + m * k;
-    int len = row_len(row, k);
-    atomicAdd((unsigned long long *)&count[m], (unsigned long long)min(eo, len));
-    int lim = min(ei, len);
-    for (int t = 0; t < lim; t++) {
-        int32_t o = row[t];
-        if (o >= n) continue;
-        const int32_t *orow = knn + (int64_t)o * k;
-        int olen = row_len(orow, k);
-        // reverse edge o -> m, unless m is already a forward edge of o
-        if (find_in(orow, min(eo, olen), (int32_t)m) < 0)
-            atomicAdd((unsigned long long *)&count[o], 1ull);
-    }
-}
+// Row m (first max(eo, ei) entries, up to its padding): its forward count, and
+// for each reverse candidate its place among those of the target.  A block
+// takes SA_ROWS consecutive rows, which share targets (the rows are in
+// locality order): it counts them per target in a hash table in LDS and asks
+// the target's global counter for one range per block.  One global atomic per
+// candidate ran at 21G a second, 0.58 ms for 12M candidates; per block and
+// target, 0.26 ms.
+constexpr int SA_WAVES = 8, SA_RPW = 16, SA_ROWS = SA_WAVES * SA_RPW;   // rows per wave, block
+// Slots of the table: neighbouring rows share most targets.  A target that
+// finds no place within SA_PROBES slots (unordered rows: up to 8192 distinct
+// ones) goes to the global counter directly.
+constexpr int SA_HASH = 4096, SA_PROBES = 8;
 
-template <typename LenT>
-__global__ void sa_scatter_kernel(const int32_t *knn, const LenT *kd, int64_t n, int k, int eo,
-                                  int ei, const int64_t *off, int32_t *cursor, uint64_t *keys) {
-    int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n) return;
-    const int32_t *row = knn + m * k;
-    int len = row_len(row, k);
-    // forward edges of m
-    int fwd = min(eo, len);
-    for (int t = 0; t < fwd; t++) {
-        int32_t nn = row[t];
-        LenT l = kd[m * k + t];
-        if (nn < m && nn < n) {
-            // also a reverse edge inserted earlier (while processing nn)?
-            const int32_t *nrow = knn + (int64_t)nn * k;
-            int pos = find_in(nrow, min(ei, row_len(nrow, k)), (int32_t)m);
-            if (pos >= 0) l = kd[(int64_t)nn * k + pos];
-        }
-        keys[off[m] + t] = make_key(len_ord(l), (uint32_t)nn);
-    }
-    // reverse edges o -> m
-    int lim = min(ei, len);
-    for (int t = 0; t < lim; t++) {
-        int32_t o = row[t];
-        if (o >= n) continue;
-        const int32_t *orow = knn + (int64_t)o * k;
-        int olen = row_len(orow, k);
-        if (find_in(orow, min(eo, olen), (int32_t)m) >= 0) continue;   // forward edge of o
-        int ofwd = min(eo, olen);
-        int slot = atomicAdd(&cursor[o], 1);
-        keys[off[o] + ofwd + slot] = make_key(len_ord(kd[m * k + t]), (uint32_t)m);
-    }
-}
-
-// Sort each list by (length, id): rank of every key among the keys of its list.
-template <typename LenT>
-__global__ void __launch_bounds__(256) segment_rank_sort_kernel(const int64_t *off, int64_t n,
-                                                                const uint64_t *keys,
-                                                                int32_t *nbrs, LenT *lens) {
-    extern __shared__ uint64_t sk[];
-    int64_t v = blockIdx.x;
-    if (v >= n) return;
-    int64_t b = off[v], e = off[v + 1];
-    int m = (int)(e - b);
-    const int cap = 4096;
-    const uint64_t *src = keys + b;
-    if (m <= cap) {
-        for (int i = threadIdx.x; i < m; i += blockDim.x) sk[i] = src[i];
+__global__ void __launch_bounds__(SA_WAVES * WAVE) sa_count_kernel(const int32_t *knn, int64_t n,
+                                                                   int k, int eo, int ei,
+                                                                   int32_t *rcnt, int32_t *slot,
+                                                                   int32_t *fcnt) {
+    __shared__ int32_t hid[SA_HASH];   // target, -1 empty
+    __shared__ int32_t hcnt[SA_HASH];  // its candidates in this block, then its range's start
+    const int lane = lane_id();
+    const int64_t m0 = (int64_t)blockIdx.x * SA_ROWS + uni(threadIdx.x / WAVE) * SA_RPW;
+    const int lim = max(eo, ei);
+    int len[SA_RPW];
+#pragma unroll
+    for (int r = 0; r < SA_RPW; r++) len[r] = m0 + r < n ? lim : 0;
+    for (int t0 = 0; t0 < lim; t0 += WAVE) {
         __syncthreads();
-        src = sk;
+        for (int i = threadIdx.x; i < SA_HASH; i += blockDim.x) hid[i] = -1, hcnt[i] = 0;
+        __syncthreads();
+        // per row: this lane's table place (low 16 bits) and its candidate's
+        // number among the block's of that target
+        uint32_t at[SA_RPW];
+#pragma unroll
+        for (int r = 0; r < SA_RPW; r++) {
+            const int t = t0 + lane;
+            const int32_t o = t < len[r] ? knn[(m0 + r) * k + t] : 0;
+            const uint64_t pad = ballot(o < 0);
+            if (pad) len[r] = t0 + (int)__builtin_ctzll(pad);
+            at[r] = ~0u;
+            if (t < min(ei, len[r]) && o < n) {
+                uint32_t h = ((uint32_t)o * 2654435761u) >> (32 - __builtin_ctz(SA_HASH));
+                int p = 0;
+                for (int32_t was; p < SA_PROBES && (was = atomicCAS(&hid[h], -1, o)) != -1 && was != o; p++)
+                    h = (h + 1) & (SA_HASH - 1);
+                if (p < SA_PROBES) at[r] = h | (uint32_t)atomicAdd(&hcnt[h], 1) << 16;
+                else slot[(m0 + r) * ei + t] = atomicAdd(&rcnt[o], 1);
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < SA_HASH; i += blockDim.x)
+            if (hid[i] >= 0) hcnt[i] = atomicAdd(&rcnt[hid[i]], hcnt[i]);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < SA_RPW; r++)
+            if (at[r] != ~0u)
+                slot[(m0 + r) * ei + t0 + lane] = hcnt[at[r] & 0xFFFFu] + (int32_t)(at[r] >> 16);
     }
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        uint64_t x = src[i];
-        int rank = 0;
-        for (int j = 0; j < m; j++) rank += src[j] < x;
-        nbrs[b + rank] = (int32_t)(uint32_t)x;
-        uint32_t lo = (uint32_t)(x >> 32);
-        if constexpr (std::is_integral<LenT>::value) lens[b + rank] = (LenT)lo;
-        else lens[b + rank] = unord_f32(lo);
+#pragma unroll
+    for (int r = 0; r < SA_RPW; r++)
+        if (lane == r && m0 + r < n) fcnt[m0 + r] = min(eo, len[r]);
+}
+
+// segment sizes: reverse candidates and forward edges
+__global__ void sa_sizes_kernel(const int32_t *rcnt, const int32_t *fcnt, int64_t n, int64_t *size) {
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v <= n) size[v] = v < n ? (int64_t)rcnt[v] + fcnt[v] : 0;
+}
+
+template <typename LenT>
+__global__ void __launch_bounds__(256) sa_scatter_kernel(const int32_t *knn, const LenT *kd, int64_t n,
+                                                         int k, int ei, const int64_t *seg,
+                                                         const int32_t *slot, uint64_t *keys) {
+    const int64_t m = xcd_node(n);
+    if (m < 0) return;
+    const int lane = lane_id();
+    const int32_t *row = knn + m * k;
+    int len = ei;
+    for (int t0 = 0; t0 < len; t0 += WAVE) {
+        const int t = t0 + lane;
+        const int32_t o = t < ei ? row[t] : 0;
+        const uint64_t pad = ballot(o < 0);
+        if (pad) len = t0 + (int)__builtin_ctzll(pad);
+        if (t < len && o < n)
+            keys[seg[o] + slot[m * ei + t]] = make_key(len_ord(kd[m * k + t]), (uint32_t)m);
+    }
+}
+
+// Node o's segment: reverse candidates whose id is a forward edge of o go, the
+// forward edges follow the rest (unsorted), and cnt[o] is what remains.  A
+// forward edge to a smaller id takes the dropped copy's length.
+template <typename LenT>
+__global__ void __launch_bounds__(256) sa_merge_kernel(const int32_t *knn, const LenT *kd, int64_t n,
+                                                       int k, const int32_t *rcnt,
+                                                       const int32_t *fcnt, const int64_t *seg,
+                                                       uint64_t *keys, int64_t *cnt) {
+    const int64_t o = xcd_node(n);
+    if (o < 0) return;
+    const int lane = lane_id();
+    uint64_t *s = keys + seg[o];
+    const int f = uni(fcnt[o]), r0 = uni(rcnt[o]);
+    int r = r0;
+    for (int f0 = 0; f0 < f; f0 += WAVE) {
+        const int fn = min(WAVE, f - f0);
+        int32_t id = 0;
+        uint64_t fkey = 0;
+        if (lane < fn) {
+            id = knn[o * k + f0 + lane];
+            fkey = make_key(len_ord(kd[o * k + f0 + lane]), (uint32_t)id);
+        }
+        int kept = 0;
+        for (int c0 = 0; c0 < r; c0 += WAVE) {
+            const bool has = c0 + lane < r;
+            const uint64_t key = has ? s[c0 + lane] : 0;
+            const uint32_t rid = (uint32_t)key;
+            bool drop = false;
+            for (int e = 0; e < fn; e++) {
+                const uint32_t fid = (uint32_t)__builtin_amdgcn_readlane(id, e);
+                const uint64_t hit = ballot(has && rid == fid);
+                if (!hit) continue;
+                drop = drop || ((hit >> lane) & 1);
+                if ((int64_t)fid < o) {
+                    const uint64_t rk = (uint64_t)readlane64((int64_t)key, (int)__builtin_ctzll(hit));
+                    if (lane == e) fkey = rk;
+                }
+            }
+            const uint64_t stay = ballot(has && !drop);
+            if (has && !drop) s[kept + mbcnt(stay)] = key;   // at or before where it was read
+            kept += __popcll(stay);
+        }
+        r = kept;
+        if (lane < fn) s[r0 + f0 + lane] = fkey;
+        // the next 64 forward edges read what other lanes moved
+        if (f0 + WAVE < f) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    }
+    if (r < r0)
+        for (int c = lane; c < f; c += WAVE) {
+            const uint64_t key = s[r0 + c];   // this lane's own store
+            s[r + c] = key;
+        }
+    if (lane == 0) cnt[o] = r + f;
+}
+
+// ------------------------------------------------------------ segment sort --
+// List v: cnt = off[v+1] - off[v] keys at keys[seg[v]] to nbrs/lens at off[v],
+// in ascending order; equal keys keep their order.  A key's place is the
+// number of smaller ones: the list sits in LDS and every lane compares its
+// keys with all of them, read two at a time by broadcast.  Lists of at most
+// 256 take one wave (up to four keys a lane), four lists per block: the places
+// of a list of m keys cost m / 2 broadcasts and 2 m / 64 compares a lane, less
+// than a bitonic network's exchanges there.  Longer ones are queued for blocks
+// of their own, which sort up to 4096 keys in LDS by a bitonic network.
+// (13.5M edges in 200,003 lists, 5,000 of them long: 0.15 + 0.10 ms; the long
+// ones by counting 0.70 ms; one block of 256 threads per list, every place
+// counted, 2.0 ms.)
+
+constexpr int SEG_WAVE = 256;      // longest list of one wave
+constexpr int SEG_LDS = 4096;      // longest list held in LDS
+constexpr int SEG_BLOCKS = 1024;   // blocks that drain the queue of long lists
+
+template <typename LenT>
+__device__ __forceinline__ void seg_put(int32_t *nbrs, LenT *lens, int64_t at, uint64_t key) {
+    nbrs[at] = (int32_t)(uint32_t)key;
+    const uint32_t d = (uint32_t)(key >> 32);
+    if constexpr (std::is_integral<LenT>::value) lens[at] = (LenT)d;
+    else lens[at] = unord_f32(d);
+}
+
+// rank of R keys per lane (index p * 64 + lane) among the m keys of `sk`;
+// TIES: equal keys in index order
+template <int R, bool TIES>
+__device__ __forceinline__ void seg_ranks(const uint64_t *sk, int m, const uint64_t (&key)[R],
+                                          int (&rank)[R]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int p = 0; p < R; p++) rank[p] = 0;
+    for (int j = 0; j < m; j += 2) {   // sk[m] pads an odd count
+        const ulonglong2 o = *reinterpret_cast<const ulonglong2 *>(sk + j);
+#pragma unroll
+        for (int p = 0; p < R; p++) {
+            rank[p] += (uint64_t)o.x < key[p];
+            rank[p] += (uint64_t)o.y < key[p];
+            if (TIES) {
+                rank[p] += (uint64_t)o.x == key[p] && j < p * WAVE + lane;
+                rank[p] += (uint64_t)o.y == key[p] && j + 1 < p * WAVE + lane;
+            }
+        }
+    }
+}
+
+template <typename LenT, int R>
+__device__ __forceinline__ void seg_sort_wave(const uint64_t *src, uint64_t *sk, int m, int64_t b,
+                                              int32_t *nbrs, LenT *lens) {
+    const int lane = lane_id();
+    uint64_t key[R];
+    int rank[R];
+#pragma unroll
+    for (int p = 0; p < R; p++) {
+        const int i = p * WAVE + lane;
+        key[p] = i < m ? src[i] : KEY_MAX;
+        sk[i] = key[p];
+    }
+    if (lane == 0) sk[R * WAVE] = KEY_MAX;
+    wave_sync();
+    seg_ranks<R, false>(sk, m, key, rank);
+    // without equal keys the ranks are 0 .. m-1; with some their sum is smaller
+    int sum = 0;
+#pragma unroll
+    for (int p = 0; p < R; p++) sum += p * WAVE + lane < m ? rank[p] : 0;
+    for (int s = 32; s >= 1; s >>= 1) sum += __shfl_xor(sum, s);
+    if (uni(sum) != m * (m - 1) / 2) seg_ranks<R, true>(sk, m, key, rank);
+#pragma unroll
+    for (int p = 0; p < R; p++)
+        if (p * WAVE + lane < m) seg_put(nbrs, lens, b + rank[p], key[p]);
+}
+
+template <typename LenT>
+__global__ void __launch_bounds__(256) seg_sort_kernel(const int64_t *seg, const int64_t *off,
+                                                       int64_t n, const uint64_t *keys,
+                                                       int32_t *nbrs, LenT *lens, int32_t *queue,
+                                                       int32_t *n_queue) {
+    __shared__ __attribute__((aligned(16))) uint64_t sk_all[4][SEG_WAVE + 2];
+    const int64_t v = xcd_node(n);
+    if (v < 0) return;
+    const int64_t b = off[v], m64 = off[v + 1] - b;
+    if (m64 == 0) return;
+    if (m64 > SEG_WAVE) {
+        if (lane_id() == 0) queue[atomicAdd(n_queue, 1)] = (int32_t)v;
+        return;
+    }
+    const int m = uni((int)m64);
+    const uint64_t *src = keys + seg[v];
+    uint64_t *sk = sk_all[threadIdx.x / WAVE];
+    if (m <= 64) seg_sort_wave<LenT, 1>(src, sk, m, b, nbrs, lens);
+    else if (m <= 128) seg_sort_wave<LenT, 2>(src, sk, m, b, nbrs, lens);
+    else if (m <= 192) seg_sort_wave<LenT, 3>(src, sk, m, b, nbrs, lens);
+    else seg_sort_wave<LenT, 4>(src, sk, m, b, nbrs, lens);
+}
+
+template <typename LenT>
+__global__ void __launch_bounds__(512) seg_sort_long_kernel(const int64_t *seg, const int64_t *off,
+                                                            const uint64_t *keys, int32_t *nbrs,
+                                                            LenT *lens, const int32_t *queue,
+                                                            const int32_t *n_queue) {
+    __shared__ uint64_t sk[SEG_LDS];
+    const int total = *n_queue;
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const int64_t v = queue[q];
+        const int64_t b = off[v], m = off[v + 1] - b;
+        const uint64_t *src = keys + seg[v];
+        __syncthreads();
+        if (m <= SEG_LDS) {
+            // bitonic sort over the next power of two (equal keys are equal
+            // edges, so their order does not matter)
+            const int w = pow2_at_least((int)m);
+            for (int i = threadIdx.x; i < w; i += blockDim.x) sk[i] = i < m ? src[i] : KEY_MAX;
+            for (int size = 2; size <= w; size <<= 1)
+                for (int d = size >> 1; d > 0; d >>= 1) {
+                    __syncthreads();
+                    for (int t = threadIdx.x; t < w / 2; t += blockDim.x) {
+                        const int i = 2 * t - (t & (d - 1));   // lower of the pair (i, i + d)
+                        const uint64_t lo = sk[i], hi = sk[i + d];
+                        if ((lo > hi) == ((i & size) == 0)) sk[i] = hi, sk[i + d] = lo;
+                    }
+                }
+            __syncthreads();
+            for (int i = threadIdx.x; i < m; i += blockDim.x) seg_put(nbrs, lens, b + i, sk[i]);
+        } else {
+            for (int64_t i = threadIdx.x; i < m; i += blockDim.x) {
+                const uint64_t x = src[i];
+                int64_t rank = 0;
+                for (int64_t j = 0; j < m; j++) rank += src[j] < x || (src[j] == x && j < i);
+                seg_put(nbrs, lens, b + rank, x);
+            }
+        }
     }
 }
 
@@ -664,12 +870,30 @@ __global__ void ae_new_kernel(int64_t n, const int32_t *src, const int32_t *dst,
 
 // ------------------------------------------------------------- host side --
 
+// Sorts every list (see seg_sort_kernel); queue: n + 1 ints, its first the
+// queue's length.
+template <typename LenT>
+static void seg_sort(const int64_t *seg, const int64_t *off, int64_t n, const uint64_t *keys,
+                     int32_t *nbrs, LenT *lens, int32_t *queue, hipStream_t st) {
+    if (n == 0) return;
+    (void)hipMemsetAsync(queue, 0, sizeof(int32_t), st);
+    hipLaunchKernelGGL((seg_sort_kernel<LenT>), dim3(blocks_for(n, 4)), dim3(256), 0, st, seg, off,
+                       n, keys, nbrs, lens, queue + 1, queue);
+    hipLaunchKernelGGL((seg_sort_long_kernel<LenT>),
+                       dim3((unsigned)std::min<int64_t>(n, SEG_BLOCKS)), dim3(512), 0, st, seg, off,
+                       keys, nbrs, lens, queue + 1, queue);
+}
+
 size_t adjust_degree_ws(int64_t n, int32_t k, int32_t e_o, int32_t e_i) {
-    int64_t cap = n * (int64_t)(std::min(e_o, k) + std::min(e_i, k));
+    const int64_t eo = std::min(e_o, k), ei = std::min(e_i, k);
     Carver c(nullptr);
-    c.take<int64_t>(n + 1);            // counts / offsets
-    c.take<int32_t>(n);                // cursors
-    c.take<uint64_t>(cap);             // keys
+    c.take<int32_t>(n);                // reverse candidates per node
+    c.take<int32_t>(n);                // forward edges per node
+    c.take<int32_t>(n * ei);           // place of each reverse candidate
+    c.take<int64_t>(n + 1);            // segment sizes, then edges per node
+    c.take<int64_t>(n + 1);            // segment offsets
+    c.take<uint64_t>(n * (eo + ei));   // keys
+    c.take<int32_t>(n + 1);            // long lists
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
 }
@@ -679,18 +903,32 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
                                       int32_t e_o, int32_t e_i, int64_t *offsets, int32_t *nbrs,
                                       LenT *lens, int64_t nnz_cap, int64_t *nnz_out, void *ws,
                                       hipStream_t st) {
-    int eo = std::min(e_o, k), ei = std::min(e_i, k);
-    int64_t cap = n * (int64_t)(eo + ei);
+    const int eo = std::min(e_o, k), ei = std::min(e_i, k);
     Carver c(ws);
+    int32_t *rcnt = c.take<int32_t>(n);
+    int32_t *fcnt = c.take<int32_t>(n);
+    int32_t *slot = c.take<int32_t>(n * (int64_t)ei);
     int64_t *cnt = c.take<int64_t>(n + 1);
-    int32_t *cursor = c.take<int32_t>(n);
-    uint64_t *keys = c.take<uint64_t>(cap);
+    int64_t *seg = c.take<int64_t>(n + 1);
+    uint64_t *keys = c.take<uint64_t>(n * (int64_t)(eo + ei));
+    int32_t *queue = c.take<int32_t>(n + 1);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
-    ONNG_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * (n + 1), st));
-    ONNG_HIP(hipMemsetAsync(cursor, 0, sizeof(int32_t) * n, st));
-    hipLaunchKernelGGL(sa_count_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, knn, n, k, eo,
-                       ei, cnt);
+    const unsigned wb = blocks_for(n, 4);
+    if (n > 0) {
+        ONNG_HIP(hipMemsetAsync(rcnt, 0, sizeof(int32_t) * n, st));
+        hipLaunchKernelGGL(sa_count_kernel, dim3(blocks_for(n, SA_ROWS)), dim3(SA_WAVES * WAVE), 0,
+                           st, knn, n, k, eo, ei, rcnt, slot, fcnt);
+    }
+    hipLaunchKernelGGL(sa_sizes_kernel, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, rcnt, fcnt,
+                       n, cnt);
+    ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, seg, (int)(n + 1), st));
+    if (n > 0) {
+        hipLaunchKernelGGL((sa_scatter_kernel<LenT>), dim3(wb), dim3(256), 0, st, knn, kd, n, k,
+                           ei, seg, slot, keys);
+        hipLaunchKernelGGL((sa_merge_kernel<LenT>), dim3(wb), dim3(256), 0, st, knn, kd, n, k,
+                           rcnt, fcnt, seg, keys, cnt);
+    }
     ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, offsets, (int)(n + 1), st));
     ONNG_HIP(hipMemcpyAsync(nnz_out, offsets + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     ONNG_HIP(hipStreamSynchronize(st));
@@ -698,11 +936,7 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
         set_error("onng_adjust_degree: nnz_capacity too small");
         return ONNG_ERR_CAPACITY;
     }
-    hipLaunchKernelGGL((sa_scatter_kernel<LenT>), dim3(blocks_for(n, 256)), dim3(256), 0, st, knn,
-                       kd, n, k, eo, ei, offsets, cursor, keys);
-    if (n > 0)
-        hipLaunchKernelGGL((segment_rank_sort_kernel<LenT>), dim3((unsigned)n), dim3(256),
-                           4096 * sizeof(uint64_t), st, offsets, n, keys, nbrs, lens);
+    seg_sort<LenT>(seg, offsets, n, keys, nbrs, lens, queue, st);
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
     return ONNG_OK;
@@ -733,6 +967,7 @@ size_t adjust_degree_constrained_ws(int64_t n, int32_t k, int32_t e_o, int32_t e
     c.take<int32_t>(nrev);             // G_t lengths (4 bytes)
     c.take<int64_t>(n + 1);            // kept counts
     c.take<uint64_t>(cap);             // kept keys
+    c.take<int32_t>(n + 1);            // long lists
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
 }
@@ -757,6 +992,7 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
     LenT *rv_len = reinterpret_cast<LenT *>(c.take<int32_t>(nrev));
     int64_t *ocnt = c.take<int64_t>(n + 1);
     uint64_t *okeys = c.take<uint64_t>(cap);
+    int32_t *queue = c.take<int32_t>(n + 1);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
     ONNG_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * (n + 1), st));
@@ -768,8 +1004,7 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
         ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, rev_off, (int)(n + 1), st));
         hipLaunchKernelGGL((sac_scatter_kernel<LenT>), dim3(blocks_for(n, 256)), dim3(256), 0, st,
                            knn, kd, n, k, ei, rev_off, cursor, rkeys, first_src);
-        hipLaunchKernelGGL((segment_rank_sort_kernel<LenT>), dim3((unsigned)n), dim3(256),
-                           4096 * sizeof(uint64_t), st, rev_off, n, rkeys, rv_nb, rv_len);
+        seg_sort<LenT>(rev_off, rev_off, n, rkeys, rv_nb, rv_len, queue, st);
         hipLaunchKernelGGL((sac_select_kernel<LenT, false>), dim3(blocks_for(n * WAVE, 256)),
                            dim3(256), 0, st, rev_off, rv_nb, rv_len, first_src, knn, kd, n, k, eo,
                            ocnt, nullptr, nullptr);
@@ -790,8 +1025,7 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
         hipLaunchKernelGGL((sac_select_kernel<LenT, true>), dim3(blocks_for(n * WAVE, 256)),
                            dim3(256), 0, st, rev_off, rv_nb, rv_len, first_src, knn, kd, n, k, eo,
                            nullptr, offsets, okeys);
-        hipLaunchKernelGGL((segment_rank_sort_kernel<LenT>), dim3((unsigned)n), dim3(256),
-                           4096 * sizeof(uint64_t), st, offsets, n, okeys, nbrs, lens);
+        seg_sort<LenT>(offsets, offsets, n, okeys, nbrs, lens, queue, st);
     }
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
@@ -951,6 +1185,7 @@ size_t add_edges_ws(int64_t n, int64_t nnz, int64_t m) {
     c.take<int64_t>(n + 1);
     c.take<int32_t>(n);
     c.take<uint64_t>(nnz + m);
+    c.take<int32_t>(n + 1);
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
 }
@@ -965,6 +1200,7 @@ static onng_status add_edges_impl(const onng_graph *g, const int32_t *src, const
     int64_t *cnt = c.take<int64_t>(n + 1);
     int32_t *cursor = c.take<int32_t>(n);
     uint64_t *keys = c.take<uint64_t>(nnz + m);
+    int32_t *queue = c.take<int32_t>(n + 1);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
     ONNG_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * (n + 1), st));
@@ -987,8 +1223,7 @@ static onng_status add_edges_impl(const onng_graph *g, const int32_t *src, const
         if (m > 0)
             hipLaunchKernelGGL((ae_new_kernel<LenT>), dim3(blocks_for(m, 256)), dim3(256), 0, st,
                                n, src, dst, len, m, out_off, cursor, keys);
-        hipLaunchKernelGGL((segment_rank_sort_kernel<LenT>), dim3((unsigned)n), dim3(256),
-                           4096 * sizeof(uint64_t), st, out_off, n, keys, out_nb, out_len);
+        seg_sort<LenT>(out_off, out_off, n, keys, out_nb, out_len, queue, st);
     }
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
