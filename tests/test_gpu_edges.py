@@ -93,3 +93,118 @@ def test_edge_insertion_keeps_equal_edges():
     o = np.lexsort((dst, ln, src))
     assert np.array_equal(host(out.nbrs), dst[o])
     assert np.array_equal(host(out.lens), ln[o])
+
+
+@pytest.mark.parametrize("dim,pitch,inrow", [(1, None, True), (3, None, False), (100, 128, True), (127, None, True),
+                                             (128, 160, False), (129, None, True), (260, None, False),
+                                             (37, 37, False), (38, 42, False)])
+def test_encode_row_shapes(dim, pitch, inrow):
+    """Rows of every step of the four-element encoder (below, at and past 128
+    components, ragged ends, wide padding) and of pitches that only the general
+    form takes; byte for byte."""
+    A, Lb = api(), L()
+    g = np.random.default_rng(dim)
+    x = (g.standard_normal((71, dim)) * 10.0 ** g.integers(-6, 4, size=(71, 1))).astype(np.float32)
+    x[3] = 0.0
+    for dt, odt, esz in ((Lb.F16, orc.F16, 2), (Lb.BF16, orc.BF16, 2), (Lb.FP8_E4M3, orc.FP8, 1)):
+        if pitch is not None and pitch < dim * esz:
+            continue
+        if pitch is not None and pitch % 16 and dt == Lb.FP8_E4M3 and inrow:
+            continue
+        say("encode", dim, pitch, dt)
+        row_in = inrow and dt == Lb.FP8_E4M3
+        v = A.encode(to_dev(x), dt, Lb.L2SQ, pitch=pitch, scale_in_row=row_in)
+        codes = host(v.data)
+        ref, rs = orc.encode_rows(x, odt, pitch=v.pitch)
+        if row_in:
+            assert np.array_equal(codes[:, -4:].copy().view(np.float32)[:, 0], rs)
+            codes, ref = codes[:, :-4], ref[:, :-4]
+        elif rs is not None:
+            assert np.array_equal(host(v.scale), rs)
+        assert np.array_equal(codes, ref)
+
+
+def test_encode_fp8_every_rounding_case():
+    """Every e4m3 value, every midpoint of two of them and their f32
+    neighbours (scale 1: the row's largest element is 448), and NaN."""
+    say("encode fp8 grid")
+    A, Lb = api(), L()
+    vals = sorted({orc.decode(orc.FP8, c) for c in range(0x7f)})
+    mid = [(a + b) / 2 for a, b in zip(vals, vals[1:])]
+    v = np.array(vals + mid, dtype=np.float32)
+    v = np.concatenate([v, np.nextafter(v, np.float32(1e9)), np.nextafter(v, np.float32(-1e9))])
+    v = v[np.abs(v) <= 448]
+    v = np.concatenate([v, -v])
+    rows = np.zeros((-(-len(v) // 99), 100), dtype=np.float32)
+    rows[:, 0] = 448
+    rows.reshape(-1)[np.flatnonzero(np.arange(rows.size) % 100 > 0)[:len(v)]] = v
+    out = A.encode(to_dev(rows), Lb.FP8_E4M3, Lb.L2SQ)
+    ref, rs = orc.encode_rows(rows, orc.FP8, pitch=out.pitch)
+    assert np.array_equal(host(out.scale), rs)
+    assert np.array_equal(host(out.data), ref)
+    nan = np.array([[448, np.nan, -1.0, 2.0, 0.5, -np.nan, 1e-9, -448.0]], dtype=np.float32)
+    nan[0, 5] = np.copysign(np.float32(np.nan), np.float32(-1))
+    got = host(A.encode(to_dev(nan), Lb.FP8_E4M3, Lb.L2SQ).data)[0]
+    assert got[:8].tolist() == [0x7e, 0x7f, 0xb8, 0x40, 0x30, 0xff, 0x00, 0xfe]
+
+
+@pytest.mark.parametrize("nq,pool,dim,metric", [(1, 1, 3, orc.L2SQ), (3, 15, 64, orc.COS), (5, 65, 65, orc.L2SQ),
+                                                (300, 128, 37, orc.COS), (2, 1000, 130, orc.L2SQ),
+                                                (9000, 20, 100, orc.COS)])
+def test_rerank_row_splits(nq, pool, dim, metric):
+    """The rerank over lane-group remainders of the pool, components past 64
+    and 128, and one to four waves per query.  f64: 1e-12 of the oracle; f32:
+    a sum of at most dim terms, (dim / 64 + 8) roundings of 2^-24 each on
+    terms whose magnitudes sum to at most |x|^2 + |q|^2 + |d|."""
+    say("rerank", nq, pool, dim)
+    A = api()
+    g = np.random.default_rng(pool)
+    x = g.standard_normal((1200, dim)).astype(np.float32)
+    q = g.standard_normal((nq, dim)).astype(np.float32)
+    if metric == orc.COS:
+        x /= np.linalg.norm(x, axis=1, keepdims=True)
+        q /= np.linalg.norm(q, axis=1, keepdims=True)
+    ids = np.argsort(g.random((nq, 1200)), axis=1)[:, :pool].astype(np.int32)
+    ids[:, pool // 2] = -1
+    k = min(10, pool)
+    bv, qv = orc.Vectors.from_array(x, metric), orc.Vectors.from_array(q, metric)
+    rid, rd = orc.rerank(qv, bv, ids, k)
+    gid, gd = A.rerank(gpu_vectors(q, metric), gpu_vectors(x, metric), to_dev(ids), k, use_f64=True)
+    fin = np.isfinite(rd)
+    assert np.array_equal(host(gid), rid)
+    assert np.array_equal(np.isfinite(host(gd)), fin)
+    assert np.allclose(host(gd)[fin], rd[fin], rtol=1e-12, atol=1e-12)
+    _, gd = A.rerank(gpu_vectors(q, metric), gpu_vectors(x, metric), to_dev(ids), k)
+    size = 2.0 * (1.0 if metric == orc.COS else rd[fin].max(initial=0.0))
+    assert np.abs(host(gd)[fin] - rd[fin]).max(initial=0.0) <= (dim / 64 + 8) * 2.0 ** -24 * size
+    if metric == orc.L2SQ and dim == 65:   # stored types other than f32
+        for dt, odt in ((L().F16, orc.F16), (L().FP8_E4M3, orc.FP8)):
+            lp = A.encode(to_dev(x), dt, L().L2SQ)
+            codes, rs = orc.encode_rows(x, odt, pitch=lp.pitch)
+            dec = np.array([orc.decode(odt, c) for c in range(256 if odt == orc.FP8 else 65536)])
+            xd = dec[codes.view(np.uint16 if odt == orc.F16 else np.uint8)[:, :dim].astype(np.int64)]
+            if rs is not None:
+                xd = xd * rs[:, None].astype(np.float64)
+            d = np.where(ids >= 0, ((xd[ids] - q[:, None, :].astype(np.float64)) ** 2).sum(2), np.inf)
+            got = host(A.rerank(gpu_vectors(q, metric), lp, to_dev(ids), k, use_f64=True)[1])
+            assert np.allclose(got, np.sort(d, axis=1)[:, :k], rtol=1e-12)
+
+
+@pytest.mark.parametrize("B,F,H,T", [(1, 14, 64, 16), (5, 1, 1, 1), (63, 33, 33, 3), (1026, 32, 64, 16), (300, 70, 17, 5)])
+def test_mlp_sizes(B, F, H, T):
+    """Sample-group remainders, one to full widths, and inputs past the
+    staged width; every result is an f32 sum of at most F + H + B terms in a
+    fixed order: 1e-5 of its norm."""
+    say("mlp", B, F, H, T)
+    A = api()
+    g = np.random.default_rng(B)
+    X, Y, W = (g.standard_normal(s).astype(np.float32) for s in ((B, F), (B, T), (B, T)))
+    W = np.abs(W)
+    W1, b1, W2, b2 = ((g.standard_normal(s) * 0.3).astype(np.float32) for s in ((H, F), (H,), (T, H), (T,)))
+    ref_h, ref_y = orc.mlp_forward(X, W1, b1, W2, b2)
+    ref_loss, ref_g = orc.mlp_loss_grad(X, Y, W1, b1, W2, b2, W)
+    dev_w = [to_dev(a) for a in (W1, b1, W2, b2)]
+    y, hid = A.mlp_forward(to_dev(X), *dev_w, want_hidden=True)
+    loss, grads = A.mlp_backward(to_dev(X), to_dev(Y), *dev_w, w=to_dev(W))
+    for got, ref in zip([y, hid, loss, *grads], [ref_y, ref_h, np.array([ref_loss]), *ref_g]):
+        assert np.linalg.norm(host(got) - ref) <= 1e-5 * np.linalg.norm(ref) + 1e-7
