@@ -14,44 +14,82 @@ namespace onng {
 
 namespace {
 
-// one thread per sample: hidden activations, outputs and, when target is
-// given, dL/dy and dL/dh (the per-sample pieces of the gradient)
-__global__ void mlp_sample_kernel(const float *X, int batch, int F, const float *W1,
-                                  const float *b1, int H, const float *W2, const float *b2, int T,
-                                  const float *target, const float *w, float *hid, float *Y,
-                                  float *dy, float *dh, float *lossp) {
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= batch) return;
-    const float *x = X + (int64_t)n * F;
-    float h[64], a[64];
-    for (int j = 0; j < H; j++) {
-        float s = b1[j];
-        for (int i = 0; i < F; i++) s = fmaf(W1[j * F + i], x[i], s);
-        a[j] = s;
-        h[j] = fmaxf(s, 0.0f);
-        if (hid) hid[(int64_t)n * H + j] = h[j];
+// MLP_S samples per wave: hidden activations, outputs and, when target is
+// given, dL/dy and dL/dh (the per-sample pieces of the gradient).  Lane j is
+// hidden unit j, then lane s * 16 + t output t of sample s; every sum runs in
+// index order in one lane.  The weights sit in LDS.  It is one chain of some
+// 200 dependent multiply-adds, so what counts is that the batch fills the
+// chip: 1024 samples are 256 waves.  (One thread per sample, its activations
+// in scratch memory, 16 waves: 279 us at 1024 x (14 -> 64 -> 16); now
+// MLP_TIME.)
+constexpr int MLP_S = 4;
+constexpr int MLP_LDS_F = 32;   // widest input whose first layer is staged in LDS
+
+__global__ void __launch_bounds__(64) mlp_sample_kernel(const float *X, int batch, int F,
+                                                        const float *W1, const float *b1, int H,
+                                                        const float *W2, const float *b2, int T,
+                                                        const float *target, const float *w,
+                                                        float *hid, float *Y, float *dy, float *dh,
+                                                        float *lossp) {
+    __shared__ float w1s[64 * MLP_LDS_F], w2s[16 * 65], hs[MLP_S][64], gs[MLP_S][16],
+        es[MLP_S][16], ws[MLP_S][16];
+    const int lane = threadIdx.x;
+    const int n0 = blockIdx.x * MLP_S;
+    const float *W1p = W1;
+    if (F <= MLP_LDS_F) {
+        for (int i = lane; i < H * F; i += 64) w1s[i] = W1[i];
+        W1p = w1s;
     }
-    float g[16];
-    float l = 0.0f;
+    for (int i = lane; i < T * H; i += 64) w2s[i / H * 65 + i % H] = W2[i];
+    __syncthreads();
+    float a[MLP_S];
+#pragma unroll
+    for (int s = 0; s < MLP_S; s++) a[s] = lane < H ? b1[lane] : 0.0f;
+    if (lane < H)
+        for (int i = 0; i < F; i++) {
+            const float wi = W1p[lane * F + i];
+#pragma unroll
+            for (int s = 0; s < MLP_S; s++)
+                a[s] = fmaf(wi, X[(int64_t)min(n0 + s, batch - 1) * F + i], a[s]);
+        }
+#pragma unroll
+    for (int s = 0; s < MLP_S; s++) {
+        const float h = fmaxf(a[s], 0.0f);
+        hs[s][lane] = h;
+        if (hid && lane < H && n0 + s < batch) hid[(int64_t)(n0 + s) * H + lane] = h;
+    }
+    __syncthreads();
     const float scale = 1.0f / ((float)batch * (float)T);
-    for (int t = 0; t < T; t++) {
+    const int so = lane / 16, t = lane % 16;
+    const int64_t n = n0 + so;
+    if (t < T && n < batch) {
         float y = b2[t];
-        for (int j = 0; j < H; j++) y = fmaf(W2[t * H + j], h[j], y);
-        if (Y) Y[(int64_t)n * T + t] = y;
+        for (int j = 0; j < H; j++) y = fmaf(w2s[t * 65 + j], hs[so][j], y);
+        if (Y) Y[n * T + t] = y;
         if (target) {
-            float wt = w ? w[(int64_t)n * T + t] : 1.0f;
-            float e = y - target[(int64_t)n * T + t];
-            l += wt * e * e;
-            g[t] = 2.0f * wt * e * scale;
-            dy[(int64_t)n * T + t] = g[t];
+            const float wt = w ? w[n * T + t] : 1.0f;
+            const float e = y - target[n * T + t];
+            const float g = 2.0f * wt * e * scale;
+            es[so][t] = e;
+            ws[so][t] = wt;
+            gs[so][t] = g;
+            dy[n * T + t] = g;
         }
     }
     if (!target) return;
-    lossp[n] = l * scale;
-    for (int j = 0; j < H; j++) {
-        float s = 0.0f;
-        for (int t = 0; t < T; t++) s = fmaf(W2[t * H + j], g[t], s);
-        dh[(int64_t)n * H + j] = a[j] > 0.0f ? s : 0.0f;
+    __syncthreads();
+    if (t == 0 && n < batch) {
+        float l = 0.0f;
+        for (int u = 0; u < T; u++) l += ws[so][u] * es[so][u] * es[so][u];
+        lossp[n] = l * scale;
+    }
+    if (lane >= H) return;
+#pragma unroll
+    for (int s = 0; s < MLP_S; s++) {
+        if (n0 + s >= batch) break;
+        float d = 0.0f;
+        for (int u = 0; u < T; u++) d = fmaf(w2s[u * 65 + lane], gs[s][u], d);
+        dh[(int64_t)(n0 + s) * H + lane] = a[s] > 0.0f ? d : 0.0f;
     }
 }
 
@@ -228,7 +266,7 @@ onng_status mlp_forward_launch(const float *X, int32_t batch, int32_t F, const f
                                const float *b1, int32_t H, const float *W2, const float *b2,
                                int32_t T, float *hidden, float *Y, hipStream_t st) {
     if (batch == 0) return ONNG_OK;
-    hipLaunchKernelGGL(mlp_sample_kernel, dim3((batch + 127) / 128), dim3(128), 0, st, X, batch,
+    hipLaunchKernelGGL(mlp_sample_kernel, dim3((batch + MLP_S - 1) / MLP_S), dim3(64), 0, st, X, batch,
                        F, W1, b1, H, W2, b2, T, nullptr, nullptr, hidden, Y, nullptr, nullptr,
                        nullptr);
     ONNG_HIP(hipGetLastError());
@@ -245,7 +283,7 @@ onng_status mlp_backward_launch(const float *X, const float *target, const float
     float *dy = c.take<float>((size_t)batch * T);
     float *dh = c.take<float>((size_t)batch * H);
     float *lp = c.take<float>((size_t)batch);
-    hipLaunchKernelGGL(mlp_sample_kernel, dim3((batch + 127) / 128), dim3(128), 0, st, X, batch,
+    hipLaunchKernelGGL(mlp_sample_kernel, dim3((batch + MLP_S - 1) / MLP_S), dim3(64), 0, st, X, batch,
                        F, W1, b1, H, W2, b2, T, target, w, hid, nullptr, dy, dh, lp);
     int nparam = H * F + H + T * H + T + 1;
     hipLaunchKernelGGL(mlp_reduce_kernel, dim3(nparam), dim3(256), 0, st, X, batch, F, H, T, hid,
