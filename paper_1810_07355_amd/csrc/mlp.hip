@@ -20,8 +20,8 @@ namespace {
 // index order in one lane.  The weights sit in LDS.  It is one chain of some
 // 200 dependent multiply-adds, so what counts is that the batch fills the
 // chip: 1024 samples are 256 waves.  (One thread per sample, its activations
-// in scratch memory, 16 waves: 279 us at 1024 x (14 -> 64 -> 16); now
-// MLP_TIME.)
+// in scratch memory, 16 waves: 279 us at 1024 x (14 -> 64 -> 16), where a
+// whole step, gradients and four Adam updates, now takes 44 us, not 302.)
 constexpr int MLP_S = 4;
 constexpr int MLP_LDS_F = 32;   // widest input whose first layer is staged in LDS
 

@@ -49,7 +49,7 @@ __device__ __forceinline__ T plus_xor1(T x) { return x + (sizeof(T) == 8 ? (T)dp
 // the tree of one component per lane (chains over components 64 apart, then
 // lanes 32, 16, .. 1 apart), kept as it was when one row at a time took the
 // whole wave, so f32 distances and their ties are unchanged.  10,000 queries
-// x 74 rows of 100 f32, f64 sums: RR_TIME; one row at a time 527 us.
+// x 74 rows of 100 f32, f64 sums: 113 us; one row at a time 527 us.
 constexpr int RR_ROWS = 4;
 
 template <bool F64, bool PLAIN_F32>
