@@ -7,6 +7,9 @@
 // -> f32 (16x16x4)
 // for float data.  Cosine distance on unit vectors is 1 - <x, y>.
 //
+// From 1024 base rows on, topk_bound.h's two passes do the work; topk_kernel
+// here takes smaller bases, larger shapes than their LDS holds, and the rows
+// whose candidate buffer overflowed there.
 // A block owns BM query rows (16 per wave) and sweeps the base rows in tiles
 // of 64 staged in LDS.  Each row keeps its current k best keys sorted in LDS
 // and a buffer of candidates that beat its k-th key; the buffer is sorted and
@@ -22,6 +25,7 @@
 #include <cstdint>
 
 #include "onng_internal.h"
+#include "topk_bound.h"
 #include "topk_common.h"
 #include "wave.h"
 
@@ -34,28 +38,28 @@ namespace {
 // ---- per-row norms (int32 |x-128|^2 for u8, f32 |x|^2 otherwise) ----------
 __global__ void norms_u8_kernel(const uint8_t *x, int64_t pitch, int64_t n, int dim,
                                 int32_t *out) {
-    int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     int lane = threadIdx.x & 63;
-    if (i >= n) return;
-    int32_t s = 0;
-    for (int c = lane; c < dim; c += 64) {
-        int v = (int)x[i * pitch + c] - 128;
-        s += v * v;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < n; i += (int64_t)gridDim.x * 4) {
+        int32_t s = 0;
+        for (int c = lane; c < dim; c += 64) {
+            int v = (int)x[i * pitch + c] - 128;
+            s += v * v;
+        }
+        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+        if (lane == 0) out[i] = s;
     }
-    for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-    if (lane == 0) out[i] = s;
 }
 
 __global__ void norms_f32_kernel(const uint8_t *x, int64_t pitch, int64_t n, int dim,
                                  float *out) {
-    int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     int lane = threadIdx.x & 63;
-    if (i >= n) return;
-    const float *r = reinterpret_cast<const float *>(x + i * pitch);
-    float s = 0.0f;
-    for (int c = lane; c < dim; c += 64) s = fmaf(r[c], r[c], s);
-    for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-    if (lane == 0) out[i] = s;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < n; i += (int64_t)gridDim.x * 4) {
+        const float *r = reinterpret_cast<const float *>(x + i * pitch);
+        float s = 0.0f;
+        for (int c = lane; c < dim; c += 64) s = fmaf(r[c], r[c], s);
+        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+        if (lane == 0) out[i] = s;
+    }
 }
 
 __global__ void gather_rows_kernel(const uint8_t *src, int64_t pitch, const int32_t *ids,
@@ -77,6 +81,12 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
     const int wv = threadIdx.x / WAVE;
     const int nwaves = a.bm / 16;
     const int64_t row0 = (int64_t)blockIdx.x * a.bm;
+    auto skip_row = [&](int64_t row) { return a.only && a.only[1 + row] <= a.only_above; };
+    if (a.only) {
+        if (!a.only[0]) return;
+        const int64_t row = row0 + threadIdx.x;
+        if (!__syncthreads_or((int)threadIdx.x < a.bm && row < a.nq && !skip_row(row))) return;
+    }
 
     // LDS: [B tile][lists bm*kcap][cands bm*cb][tau bm][cnt bm][nlist bm][stage nwaves*64]
     char *p = smem;
@@ -198,21 +208,14 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
     constexpr int total = BN * CPR;
     const bool piped = total <= STG * (int)blockDim.x;
     uint4 stg[STG];
-    uint32_t side_n = 0, side_g = 0;
+    uint32_t side_g = 0;
     auto fetch_side = [&](int t) {
         const int64_t col = (int64_t)t * BN + threadIdx.x;
-        side_n = 0;
         side_g = 0;
-        if (threadIdx.x < BN && col < a.nb) {
-            if (a.side_norms) side_n = reinterpret_cast<const uint32_t *>(a.bn)[col];
-            if (a.b_ids) side_g = (uint32_t)a.b_ids[col];
-        }
+        if (threadIdx.x < BN && col < a.nb && a.b_ids) side_g = (uint32_t)a.b_ids[col];
     };
     auto put_side = [&]() {
-        if (threadIdx.x < BN) {
-            if (a.side_norms) t_norm[threadIdx.x] = side_n;
-            if (a.b_ids) t_gid[threadIdx.x] = side_g;
-        }
+        if (threadIdx.x < BN && a.b_ids) t_gid[threadIdx.x] = side_g;
     };
     // A thread's chunks sit at the same place in every tile; rows are read
     // with 32-bit offsets from the tile's first row.
@@ -312,6 +315,10 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
         }
         __syncthreads();
         if (piped && t + 1 < t_end) fetch_tile(tile_at(t + 1));
+        if (a.side_norms) {
+            tile_norms<U8, CPR>(btile, a.lds_pitch, blockDim.x, t_norm);
+            __syncthreads();
+        }
         if (row0 + wv * 16 >= a.nq) continue;
 
         // ---- 16 query rows x 64 tile columns: four 16x16 blocks, their
@@ -419,6 +426,7 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
         int lr = wv * 16 + r;
         int64_t grow = row0 + lr;
         if (grow >= a.nq) break;
+        if (skip_row(grow)) continue;
         flush_row(lr);
         int nl = uni(nlist[lr]);
         const uint64_t *lst = lists + (size_t)lr * a.kcap;
@@ -445,12 +453,14 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
 template <bool U8>
 __global__ void __launch_bounds__(256) merge_parts_kernel(const uint64_t *part, int64_t nq,
                                                           int splits, int k, int kcap,
-                                                          int32_t *out_ids, void *out_d) {
+                                                          int32_t *out_ids, void *out_d,
+                                                          const int32_t *only, int only_above) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = lane_id();
     const int wv = threadIdx.x / WAVE;
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv;
     if (row >= nq) return;
+    if (only && (!only[0] || only[1 + row] <= only_above)) return;
     uint64_t *lst = reinterpret_cast<uint64_t *>(smem) + (size_t)wv * (kcap + WAVE);
     uint64_t *stage = lst + kcap;
     const uint64_t *src = part + (size_t)row * splits * k;
@@ -473,6 +483,86 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(const uint64_t *part, 
             reinterpret_cast<float *>(out_d)[row * k + i] =
                 i < nl ? unord_f32((uint32_t)(key >> 32)) : __builtin_inff();
     }
+}
+
+// ---- between and after the passes of topk_bound.h ----
+// One wave per row: an upper bound of the rank-th smallest of its group minima
+// (the distances' low bits below `low` rounded up), and its counter cleared.
+// Bits are settled from `top` down by counting the minima at or below each
+// trial value, VPL minima per lane in registers.
+template <int VPL>
+__global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins, int64_t nq, int groups,
+                                                           int rank, int top, int low, uint32_t *tau,
+                                                           int32_t *cnt) {
+    const int64_t row = (int64_t)blockIdx.x * 4 + uni(threadIdx.x / WAVE);
+    const int lane = lane_id();
+    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[0] = 0;   // no row has overflowed
+    if (row >= nq) return;
+    uint32_t x[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; i++) {
+        const int g = i * WAVE + lane;
+        x[i] = g < groups ? mins[row * groups + g] : ~0u;
+    }
+    uint32_t v = 0;
+    for (int bit = top; bit >= low; bit--) {
+        const uint32_t trial = v | ((1u << bit) - 1u);
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < VPL; i++) c += __popcll(ballot(x[i] <= trial));
+        if (c < rank) v |= 1u << bit;
+    }
+    if (lane == 0) {
+        tau[row] = v | ((1u << low) - 1u);
+        cnt[1 + row] = 0;
+    }
+}
+
+// One block per row: its cnt[1 + row] candidates in order, the k first written
+// (padded when there are fewer).  A row with more than `cap` sets cnt[0] and is
+// left to the general kernel.  Up to 64 candidates sort in registers, more by a
+// bitonic network in LDS; with few rows the block has four waves.
+template <bool U8>
+__global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, int cap, int32_t *cnt,
+                                                        int k, int32_t *out_ids, void *out_d) {
+    extern __shared__ __attribute__((aligned(16))) uint64_t sk[];
+    const int64_t row = blockIdx.x;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int n = uni(cnt[1 + row]);
+    if (n > cap) {
+        if (tid == 0) cnt[0] = 1;
+        return;
+    }
+    const uint64_t *src = cand + row * cap;
+    auto put = [&](int i, uint64_t key) {
+        out_ids[row * k + i] = i < n ? (int32_t)(uint32_t)key : -1;
+        if constexpr (U8)
+            reinterpret_cast<int32_t *>(out_d)[row * k + i] = i < n ? (int32_t)(key >> 32) : INT32_MAX;
+        else
+            reinterpret_cast<float *>(out_d)[row * k + i] =
+                i < n ? unord_f32((uint32_t)(key >> 32)) : __builtin_inff();
+    };
+    if (n <= WAVE) {
+        if (tid >= WAVE) return;
+        uint64_t key = tid < n ? src[tid] : KEY_MAX;
+        key = wave_sort(key, pow2_at_least(max(n, 1)));
+        if (tid < k) put(tid, key);
+        for (int i = WAVE + tid; i < k; i += WAVE) put(i, KEY_MAX);
+        return;
+    }
+    const int w = pow2_at_least(n);
+    for (int i = tid; i < w; i += nt) sk[i] = i < n ? src[i] : KEY_MAX;
+    for (int size = 2; size <= w; size <<= 1)
+        for (int d = size >> 1; d > 0; d >>= 1) {
+            __syncthreads();
+            for (int t = tid; t < w / 2; t += nt) {
+                const int i = 2 * t - (t & (d - 1));   // lower of the pair (i, i + d)
+                const uint64_t lo = sk[i], hi = sk[i + d];
+                if ((lo > hi) == ((i & size) == 0)) sk[i] = hi, sk[i + d] = lo;
+            }
+        }
+    __syncthreads();
+    for (int i = tid; i < k; i += nt) put(i, i < w ? sk[i] : KEY_MAX);
 }
 
 // Parts per row block.  With one block per compute unit (the LDS holds one
@@ -552,6 +642,82 @@ bool topk_use_wide(const onng_vectors *Q, int64_t nb, int32_t k) {
            wide_lds_bytes(lds_pitch_for(ONNG_U8, Q->dim), topk_kcap(k)) <= 64 * 1024;
 }
 
+// The bound-and-filter path (topk_bound.h): what it samples and how it is laid
+// out, or use = false.
+struct BoundPlan {
+    bool use = false;
+    int rw = 0;                  // row waves per block: 1, 4 or 8
+    int ns_log2 = 0, group_tiles = 0, quads = 0, groups = 0, cap = 0;
+    int splits[2] = {1, 1}, per_split[2] = {0, 0};   // bound, filter
+    size_t lds[2] = {0, 0};
+};
+
+BoundPlan topk_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k) {
+    BoundPlan P;
+    const int rank = k + 1;      // one more, as the row itself may be a minimum
+    if (Q->n < 1 || nb < 1024) return P;
+    const int cw = Q->n <= 16 ? 4 : 1;
+    P.rw = Q->n <= 16 ? 1 : Q->n <= 64 ? 4 : 8;
+    // One row in f is sampled: the bound costs 1 / f of the filter's products
+    // and lets about k f candidates through.  Measured (us) at f = 2, 4, 8: u8
+    // 10,007 x 10,007 x 128, k 20: 180, 199, -, k 100: 284, 382, -; f32 10,000 x
+    // 10,000 x 100, k 8: 388, 362, -; f32 100 x 1M x 96, k 100: -, 369, 351;
+    // f32 10,000 x 200,000 x 100, k 74: -, 5746, 5313.
+    int f = nb >= 65536 ? 8 : Q->dtype == ONNG_U8 && nb < 16384 ? 2 : 4;
+    for (; f >= 1; f /= 2) {
+        const int64_t want = nb * 181 / 128 / f;         // pow2 within sqrt 2 of nb / f
+        P.ns_log2 = 6;
+        while ((2ll << P.ns_log2) <= std::min(want, nb)) P.ns_log2++;
+        int64_t need = (int64_t)(1.5 * k * (double)nb / (double)(1ll << P.ns_log2)) + 64;
+        P.cap = 256;
+        while (P.cap < need) P.cap *= 2;
+        if (P.cap <= 4096 && Q->n * (int64_t)P.cap * 8 <= (1ll << 29)) break;
+    }
+    if (f < 1) return P;
+    const int64_t ns = 1ll << P.ns_log2, tiles = ns / BN;
+    int want_groups = 512;
+    while (want_groups < 8 * rank) want_groups *= 2;
+    want_groups = std::min(want_groups, 2048);
+    const int bm = P.rw * 16;
+    const int64_t row_blocks = (Q->n + bm - 1) / bm;
+    P.group_tiles = 1;
+    while (tiles / P.group_tiles * 16 * cw > want_groups) P.group_tiles *= 2;
+    // few row blocks: groups of fewer tiles, the minima of four lanes together,
+    // so that more blocks share the sample
+    if (P.group_tiles >= 4 && tiles / P.group_tiles * row_blocks < 2 * device_cu_count()) {
+        P.group_tiles /= 4;
+        P.quads = 1;
+    }
+    P.groups = (int)(tiles / P.group_tiles * 16 * cw) / (P.quads ? 4 : 1);
+    if (P.groups < 2 * rank || P.groups > 2048) return P;
+    for (int m = 0; m < 2; m++) P.lds[m] = bound_lds(lds_pitch_for(Q->dtype, Q->dim), P.rw, m == 1);
+    if (P.lds[1] > 160 * 1024) return P;
+    // Splits: all resident blocks (by LDS and by registers: four waves per SIMD,
+    // three with RW = 4) run at once, so a launch takes ceil(blocks / resident)
+    // rounds, each as long as one split and two tiles' worth of start and end.
+    const int64_t ntiles[2] = {tiles, (nb + BN - 1) / BN};
+    for (int m = 0; m < 2; m++) {
+        const int64_t per_cu = std::min<int64_t>(160 * 1024 / (int64_t)P.lds[m], P.rw == 8 ? 2 : P.rw == 4 ? 3 : 4);
+        const int64_t resident = std::max<int64_t>(per_cu, 1) * device_cu_count();
+        const int64_t unit = m == 0 ? P.group_tiles : 1;
+        const int64_t units = (ntiles[m] + unit - 1) / unit;
+        int64_t best_cost = INT64_MAX;
+        const int64_t top = std::min(units, std::max<int64_t>(1, 4 * resident / row_blocks));
+        for (int64_t sp = 1; sp <= top; sp++) {
+            const int64_t per = (units + sp - 1) / sp * unit;
+            const int64_t rounds = (row_blocks * ((ntiles[m] + per - 1) / per) + resident - 1) / resident;
+            const int64_t cost = rounds * (per + 2);
+            if (cost < best_cost) {
+                best_cost = cost;
+                P.per_split[m] = (int)per;
+                P.splits[m] = (int)((ntiles[m] + per - 1) / per);
+            }
+        }
+    }
+    P.use = true;
+    return P;
+}
+
 }  // namespace
 
 size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand, int32_t k) {
@@ -575,6 +741,13 @@ size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand
     }
     const int sp = topk_splits(Q->n, nb, topk_bm(k, Q->dtype, Q->dim, topk_side_words(Q->dtype, Q->metric, n_cand > 0)));
     if (sp > 1) c.take<uint64_t>((size_t)Q->n * sp * k);
+    const BoundPlan bp = topk_bound_plan(Q, nb, k);
+    if (bp.use) {
+        c.take<uint32_t>((size_t)Q->n * bp.groups);
+        c.take<uint32_t>(Q->n);
+        c.take<int32_t>(Q->n + 1);
+        c.take<uint64_t>((size_t)Q->n * bp.cap);
+    }
     return c.size() + 256;
 }
 
@@ -625,24 +798,30 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         flist = c.take<uint64_t>((size_t)Q->n * topk_kcap(k));
         fcand = c.take<uint32_t>((size_t)Q->n * FW_CB);
     }
-    if (Q->n > 0) {
-        if (u8)
-            hipLaunchKernelGGL(norms_u8_kernel, dim3((unsigned)((Q->n + 3) / 4)), dim3(256), 0, st,
-                               static_cast<const uint8_t *>(Q->data), Q->pitch_bytes, Q->n, Q->dim,
-                               static_cast<int32_t *>(qn));
-        else
-            hipLaunchKernelGGL(norms_f32_kernel, dim3((unsigned)((Q->n + 3) / 4)), dim3(256), 0,
-                               st, static_cast<const uint8_t *>(Q->data), Q->pitch_bytes, Q->n,
-                               Q->dim, static_cast<float *>(qn));
+    const BoundPlan bp = (wide || wide_f32) ? BoundPlan() : topk_bound_plan(Q, nb, k);
+    uint32_t *mins = nullptr, *tau = nullptr;
+    int32_t *cnt = nullptr;
+    uint64_t *bcand = nullptr;
+    if (bp.use) {
+        mins = c.take<uint32_t>((size_t)Q->n * bp.groups);
+        tau = c.take<uint32_t>(Q->n);
+        cnt = c.take<int32_t>(Q->n + 1);
+        bcand = c.take<uint64_t>((size_t)Q->n * bp.cap);
     }
-    if (nb > 0) {
+    auto norms = [&](const void *x, int64_t pitch, int64_t n, void *out) {
+        if (n == 0) return;
+        const dim3 grid((unsigned)((n + 3) / 4));
         if (u8)
-            hipLaunchKernelGGL(norms_u8_kernel, dim3((unsigned)((nb + 3) / 4)), dim3(256), 0, st,
-                               brows, B->pitch_bytes, nb, B->dim, static_cast<int32_t *>(bn));
+            hipLaunchKernelGGL(norms_u8_kernel, grid, dim3(256), 0, st, static_cast<const uint8_t *>(x),
+                               pitch, n, Q->dim, static_cast<int32_t *>(out));
         else
-            hipLaunchKernelGGL(norms_f32_kernel, dim3((unsigned)((nb + 3) / 4)), dim3(256), 0, st,
-                               brows, B->pitch_bytes, nb, B->dim, static_cast<float *>(bn));
-    }
+            hipLaunchKernelGGL(norms_f32_kernel, grid, dim3(256), 0, st, static_cast<const uint8_t *>(x),
+                               pitch, n, Q->dim, static_cast<float *>(out));
+    };
+    // the wide kernels read the base's norms; the others take them from the
+    // staged tiles, and cosine needs none
+    if (wide || wide_f32) norms(brows, B->pitch_bytes, nb, bn);
+    if (wide_f32 || u8 || Q->metric == ONNG_L2SQ) norms(Q->data, Q->pitch_bytes, Q->n, qn);
     ONNG_HIP(hipGetLastError());
     if (Q->n == 0) return ONNG_OK;
 
@@ -665,6 +844,8 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     a.bm = topk_bm(k, Q->dtype, Q->dim, side_words);
     a.exclude_self = exclude_self;
     a.rotate = 0;   // set below once the split count is known
+    a.only = nullptr;
+    a.only_above = 0;
     // the staged tile holds a row's components (zero-extended), not its padding
     a.lds_pitch = lds_pitch_for(Q->dtype, B->dim);
     a.out_ids = ids;
@@ -690,6 +871,47 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         set_error("onng_topk: k or dim too large for the on-chip tile");
         return ONNG_ERR_UNSUPPORTED;
     }
+    if (bp.use) {
+        BoundArgs ba;
+        ba.t = a;
+        ba.ns_log2 = bp.ns_log2;
+        ba.group_tiles = bp.group_tiles;
+        ba.quads = bp.quads;
+        ba.groups = bp.groups;
+        ba.mins = mins;
+        ba.tau = tau;
+        ba.cnt = cnt + 1;
+        ba.cand = bcand;
+        ba.cap = bp.cap;
+        auto fn_of = u8 ? topk_bound_fn_u8 : Q->metric == ONNG_L2SQ ? topk_bound_fn_l2 : topk_bound_fn_cosine;
+        const int bm = bp.rw * 16;
+        const int rank = k + (exclude_self ? 1 : 0);
+        for (int m = 0; m < 2; m++) {
+            const void *fn = fn_of(nch_for(Q->dtype, Q->dim), bp.rw, m == 0);
+            ONNG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bp.lds[m]));
+            ba.t.tiles_per_split = bp.per_split[m];
+            void *bargs[] = {&ba};
+            ONNG_HIP(hipLaunchKernel(fn, dim3((unsigned)((Q->n + bm - 1) / bm), (unsigned)bp.splits[m]),
+                                     dim3((unsigned)bound_threads(bp.rw)), bargs, bp.lds[m], st));
+            if (m == 0) {
+                // f32 bounds need no more than 16 bits past the exponent's first
+                const dim3 g((unsigned)((Q->n + 3) / 4)), bl(256);
+                const int top = u8 ? 23 : 31, low = u8 ? 0 : 8;
+                auto sel = bp.groups <= 512 ? bound_select_kernel<8>
+                           : bp.groups <= 1024 ? bound_select_kernel<16> : bound_select_kernel<32>;
+                hipLaunchKernelGGL(sel, g, bl, 0, st, mins, Q->n, bp.groups, rank, top, low, tau, cnt);
+            }
+        }
+        const size_t sl = (size_t)bp.cap * 8;
+        const void *sf = u8 ? (const void *)bound_sort_kernel<true> : (const void *)bound_sort_kernel<false>;
+        const uint64_t *cc = bcand;
+        int cap = bp.cap, kk = k;
+        void *sargs[] = {&cc, &cap, &cnt, &kk, &ids, &dists};
+        ONNG_HIP(hipLaunchKernel(sf, dim3((unsigned)Q->n), dim3(Q->n < 1024 ? 256 : WAVE), sargs, sl, st));
+        // rows that overflowed, if any
+        a.only = cnt;
+        a.only_above = bp.cap;
+    }
     const int nch = nch_for(Q->dtype, Q->dim);
     const void *fn;
     if (u8) fn = topk_fn_for<ONNG_U8, ONNG_L2SQ>(nch);
@@ -713,7 +935,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         ONNG_HIP(hipFuncSetAttribute(mf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds));
         int64_t nq = Q->n;
         int splits = sp, kk = k, kcap = a.kcap;
-        void *margs[] = {&part, &nq, &splits, &kk, &kcap, &ids, &dists};
+        void *margs[] = {&part, &nq, &splits, &kk, &kcap, &ids, &dists, &a.only, &a.only_above};
         ONNG_HIP(hipLaunchKernel(mf, dim3((unsigned)((Q->n + wpb - 1) / wpb)), dim3(wpb * WAVE),
                                  margs, mlds, st));
     }

@@ -64,6 +64,8 @@ struct TopkArgs {
     int32_t splits;           // blocks sharing one row block's base tiles
     int32_t tiles_per_split;
     uint64_t *part;           // splits > 1: [nq][splits][k] keys of each part
+    const int32_t *only;      // null, or [1 + nq]: only[0] != 0 when any row, and
+    int32_t only_above;       // only[1 + row] > only_above when this row, is to be done
 };
 
 // 16 int8 values of (x - 128) at row bytes [c, c+16), zero past dim
@@ -81,6 +83,39 @@ __device__ __forceinline__ i32x4 shifted16(const uint8_t *row, int c, int dim) {
         out[w] = (int32_t)v;
     }
     return out;
+}
+
+// Norms of a staged tile's BN rows (CPR 16-byte chunks each) by nthr threads,
+// sixteen lanes per row: int32 of the shifted u8 rows; f32 in the order of
+// norms_f32_kernel (one component per lane, chains 64 apart, then lanes 32, 16,
+// .. 1 apart), four of its lanes in each of these, so the same bits.
+template <bool U8, int CPR>
+__device__ __forceinline__ void tile_norms(const uint8_t *tile, int lds_pitch, int nthr, uint32_t *out) {
+    const int l = threadIdx.x & 15;
+    for (int r = threadIdx.x / 16; r < BN; r += nthr / 16) {
+        const uint8_t *row = tile + (uint32_t)r * (uint32_t)lds_pitch;
+        if constexpr (U8) {
+            int32_t s = 0;
+            for (int c = l; c < CPR; c += 16) {
+                const i32x4 x = *reinterpret_cast<const i32x4 *>(row + c * 16);
+#pragma unroll
+                for (int w = 0; w < 4; w++) s = __builtin_amdgcn_sdot4(x[w], x[w], s, false);
+            }
+            s = group_sum<16>(s);
+            if (l == 0) out[r] = (uint32_t)s;
+        } else {
+            float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int c = l; c < CPR; c += 16) {
+                const f32x4 x = *reinterpret_cast<const f32x4 *>(row + c * 16);
+#pragma unroll
+                for (int e = 0; e < 4; e++) p[e] = fmaf(x[e], x[e], p[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; e++) p[e] = group_sum<16>(p[e]);
+            const float s = (p[0] + p[2]) + (p[1] + p[3]);
+            if (l == 0) out[r] = __float_as_uint(s);
+        }
+    }
 }
 
 // Bytes of a staged row: what the MFMA operands read (u8: whole 64-byte

@@ -208,3 +208,40 @@ def test_mlp_sizes(B, F, H, T):
     loss, grads = A.mlp_backward(to_dev(X), to_dev(Y), *dev_w, w=to_dev(W))
     for got, ref in zip([y, hid, loss, *grads], [ref_y, ref_h, np.array([ref_loss]), *ref_g]):
         assert np.linalg.norm(host(got) - ref) <= 1e-5 * np.linalg.norm(ref) + 1e-7
+
+
+@pytest.mark.parametrize("kind,nq,nb,dim,k,form", [
+    ("u8", 1, 1024, 128, 8, "cand"), ("u8", 16, 1023, 64, 10, ""), ("u8", 17, 1025, 65, 1, ""),
+    ("u8", 64, 5000, 300, 40, "cand"), ("u8", 65, 4097, 17, 100, ""), ("u8", 1500, 1500, 40, 20, "self"),
+    ("u8", 2049, 2049, 128, 100, "self"), ("u8", 129, 3000, 128, 256, ""), ("u8tie", 200, 6000, 4, 50, ""),
+    ("u8tie", 1300, 1300, 3, 9, "self"), ("f32l2", 3, 70000, 96, 20, ""), ("f32l2", 130, 20000, 33, 100, "cand"),
+    ("f32l2", 1100, 1100, 128, 10, "self"), ("f32l2", 20, 3000, 200, 5, ""), ("f32cos", 64, 2000, 100, 8, "cand"),
+    ("f32cos", 300, 9000, 112, 74, ""), ("f32cos", 10, 1200, 256, 3, ""), ("f32tie", 90, 8000, 5, 30, ""),
+    ("f32tie", 1040, 1040, 6, 12, "self")])
+def test_topk_bound_and_filter(kind, nq, nb, dim, k, form):
+    """Top-k by a bound and a filter at the edges of its layouts: 1 / 16 / 17 / 64
+    / 65 / 128 / 129 query rows, base rows around 1024 and ragged tiles, one to
+    all k-steps, k from 1 to 256, candidate lists, self exclusion, and rows of so
+    few distinct distances that every candidate buffer overflows.  f32 rows hold
+    small integers, whose distances are exact in f32: ids and distances equal
+    the oracle's."""
+    say("topk bound", kind, nq, nb, dim, k, form)
+    A = api()
+    g = np.random.default_rng(nb + k)
+    n = nb + 500 if form == "cand" else nb
+    metric = orc.COS if kind == "f32cos" else orc.L2SQ
+    hi = 3 if kind.endswith("tie") else 200 if kind == "u8" else 9
+    dt = np.uint8 if kind.startswith("u8") else np.float32
+    x = g.integers(0, hi, size=(n, dim)).astype(dt)
+    q = x if form == "self" else g.integers(0, hi, size=(nq, dim)).astype(dt)
+    cand = g.permutation(n)[:nb].astype(np.int32) if form == "cand" else None
+    bv, qv = orc.Vectors.from_array(x, metric), orc.Vectors.from_array(q, metric)
+    B = gpu_vectors(x, metric)
+    if form == "self":
+        rid, rd = orc.knn_graph(bv, k)
+        ids, d = A.build_knn(B, k)
+    else:
+        rid, rd = orc.topk(qv, bv, k, cand=cand)
+        ids, d = A.topk(gpu_vectors(q, metric), B, k, cand=None if cand is None else to_dev(cand))
+    assert np.array_equal(host(ids), rid)
+    assert np.array_equal(host(d).astype(np.float64), rd)
