@@ -20,10 +20,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-# Per-file flags.  topk_wide.hip: MFMA results in ordinary VGPRs, which the
-# epilogue compares directly (in accumulation registers every value first
+# Per-file flags.  The wide top-k kernels: MFMA results in ordinary VGPRs, which
+# the epilogue compares directly (in accumulation registers every value first
 # costs a copy).
-EXTRA = {"topk_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("topk_wide.hip", "topk_wide_bound.hip")}
 
 
 def _compile(src: str) -> str:

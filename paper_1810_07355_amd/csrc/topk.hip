@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
     const int wv = threadIdx.x / WAVE;
     const int nwaves = a.bm / 16;
     const int64_t row0 = (int64_t)blockIdx.x * a.bm;
-    auto skip_row = [&](int64_t row) { return a.only && a.only[1 + row] <= a.only_above; };
+    auto skip_row = [&](int64_t row) { return a.only && !a.only[1 + row]; };
     if (a.only) {
         if (!a.only[0]) return;
         const int64_t row = row0 + threadIdx.x;
@@ -454,13 +454,13 @@ template <bool U8>
 __global__ void __launch_bounds__(256) merge_parts_kernel(const uint64_t *part, int64_t nq,
                                                           int splits, int k, int kcap,
                                                           int32_t *out_ids, void *out_d,
-                                                          const int32_t *only, int only_above) {
+                                                          const int32_t *only) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = lane_id();
     const int wv = threadIdx.x / WAVE;
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv;
     if (row >= nq) return;
-    if (only && (!only[0] || only[1 + row] <= only_above)) return;
+    if (only && (!only[0] || !only[1 + row])) return;
     uint64_t *lst = reinterpret_cast<uint64_t *>(smem) + (size_t)wv * (kcap + WAVE);
     uint64_t *stage = lst + kcap;
     const uint64_t *src = part + (size_t)row * splits * k;
@@ -493,10 +493,10 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(const uint64_t *part, 
 template <int VPL>
 __global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins, int64_t nq, int groups,
                                                            int rank, int top, int low, uint32_t *tau,
-                                                           int32_t *cnt) {
+                                                           int32_t *cnt, int32_t *clear) {
     const int64_t row = (int64_t)blockIdx.x * 4 + uni(threadIdx.x / WAVE);
     const int lane = lane_id();
-    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[0] = 0;   // no row has overflowed
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
     if (row >= nq) return;
     uint32_t x[VPL];
 #pragma unroll
@@ -514,32 +514,35 @@ __global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins,
     }
     if (lane == 0) {
         tau[row] = v | ((1u << low) - 1u);
-        cnt[1 + row] = 0;
+        cnt[row] = 0;
     }
 }
 
-// One block per row: its cnt[1 + row] candidates in order, the k first written
-// (padded when there are fewer).  A row with more than `cap` sets cnt[0] and is
-// left to the general kernel.  Up to 64 candidates sort in registers, more by a
+// One block per row: its cnt[row] candidates in order, the k first written
+// (padded when there are fewer).  A row with more than `cap` is left to the
+// general kernel (redo[1 + row], and redo[0] for any).  Up to 64 candidates sort in registers, more by a
 // bitonic network in LDS; with few rows the block has four waves.
 template <bool U8>
-__global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, int cap, int32_t *cnt,
-                                                        int k, int32_t *out_ids, void *out_d) {
+__global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, int cap, const int32_t *cnt,
+                                                         int k, int32_t *out_ids, void *out_d,
+                                                         int32_t *redo, int64_t row0) {
     extern __shared__ __attribute__((aligned(16))) uint64_t sk[];
     const int64_t row = blockIdx.x;
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int n = uni(cnt[1 + row]);
+    const int n = uni(cnt[row]);
+    if (tid == 0) redo[1 + row0 + row] = n > cap;
     if (n > cap) {
-        if (tid == 0) cnt[0] = 1;
+        if (tid == 0) redo[0] = 1;
         return;
     }
     const uint64_t *src = cand + row * cap;
     auto put = [&](int i, uint64_t key) {
-        out_ids[row * k + i] = i < n ? (int32_t)(uint32_t)key : -1;
+        const int64_t at = (row0 + row) * k + i;
+        out_ids[at] = i < n ? (int32_t)(uint32_t)key : -1;
         if constexpr (U8)
-            reinterpret_cast<int32_t *>(out_d)[row * k + i] = i < n ? (int32_t)(key >> 32) : INT32_MAX;
+            reinterpret_cast<int32_t *>(out_d)[at] = i < n ? (int32_t)(key >> 32) : INT32_MAX;
         else
-            reinterpret_cast<float *>(out_d)[row * k + i] =
+            reinterpret_cast<float *>(out_d)[at] =
                 i < n ? unord_f32((uint32_t)(key >> 32)) : __builtin_inff();
     };
     if (n <= WAVE) {
@@ -720,6 +723,43 @@ BoundPlan topk_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k) {
 
 }  // namespace
 
+namespace topk_detail {
+
+void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int top, int low,
+                         uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st) {
+    auto sel = groups <= 512 ? bound_select_kernel<8> : groups <= 1024 ? bound_select_kernel<16>
+                                                                       : bound_select_kernel<32>;
+    hipLaunchKernelGGL(sel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, mins, nq, groups, rank, top,
+                       low, tau, cnt, clear);
+}
+
+void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cnt, int64_t nq, int k,
+                       int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st) {
+    auto fn = u8 ? bound_sort_kernel<true> : bound_sort_kernel<false>;
+    hipLaunchKernelGGL(fn, dim3((unsigned)nq), dim3(nq < 1024 ? 256 : WAVE), (size_t)cap * 8, st, cand, cap,
+                       cnt, k, ids, dists, redo, row0);
+}
+
+}  // namespace topk_detail
+
+static WideBufs carve_wide(Carver &c, const onng_vectors *Q, int64_t nb, const WidePlan &P) {
+    WideBufs w{};
+    if (!P.use) return w;
+    const int64_t rows = std::min<int64_t>(Q->n, P.chunk);
+    w.mins = c.take<uint32_t>((size_t)rows * P.groups);
+    w.tau = c.take<uint32_t>(rows);
+    w.cnt = c.take<int32_t>(rows);
+    w.cand = c.take<uint64_t>((size_t)rows * P.cap);
+    w.redo = c.take<int32_t>(Q->n + 1);
+    w.bh = c.take<uint8_t>((size_t)nb * P.nch * 64);
+    w.qh = c.take<uint8_t>((size_t)Q->n * P.nch * 64);
+    if (Q->dtype == ONNG_F32) {
+        w.side = c.take<float>(nb);
+        w.len = c.take<float>(2);
+    }
+    return w;
+}
+
 size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand, int32_t k) {
     Carver c(nullptr);
     int64_t nb = n_cand > 0 ? n_cand : B->n;
@@ -729,9 +769,11 @@ size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand
     if (topk_use_wide(Q, nb, k)) {
         c.take<uint64_t>((size_t)Q->n * topk_kcap(k));
         c.take<uint64_t>((size_t)Q->n * WIDE_CB);
+        carve_wide(c, Q, nb, wide_bound_plan(Q, nb, k));
         return c.size() + 256;
     }
     if (topk_use_wide_f32(Q, nb, k)) {
+        carve_wide(c, Q, nb, wide_bound_plan(Q, nb, k));
         c.take<uint8_t>((size_t)nb * FW_NCH * 64);
         c.take<uint8_t>((size_t)Q->n * FW_NCH * 64);
         c.take<uint32_t>(1);
@@ -745,6 +787,7 @@ size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand
     if (bp.use) {
         c.take<uint32_t>((size_t)Q->n * bp.groups);
         c.take<uint32_t>(Q->n);
+        c.take<int32_t>(Q->n);
         c.take<int32_t>(Q->n + 1);
         c.take<uint64_t>((size_t)Q->n * bp.cap);
     }
@@ -800,12 +843,15 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     }
     const BoundPlan bp = (wide || wide_f32) ? BoundPlan() : topk_bound_plan(Q, nb, k);
     uint32_t *mins = nullptr, *tau = nullptr;
-    int32_t *cnt = nullptr;
+    int32_t *cnt = nullptr, *redo = nullptr;
     uint64_t *bcand = nullptr;
+    const WidePlan wp = wide || wide_f32 ? wide_bound_plan(Q, nb, k) : WidePlan();
+    const WideBufs wb = carve_wide(c, Q, nb, wp);
     if (bp.use) {
         mins = c.take<uint32_t>((size_t)Q->n * bp.groups);
         tau = c.take<uint32_t>(Q->n);
-        cnt = c.take<int32_t>(Q->n + 1);
+        cnt = c.take<int32_t>(Q->n);
+        redo = c.take<int32_t>(Q->n + 1);
         bcand = c.take<uint64_t>((size_t)Q->n * bp.cap);
     }
     auto norms = [&](const void *x, int64_t pitch, int64_t n, void *out) {
@@ -845,7 +891,6 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     a.exclude_self = exclude_self;
     a.rotate = 0;   // set below once the split count is known
     a.only = nullptr;
-    a.only_above = 0;
     // the staged tile holds a row's components (zero-extended), not its padding
     a.lds_pitch = lds_pitch_for(Q->dtype, B->dim);
     a.out_ids = ids;
@@ -857,6 +902,11 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         const bool same = !cand && Q->data == B->data && Q->n == B->n &&
                           Q->pitch_bytes == B->pitch_bytes;
         a.rotate = same ? 1 : 0;
+        if (wp.use) {
+            const onng_status s = launch_wide_bound(a, Q, same, wp, wb, st);
+            if (s != ONNG_OK) return s;
+            a.only = wb.redo;   // rows that overflowed, if any
+        }
         return launch_topk_wide_f32(a, Q, same, fqh, fbh, fymax, flist, fcand, st);
     }
     if (wide) {
@@ -864,6 +914,11 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         a.tiles_per_split = (int)((nb + BN - 1) / BN);
         a.part = nullptr;
         a.rotate = (!cand && Q->data == B->data && Q->n == B->n) ? 1 : 0;
+        if (wp.use) {
+            const onng_status s = launch_wide_bound(a, Q, a.rotate != 0, wp, wb, st);
+            if (s != ONNG_OK) return s;
+            a.only = wb.redo;
+        }
         return launch_topk_wide(a, nch_for(ONNG_U8, Q->dim), glist, gcand, st);
     }
     size_t lds = topk_lds_bytes(a.bm, a.kcap, a.cb, a.lds_pitch, side_words);
@@ -880,7 +935,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         ba.groups = bp.groups;
         ba.mins = mins;
         ba.tau = tau;
-        ba.cnt = cnt + 1;
+        ba.cnt = cnt;
         ba.cand = bcand;
         ba.cap = bp.cap;
         auto fn_of = u8 ? topk_bound_fn_u8 : Q->metric == ONNG_L2SQ ? topk_bound_fn_l2 : topk_bound_fn_cosine;
@@ -893,24 +948,13 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
             void *bargs[] = {&ba};
             ONNG_HIP(hipLaunchKernel(fn, dim3((unsigned)((Q->n + bm - 1) / bm), (unsigned)bp.splits[m]),
                                      dim3((unsigned)bound_threads(bp.rw)), bargs, bp.lds[m], st));
-            if (m == 0) {
-                // f32 bounds need no more than 16 bits past the exponent's first
-                const dim3 g((unsigned)((Q->n + 3) / 4)), bl(256);
-                const int top = u8 ? 23 : 31, low = u8 ? 0 : 8;
-                auto sel = bp.groups <= 512 ? bound_select_kernel<8>
-                           : bp.groups <= 1024 ? bound_select_kernel<16> : bound_select_kernel<32>;
-                hipLaunchKernelGGL(sel, g, bl, 0, st, mins, Q->n, bp.groups, rank, top, low, tau, cnt);
-            }
+            // (f32 bounds need no more than 16 bits past the exponent's first)
+            if (m == 0)
+                launch_bound_select(mins, Q->n, bp.groups, rank, u8 ? 23 : 31, u8 ? 0 : 8, tau, cnt, redo, st);
         }
-        const size_t sl = (size_t)bp.cap * 8;
-        const void *sf = u8 ? (const void *)bound_sort_kernel<true> : (const void *)bound_sort_kernel<false>;
-        const uint64_t *cc = bcand;
-        int cap = bp.cap, kk = k;
-        void *sargs[] = {&cc, &cap, &cnt, &kk, &ids, &dists};
-        ONNG_HIP(hipLaunchKernel(sf, dim3((unsigned)Q->n), dim3(Q->n < 1024 ? 256 : WAVE), sargs, sl, st));
+        launch_bound_sort(u8, bcand, bp.cap, cnt, Q->n, k, ids, dists, redo, 0, st);
         // rows that overflowed, if any
-        a.only = cnt;
-        a.only_above = bp.cap;
+        a.only = redo;
     }
     const int nch = nch_for(Q->dtype, Q->dim);
     const void *fn;
@@ -935,7 +979,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         ONNG_HIP(hipFuncSetAttribute(mf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds));
         int64_t nq = Q->n;
         int splits = sp, kk = k, kcap = a.kcap;
-        void *margs[] = {&part, &nq, &splits, &kk, &kcap, &ids, &dists, &a.only, &a.only_above};
+        void *margs[] = {&part, &nq, &splits, &kk, &kcap, &ids, &dists, &a.only};
         ONNG_HIP(hipLaunchKernel(mf, dim3((unsigned)((Q->n + wpb - 1) / wpb)), dim3(wpb * WAVE),
                                  margs, mlds, st));
     }

@@ -28,7 +28,6 @@ namespace onng {
 namespace topk_detail {
 
 constexpr int BOUND_QUEUE = 192;          // candidates a wave holds before it places them
-constexpr uint32_t SAMPLE_ODD = 0x9E3779B1u;
 
 struct BoundArgs {
     TopkArgs t;
@@ -49,14 +48,6 @@ constexpr int bound_threads(int rw) { return rw == 8 ? 512 : 256; }
 inline size_t bound_lds(int lds_pitch, int rw, bool filter) {
     return (size_t)2 * BN * (lds_pitch + 8) +
            (filter ? (size_t)bound_threads(rw) / WAVE * (BOUND_QUEUE * 10 + 64) : 0);
-}
-
-// base row of sampled column i: odd multiples modulo a power of two visit
-// every sample once, neighbouring columns far apart (rows in locality order
-// would put a query's near rows into one group, whose minimum counts once)
-__device__ __forceinline__ int64_t sample_row(uint32_t i, int ns_log2, int64_t nb) {
-    const uint32_t j = (i * SAMPLE_ODD) & ((1u << ns_log2) - 1u);
-    return (int64_t)(((uint64_t)j * (uint64_t)nb) >> ns_log2);
 }
 
 // A block: RW waves with 16 query rows each, over all 64 columns of a tile; for

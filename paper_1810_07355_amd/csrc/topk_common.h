@@ -64,8 +64,8 @@ struct TopkArgs {
     int32_t splits;           // blocks sharing one row block's base tiles
     int32_t tiles_per_split;
     uint64_t *part;           // splits > 1: [nq][splits][k] keys of each part
-    const int32_t *only;      // null, or [1 + nq]: only[0] != 0 when any row, and
-    int32_t only_above;       // only[1 + row] > only_above when this row, is to be done
+    const int32_t *only;      // null, or [1 + nq]: only[0] != 0 when any row is to be
+                              // done, only[1 + row] != 0 when this one is
 };
 
 // 16 int8 values of (x - 128) at row bytes [c, c+16), zero past dim
@@ -83,6 +83,16 @@ __device__ __forceinline__ i32x4 shifted16(const uint8_t *row, int c, int dim) {
         out[w] = (int32_t)v;
     }
     return out;
+}
+
+constexpr uint32_t SAMPLE_ODD = 0x9E3779B1u;
+
+// base row of sampled column i: odd multiples modulo a power of two visit
+// every sample once, neighbouring columns far apart (rows in locality order
+// would put a query's near rows into one group, whose minimum counts once)
+__device__ __forceinline__ int64_t sample_row(uint32_t i, int ns_log2, int64_t nb) {
+    const uint32_t j = (i * SAMPLE_ODD) & ((1u << ns_log2) - 1u);
+    return (int64_t)(((uint64_t)j * (uint64_t)nb) >> ns_log2);
 }
 
 // Norms of a staged tile's BN rows (CPR 16-byte chunks each) by nthr threads,
@@ -182,6 +192,45 @@ __host__ __device__ inline size_t fw_lds_bytes(int kcap) {
 onng_status launch_topk_wide_f32(const TopkArgs &a, const onng_vectors *Q, bool same_rows,
                                  uint8_t *qh, uint8_t *bh, uint32_t *ymax, uint64_t *glist,
                                  uint32_t *gcand, hipStream_t st);
+
+// ---- many query rows by a bound and a filter (topk_wide.hip) -------------
+// The two passes of topk_bound.h for many query rows: a wave holds 64 of them
+// (four 16-row blocks), whose operands stay in registers for the sweep, so each
+// operand read from LDS feeds four matrix instructions.
+constexpr int WB_ROWS = 256;              // query rows per block of four waves
+constexpr int WB_QUEUE = 256;             // candidates a wave holds before it places them
+constexpr int64_t WB_CHUNK = 32768;       // query rows whose candidates are held at a time
+
+struct WidePlan {
+    bool use = false;
+    int nch = 0;                          // 64-byte k-steps per row
+    int64_t chunk = 0;                    // query rows per launch, at most WB_CHUNK
+    int ns_log2 = 0, group_tiles = 0, groups = 0, cap = 0;
+    int splits[2] = {1, 1}, per_split[2] = {0, 0};   // bound, filter
+};
+// workspace of the wide passes, carved by the caller
+struct WideBufs {
+    uint32_t *mins;      // [chunk][groups]
+    uint32_t *tau;       // [chunk]
+    int32_t *cnt;        // [chunk]
+    uint64_t *cand;      // [chunk][cap]
+    int32_t *redo;       // [1 + nq]: rows left to the older kernel
+    uint8_t *bh, *qh;    // converted rows (int8, or f16 of f32 data)
+    float *side;         // [nb] (f32)
+    float *len;          // [2]: largest |y| of the base, of the queries (f32)
+};
+WidePlan wide_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k);
+onng_status launch_wide_bound(const TopkArgs &a, const onng_vectors *Q, bool same_rows, const WidePlan &P,
+                              const WideBufs &w, hipStream_t st);
+
+// Per row an upper bound of the rank-th smallest of its group minima, its
+// counter cleared (and *clear, when given); per row its candidates sorted and
+// the k first written at row0 + row, or redo[1 + row0 + row] and redo[0] set
+// (topk.hip).
+void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int top, int low,
+                         uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st);
+void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cnt, int64_t nq, int k,
+                       int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st);
 
 }  // namespace topk_detail
 }  // namespace onng

@@ -15,6 +15,14 @@ namespace topk_detail {
 
 namespace {
 
+// whether any of a block's ROWS query rows is to be done (a.only given)
+template <int ROWS>
+__device__ __forceinline__ bool wide_any_row(const TopkArgs &a, int64_t row0) {
+    if (!a.only[0]) return false;
+    const int64_t row = row0 + threadIdx.x;
+    return __syncthreads_or((int)threadIdx.x < ROWS && row < a.nq && a.only[1 + row]) != 0;
+}
+
 template <int NCH>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) topk_u8_wide_kernel(TopkArgs a, uint64_t *glist,
                                                            uint64_t *gcand) {
@@ -25,6 +33,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) t
     const int lane = lane_id();
     const int wv = threadIdx.x / WAVE;
     const int64_t row0 = (int64_t)blockIdx.x * WIDE_ROWS;
+    if (a.only && !wide_any_row<WIDE_ROWS>(a, row0)) return;
     const int wl0 = wv * RB * 16;         // the wave's first row within the block
     const int64_t wrow0 = row0 + wl0;
 
@@ -284,6 +293,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) t
         const int lr = wl0 + r;
         const int64_t grow = row0 + lr;
         if (grow >= a.nq) break;
+        if (a.only && !a.only[1 + grow]) continue;
         flush_row(lr);
         const int nl = uni(nlist[lr]);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
@@ -323,6 +333,7 @@ topk_f32_wide_kernel(TopkArgs a, FwRows h, uint64_t *glist, uint32_t *gcand) {
     const int lane = lane_id();
     const int wv = threadIdx.x / WAVE;
     const int64_t row0 = (int64_t)blockIdx.x * FW_ROWS;
+    if (a.only && !wide_any_row<FW_ROWS>(a, row0)) return;
     const int wl0 = wv * RPW;
     const int64_t wrow0 = row0 + wl0;
     const int lpitch = FW_LDS_PITCH;
@@ -583,6 +594,7 @@ topk_f32_wide_kernel(TopkArgs a, FwRows h, uint64_t *glist, uint32_t *gcand) {
         const int lr = wl0 + r;
         const int64_t grow = row0 + lr;
         if (grow >= a.nq) break;
+        if (a.only && !a.only[1 + grow]) continue;
         flush_row(lr);
         const int nl = uni(nlist[lr]);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
@@ -599,7 +611,8 @@ topk_f32_wide_kernel(TopkArgs a, FwRows h, uint64_t *glist, uint32_t *gcand) {
 // f32 rows -> bf16 rows (round to nearest even) of FW_NCH * 64 bytes, zero
 // past dim; one thread per component.
 __global__ void to_bf16_kernel(const uint8_t *src, int64_t pitch, int64_t n, int dim,
-                               uint8_t *dst, int64_t dst_pitch) {
+                               uint8_t *dst, int64_t dst_pitch, const int32_t *only) {
+    if (only && !*only) return;
     constexpr int W = FW_NCH * 32;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n * W) return;
@@ -616,7 +629,8 @@ __global__ void to_bf16_kernel(const uint8_t *src, int64_t pitch, int64_t n, int
 // max over i of sqrt(n2[i]) (non-negative floats order as their bits);
 // out must hold 0 first.
 __global__ void zero_u32_kernel(uint32_t *p) { *p = 0u; }
-__global__ void max_len_kernel(const float *n2, int64_t n, uint32_t *out) {
+__global__ void max_len_kernel(const float *n2, int64_t n, uint32_t *out, const int32_t *only) {
+    if (only && !*only) return;
     float m = 0.0f;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
@@ -652,13 +666,13 @@ onng_status launch_topk_wide_f32(const TopkArgs &a, const onng_vectors *Q, bool 
     const int64_t hp = FW_NCH * 64;
     const int W = FW_NCH * 32;
     hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((a.nb * W + 255) / 256)), dim3(256), 0, st,
-                       a.b, a.b_pitch, a.nb, a.dim, bh, hp);
+                       a.b, a.b_pitch, a.nb, a.dim, bh, hp, a.only);
     if (!same_rows)
         hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((a.nq * W + 255) / 256)), dim3(256), 0,
-                           st, a.q, a.q_pitch, a.nq, a.dim, qh, hp);
+                           st, a.q, a.q_pitch, a.nq, a.dim, qh, hp, a.only);
     hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(1), 0, st, ymax);
     hipLaunchKernelGGL(max_len_kernel, dim3(1024), dim3(256), 0, st,
-                       reinterpret_cast<const float *>(a.bn), a.nb, ymax);
+                       reinterpret_cast<const float *>(a.bn), a.nb, ymax, a.only);
     ONNG_HIP(hipGetLastError());
     FwRows h;
     h.q = same_rows ? bh : qh;

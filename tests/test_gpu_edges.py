@@ -245,3 +245,29 @@ def test_topk_bound_and_filter(kind, nq, nb, dim, k, form):
         ids, d = A.topk(gpu_vectors(q, metric), B, k, cand=None if cand is None else to_dev(cand))
     assert np.array_equal(host(ids), rid)
     assert np.array_equal(host(d).astype(np.float64), rd)
+
+
+@pytest.mark.parametrize("kind,n,dim,k", [("f32l2", 33000, 1, 5), ("f32l2", 33001, 33, 20), ("f32cos", 32800, 96, 256),
+                                          ("f32l2", 40000, 128, 100), ("f32tie", 33000, 4, 20),
+                                          ("u8", 65600, 64, 100), ("u8", 66000, 17, 10), ("u8tie", 65536, 3, 12)])
+def test_topk_wide_bound_and_filter(kind, n, dim, k):
+    """The wide two-pass kNN over its k-steps (one to four of 32 f16 components,
+    one and two of 64 bytes), more than one chunk of query rows with a ragged
+    last block, k up to 256, and rows whose few distinct distances overflow
+    every candidate buffer; integer rows, whose f32 distances are exact, so the
+    sampled rows equal the oracle's."""
+    say("wide bound", kind, n, dim, k)
+    A = api()
+    g = np.random.default_rng(n + dim)
+    metric = orc.COS if kind == "f32cos" else orc.L2SQ
+    hi = 2 if kind.endswith("tie") else 250 if kind == "u8" else 16
+    x = g.integers(0, hi, size=(n, dim)).astype(np.uint8 if kind.startswith("u8") else np.float32)
+    if kind == "f32l2":
+        x[:, 0] += np.arange(n) % 1009   # (one component alone has few distinct values)
+    bv = orc.Vectors.from_array(x, metric)
+    rows = np.unique(np.concatenate([np.arange(70), np.arange(n - 70, n), [255, 256, 16639, 16640, 32767],
+                                     g.choice(n, 60, replace=False)])).astype(np.int32)
+    rid, rd = orc.knn_graph(bv, k, rows=rows)
+    ids, d = A.build_knn(gpu_vectors(x, metric), k)
+    assert np.array_equal(host(ids)[rows], rid)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
