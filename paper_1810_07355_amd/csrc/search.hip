@@ -32,6 +32,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "dist.h"
 #include "onng_internal.h"
@@ -82,14 +83,6 @@ struct Q<ONNG_U8, ONNG_L2SQ> {
             }
         }
     }
-    // this lane's pieces of a row (zero where the lane has none)
-    __device__ void fetch(const uint8_t *row, int p, int L, int n16, u32x4 *x) const {
-#pragma unroll
-        for (int t = 0; t < PPL; t++) {
-            int pc = p + t * L;
-            x[t] = pc < n16 ? load16(row + pc * 16) : u32x4{0, 0, 0, 0};
-        }
-    }
     // sum over this lane's pieces of (x - q)^2
     __device__ uint32_t fold(const u32x4 *x, float) const {
         uint32_t s = qq;
@@ -117,13 +110,6 @@ struct Q {
                 int c = pc * N + e;
                 q[t][e] = (pc < n16 && c < dim) ? qrow[c] : 0.0f;
             }
-        }
-    }
-    __device__ void fetch(const uint8_t *row, int p, int L, int n16, u32x4 *x) const {
-#pragma unroll
-        for (int t = 0; t < PPL; t++) {
-            int pc = p + t * L;
-            x[t] = pc < n16 ? load16(row + pc * 16) : u32x4{0, 0, 0, 0};
         }
     }
     // this lane's part of sum (x - q)^2, or of <x, q> for cosine
@@ -176,14 +162,25 @@ struct LdsWave {
     float *misc;
 };
 
+// The launch's arguments, read again from the argument segment where they are
+// used.  The arguments of the rare parts (set-up, probe phase, output) would
+// otherwise be loaded once and kept, and the scalar registers that they then
+// take are missing in the expansion loop.
+__device__ __forceinline__ const SearchKArgs &late_args() {
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const SearchKArgs *)p;
+}
+
 }  // namespace
 
 template <int DT, int MT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3, 8)))
-search_kernel(SearchKArgs a) {
+search_kernel(SearchKArgs a0) {
     typedef Q<DT, MT> QT;
     constexpr bool INT = QT::INT;
     extern __shared__ __attribute__((aligned(16))) char smem[];
+    const SearchKArgs &a = a0;
     const int lane = lane_id();
     const int wib = uni(threadIdx.x / WAVE);   // wave-uniform: derived pointers stay scalar
     const int slot = blockIdx.x * a.waves_per_block + wib;
@@ -220,6 +217,18 @@ search_kernel(SearchKArgs a) {
     const int p = lane & (L - 1);
     const int grp = lane / L;
     const int rpp = WAVE / L;   // rows per pass
+    // byte offsets of this lane's pieces of a row
+    int piece[QT::PPL];
+    bool has_piece[QT::PPL];
+#pragma unroll
+    for (int e = 0; e < QT::PPL; e++) {
+        has_piece[e] = p + e * L < a.n16;
+        piece[e] = min(p + e * L, a.n16 - 1) * 16;
+    }
+    // row scales: row id's is at scales + id * scale_pitch
+    const uint8_t *scales = a.scale_in_row ? a.base + a.base_pitch - 4
+                                           : reinterpret_cast<const uint8_t *>(a.base_scale);
+    const uint32_t scale_pitch = a.scale_in_row ? (uint32_t)a.base_pitch : 4u;
     // on-chip visited bits: 2^vis_log2 words, one bit per id of a window of
     // W consecutive ids (the rows are in locality order, so a query's
     // neighbourhood has nearby ids); other ids use the global bitset
@@ -234,30 +243,32 @@ search_kernel(SearchKArgs a) {
         const uint64_t t_start = wall_clock64();
 
         // ---------------------------------------------- per-query setup --
-        const int k = a.k_pq ? min(max(uni(a.k_pq[qi]), 1), a.k_stride) : a.k;
-        float eps = a.eps_pq ? unif(a.eps_pq[qi]) : a.eps;
-        uint32_t ep = a.ep_pq ? uniu(a.ep_pq[qi]) : a.ep;
-        if (a.range_from) {
-            eps = unif(a.range_from[qi].eps);
-            ep = uniu(a.range_from[qi].e_p);
+        const SearchKArgs &as = late_args();
+        const int k = as.k_pq ? min(max(uni(as.k_pq[qi]), 1), as.k_stride) : as.k;
+        float eps = as.eps_pq ? unif(as.eps_pq[qi]) : as.eps;
+        uint32_t ep = as.ep_pq ? uniu(as.ep_pq[qi]) : as.ep;
+        if (as.range_from) {
+            eps = unif(as.range_from[qi].eps);
+            ep = uniu(as.range_from[qi].e_p);
         }
         float cost = eps;
         float f = range_factor(eps, MT);
-        if (a.two_phase) {
+        if (as.two_phase) {
             f = F_INF;
-            ep = a.ep_first;
+            ep = as.ep_first;
         }
-        const int pool_q = a.has_rr ? min(a.pool_cap, max(k, a.pool_factor * k)) : k;
-        int max_dc = a.max_dc_pq ? uni(a.max_dc_pq[qi]) : a.max_dc;
+        const int pool_q = as.has_rr ? min(as.pool_cap, max(k, as.pool_factor * k)) : k;
+        int max_dc = as.max_dc_pq ? uni(as.max_dc_pq[qi]) : as.max_dc;
         if (max_dc <= 0) max_dc = INT32_MAX;
         // budget relative to the predicted cost of the chosen range
         auto cost_budget = [&](float c) {
-            if (a.max_dc_factor > 0.0f) {
-                float b = fminf(a.max_dc_factor * c, 2.0e9f);
+            const float factor = late_args().max_dc_factor;
+            if (factor > 0.0f) {
+                float b = fminf(factor * c, 2.0e9f);
                 max_dc = min(max_dc, max(64, (int)b));
             }
         };
-        if (a.range_from) cost_budget(unif(a.range_from[qi].cost));
+        if (as.range_from) cost_budget(unif(as.range_from[qi].cost));
 
         QT qr;
         const uint8_t *qrow = a.qry + (size_t)qi * a.q_pitch;
@@ -271,6 +282,8 @@ search_kernel(SearchKArgs a) {
         uint64_t spill_min = KEY_MAX;
         int log_n = 0;          // words of the global bitset this query made non-zero
         int dc = 0, hops = 0;
+        // expansions of the probe phase (0: no such phase)
+        const int probe_end = as.two_phase ? (int)as.probe_hops : 0;
         int scanned = 0;   // adjacency entries read (sum of min(deg, e_p) over expansions)
         int flags = 0;
         bool rfull = false;
@@ -278,11 +291,17 @@ search_kernel(SearchKArgs a) {
         // guessed next expansion (see the expansion loop)
         constexpr uint32_t NO_SPEC = 0xFFFFFFFFu;
         uint32_t spec_id = NO_SPEC;
-        int64_t spec_e0 = 0, spec_deg = 0;
+        int64_t spec_e0 = 0;
+        int spec_deg = 0;
         uint32_t spec_nb = 0, spec_nb1 = 0;
         bool spec_vis = false;
-        // per guessed id, read ahead: its visited bit, and whether its bitset word was zero
-        bool spec_bit = false, spec_bit1 = false, spec_wz = false, spec_wz1 = false;
+        // offsets read ahead: lanes 0 and 1 those of next1, lanes 2 and 3 those
+        // of ofs_id (next2 of the latest expansion)
+        int64_t ofs = 0;
+        uint32_t ofs_id = NO_SPEC;
+        // bitset words of the guessed ids, read ahead (first looked at by the
+        // guessed expansion: a test beside the read would wait for it there)
+        uint32_t spec_wd = 0, spec_wd1 = 0;
 
         // the on-chip window: W ids around the first seed, within [0, n)
         uint32_t w0 = 0;
@@ -298,13 +317,12 @@ search_kernel(SearchKArgs a) {
 
         // -------------------------------------------------- helpers ------
         // Mark a batch of ids visited; returns whether this lane's id is new.
-        // known_ok: the caller read this id's bitset word after every earlier
-        // mark of the query (known_bit: the id's bit, known_zero: the whole
-        // word was zero); the mark then needs no reply, and *from_known tells
+        // known_ok: `known` is this id's bitset word, read after every earlier
+        // mark of the query; the mark then needs no reply, and *from_known tells
         // the caller the answer came from that word (an id repeated in one
         // list looks new in each copy: see dedupe_known).
-        auto visit = [&](bool valid, uint32_t id, bool known_ok = false, bool known_bit = false,
-                         bool known_zero = false, bool *from_known = nullptr) -> bool {
+        auto visit = [&](bool valid, uint32_t id, bool known_ok = false, uint32_t known = 0u,
+                         bool *from_known = nullptr) -> bool {
             const uint32_t off = id - w0;   // wraps below the window
             const bool inw = valid && off < W;
             const bool outw = valid && !inw;
@@ -315,8 +333,8 @@ search_kernel(SearchKArgs a) {
             } else if (outw) {
                 const uint32_t bit = 1u << (id & 31);
                 if (known_ok) {
-                    isnew = !known_bit;
-                    first = known_zero;
+                    isnew = (known & bit) == 0u;
+                    first = known == 0u;
                     if (isnew)
                         __hip_atomic_fetch_or(&gbits[id >> 5], bit, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
@@ -381,48 +399,53 @@ search_kernel(SearchKArgs a) {
         };
 
         // Distances of rows lds.ids[0..u) -> kbuf[i] as keys (u <= 128).  A lane
-        // group of L lanes takes one row; the loads of UP row passes are
-        // issued together so that several rows per lane are in flight.
-        auto batch_keys = [&](int u) {
-            constexpr int UP = DT == ONNG_FP8_E4M3 ? 2 : 4;
-            for (int r0 = 0; r0 < u; r0 += rpp * UP) {
-                u32x4 x[UP][QT::PPL];
-                uint32_t rid[UP];
-                float sc[UP];
+        // group of L lanes takes one row; NP row passes are requested together.
+        // No load sits under a lane mask (a lane without a row or a piece reads
+        // the last one again and its piece is cleared before use): masked loads
+        // became branches, between which the compiler waited for memory, so
+        // that the passes of a batch were served one after the other.
+        auto row_passes = [&](auto np_c, int r0, int u) __attribute__((always_inline)) {
+            constexpr int NP = decltype(np_c)::value;
+            u32x4 x[NP][QT::PPL];
+            uint32_t rid[NP];
+            float sc[NP];
 #pragma unroll
-                for (int up = 0; up < UP; up++) {
-                    int row = r0 + up * rpp + grp;
-                    rid[up] = row < u ? lds.ids[row] : 0u;
-                }
+            for (int t = 0; t < NP; t++) rid[t] = lds.ids[min(r0 + t * rpp + grp, u - 1)];
 #pragma unroll
-                for (int up = 0; up < UP; up++) {
-                    int row = r0 + up * rpp + grp;
-                    const uint8_t *rp = a.base + (size_t)rid[up] * a.base_pitch;
-                    qr.fetch(rp, p, L, row < u ? a.n16 : 0, x[up]);
-                    sc[up] = 1.0f;
-                    if constexpr (DT == ONNG_FP8_E4M3) {
-                        // the row's scale (in its own line when the rows carry
-                        // it); the lanes of a row read one address
-                        float v = 1.0f;
-                        if (row < u)
-                            v = a.scale_in_row ? *reinterpret_cast<const float *>(rp + a.base_pitch - 4)
-                                               : a.base_scale[rid[up]];
-                        sc[up] = v;
-                    }
-                }
+            for (int t = 0; t < NP; t++) {
+                const uint8_t *rp = a.base + (uint64_t)rid[t] * (uint32_t)a.base_pitch;
 #pragma unroll
-                for (int up = 0; up < UP; up++) {
-                    int row = r0 + up * rpp + grp;
-                    typename DistTraits<DT>::acc_t acc = qr.fold(x[up], sc[up]);
-                    // sum over the L lanes of the row (DPP, no LDS round trip)
-                    acc = group_sum_rt(acc, L);
-                    if (row < u && p == 0) {
-                        uint32_t dord;
-                        if constexpr (INT) dord = acc;
-                        else dord = ord_f32(MT == ONNG_COSINE ? 1.0f - acc : acc);
-                        kbuf[row] = make_key(dord, rid[up]);
-                    }
+                for (int e = 0; e < QT::PPL; e++) x[t][e] = load16(rp + piece[e]);
+                sc[t] = 1.0f;
+                // the row's scale (in its own line when the rows carry it); the
+                // lanes of a row read one address
+                if constexpr (DT == ONNG_FP8_E4M3)
+                    sc[t] = *reinterpret_cast<const float *>(scales + (uint64_t)rid[t] * scale_pitch);
+            }
+#pragma unroll
+            for (int t = 0; t < NP; t++) {
+                const int row = r0 + t * rpp + grp;
+#pragma unroll
+                for (int e = 0; e < QT::PPL; e++) {
+                    const uint32_t m = has_piece[e] ? ~0u : 0u;
+                    x[t][e] &= u32x4{m, m, m, m};
                 }
+                // sum over the L lanes of the row (DPP, no LDS round trip)
+                const typename DistTraits<DT>::acc_t acc = group_sum_rt(qr.fold(x[t], sc[t]), L);
+                if (row < u && p == 0) {
+                    uint32_t dord;
+                    if constexpr (INT) dord = acc;
+                    else dord = ord_f32(MT == ONNG_COSINE ? 1.0f - acc : acc);
+                    kbuf[row] = make_key(dord, rid[t]);
+                }
+            }
+        };
+        auto batch_keys = [&](int u) __attribute__((always_inline)) {
+            for (int r0 = 0; r0 < u; r0 += 4 * rpp) {
+                const int left = u - r0;
+                if (left > 2 * rpp) row_passes(std::integral_constant<int, 4>(), r0, u);
+                else if (left > rpp) row_passes(std::integral_constant<int, 2>(), r0, u);
+                else row_passes(std::integral_constant<int, 1>(), r0, u);
             }
             wave_sync();
         };
@@ -579,8 +602,8 @@ search_kernel(SearchKArgs a) {
             uint64_t key = lane < u ? kbuf[lane] : KEY_MAX;
             wave_sync();
             key = wave_sort(key, pow2_at_least(u));
-            if (a.two_phase) lds.misc[lane] = lane < u ? key_dist<INT>(key) : 0.0f;
-            if (a.two_phase && lane == 0) lds.misc[64] = (float)u;
+            if (probe_end > 0) lds.misc[lane] = lane < u ? key_dist<INT>(key) : 0.0f;
+            if (probe_end > 0 && lane == 0) lds.misc[64] = (float)u;
             // every seed enters S (no range test) and is offered to R
             absorb(key, u, false);
         }
@@ -596,29 +619,53 @@ search_kernel(SearchKArgs a) {
                 refill();
                 if (head == size) break;
             }
-            uint64_t sk = uni64(lds.S[head]);
+            // the pop and the two keys behind it in one read
+            const uint64_t front = lds.S[min(head + lane, size - 1)];
+            const uint64_t sk = readlane64(front, 0);
+            const uint32_t next1 = head + 1 < size ? (uint32_t)readlane64(front, 1) : NO_SPEC;
+            const uint32_t next2 = head + 2 < size ? (uint32_t)readlane64(front, 2) : NO_SPEC;
             head++;
             float thr = threshold(rfull, r, f);
             if (key_dist<INT>(sk) > thr) break;                        // d(s,q) > r(1+eps)
             hops++;
             const uint32_t s = (uint32_t)sk;
-            // adjacency of s: prefetched during the previous expansion when
-            // that one guessed this pop, else read now
+            // adjacency of s: read ahead when the previous expansion guessed
+            // this pop, else read now
             const bool hit = s == spec_id;
             spec_id = NO_SPEC;
-            int64_t e0, deg;
+            int64_t e0;
+            int deg;
             if (hit) {
                 e0 = spec_e0;
                 deg = spec_deg;
             } else {
                 e0 = a.offsets[s];
-                deg = a.offsets[s + 1] - e0;
+                deg = (int)(a.offsets[s + 1] - e0);
             }
-            const int64_t np = (int64_t)ep < deg ? (int64_t)ep : deg;
-            scanned += (int)np;
+            const int np = (int)min(ep, (uint32_t)deg);
+            scanned += np;
+            // The next pop is next1 unless this expansion finds a nearer node
+            // (at the measured settings next1 it is in 62 to 94 % of the
+            // expansions), so its reads start now: the offsets of next1 and of
+            // next2 are requested here, and where next1 was next2 one
+            // expansion ago its offsets are known and the adjacency itself is
+            // requested before this expansion's rows.
+            const bool ahead = next1 != NO_SPEC && next1 == ofs_id;
+            int64_t n_e0 = 0;
+            int n_deg = 0;
+            if (ahead) {
+                n_e0 = readlane64(ofs, 2);
+                n_deg = (int)(readlane64(ofs, 3) - n_e0);
+            }
+            {
+                const uint32_t id = (lane & 2) ? next2 : next1;
+                ofs = a.offsets[(size_t)(id != NO_SPEC ? id : 0u) + (lane & 1)];
+                ofs_id = next2;
+            }
             // The edges in groups of up to two 64-edge chunks: ids and visited
             // marks of the group, then one distance batch for its new nodes.
-            for (int64_t g0 = 0; g0 < np; g0 += 2 * WAVE) {
+            for (int g0 = 0;; g0 += 2 * WAVE) {
+                const bool last = g0 + 2 * WAVE >= np;
                 int u = 0;
                 const bool pre = hit && g0 == 0;
                 if (pre && spec_vis) {
@@ -626,10 +673,10 @@ search_kernel(SearchKArgs a) {
                     const bool v0 = lane < np && (int64_t)spec_nb < a.n_base;
                     const bool v1 = WAVE + lane < np && (int64_t)spec_nb1 < a.n_base;
                     bool k0 = false, k1 = false;
-                    bool n0 = visit(v0, spec_nb, true, spec_bit, spec_wz, &k0);
+                    bool n0 = visit(v0, spec_nb, true, spec_wd, &k0);
                     bool n1 = false;
-                    if (WAVE < np) n1 = visit(v1, spec_nb1, true, spec_bit1, spec_wz1, &k1);
-                    dedupe_known(spec_nb, n0, k0, spec_nb1, n1, k1);
+                    if (WAVE < np) n1 = visit(v1, spec_nb1, true, spec_wd1, &k1);
+                    if (ballot(k0 || k1)) dedupe_known(spec_nb, n0, k0, spec_nb1, n1, k1);
                     uint64_t m = ballot(n0);
                     if (n0) lds.ids[mbcnt(m)] = spec_nb;
                     u = __popcll(m);
@@ -639,9 +686,9 @@ search_kernel(SearchKArgs a) {
                 } else {
 #pragma unroll
                     for (int cc = 0; cc < 2; cc++) {
-                        const int64_t c0 = g0 + cc * WAVE;
+                        const int c0 = g0 + cc * WAVE;
                         if (c0 >= np) break;
-                        const int64_t j = c0 + lane;
+                        const int j = c0 + lane;
                         uint32_t id;
                         if (pre) id = j < np ? (cc == 0 ? spec_nb : spec_nb1) : 0u;
                         else id = j < np ? (uint32_t)a.nbrs[e0 + j] : 0u;
@@ -652,18 +699,51 @@ search_kernel(SearchKArgs a) {
                         u += __popcll(m);
                     }
                 }
-                if (u == 0) continue;
-                wave_sync();
-                batch_keys(u);
-                dc += u;
-                uint64_t k0 = lane < u ? kbuf[lane] : KEY_MAX;
-                uint64_t k1 = lane + WAVE < u ? kbuf[lane + WAVE] : KEY_MAX;
-                wave_sync();
+                if (u == 0 && !last) continue;
+                // the guess's reads: 0 nothing usable, 1 offsets requested,
+                // 2 adjacency requested, 3 visited words requested
+                int stage = 0;
+                int nl0 = 0, nl1 = 0;
+                auto read_adjacency = [&](int64_t g_e0, int g_deg) {
+                    spec_e0 = g_e0;
+                    spec_deg = g_deg;
+                    nl0 = min(spec_deg, WAVE);
+                    nl1 = min(spec_deg - nl0, WAVE);
+                    spec_nb = lane < nl0 ? (uint32_t)a.nbrs[spec_e0 + lane] : 0u;
+                    spec_nb1 = lane < nl1 ? (uint32_t)a.nbrs[spec_e0 + WAVE + lane] : 0u;
+                    stage = 2;
+                };
+                auto read_visited = [&]() {
+                    // the marks of this expansion are complete before the
+                    // visited words of the guess are read (those outside the
+                    // window: the others are on chip)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    spec_wd = 0u;
+                    spec_wd1 = 0u;
+                    if (lane < nl0 && (int64_t)spec_nb < a.n_base && spec_nb - w0 >= W)
+                        spec_wd = __hip_atomic_load(&gbits[spec_nb >> 5], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+                    if (lane < nl1 && (int64_t)spec_nb1 < a.n_base && spec_nb1 - w0 >= W)
+                        spec_wd1 = __hip_atomic_load(&gbits[spec_nb1 >> 5], __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+                    stage = 3;
+                };
+                if (last && ahead) read_adjacency(n_e0, n_deg);
+                uint64_t k0 = KEY_MAX, k1 = KEY_MAX;
+                int nk = 0;
+                if (u > 0) {
+                    wave_sync();
+                    batch_keys(u);
+                    dc += u;
+                    k0 = lane < u ? kbuf[lane] : KEY_MAX;
+                    k1 = lane + WAVE < u ? kbuf[lane + WAVE] : KEY_MAX;
+                    wave_sync();
+                }
+                if (stage == 2) read_visited();
                 // Keys that can neither enter S (beyond the current range,
                 // which only shrinks) nor the pool (beyond its last key when
                 // full) are dropped before sorting.
-                int nk;
-                {
+                if (u > 0) {
                     const float thr0 = threshold(rfull, r, f);
                     const uint64_t plast = npool == pool_q ? lds.pool[pool_q - 1] : KEY_MAX;
                     bool keep0 = lane < u && (key_dist<INT>(k0) <= thr0 || k0 < plast);
@@ -671,7 +751,7 @@ search_kernel(SearchKArgs a) {
                     uint64_t m0 = ballot(keep0), m1 = ballot(keep1);
                     const int n0 = __popcll(m0);
                     nk = n0 + __popcll(m1);
-                    if (nk < u) {
+                    if (nk < u && nk > 0) {
                         if (keep0) kbuf[mbcnt(m0)] = k0;
                         if (keep1) kbuf[n0 + mbcnt(m1)] = k1;
                         wave_sync();
@@ -681,66 +761,57 @@ search_kernel(SearchKArgs a) {
                     }
                 }
                 const int na = min(nk, WAVE), nb2 = nk - na;
+                if (na > 0) k0 = wave_sort(k0, pow2_at_least(na));
+                if (nb2 > 0) k1 = wave_sort(k1, pow2_at_least(nb2));
                 // Guess the next pop (the smaller of S's head and this group's
-                // minimum, when within range and no spilled key is smaller)
-                // and start reading its adjacency (two chunks) and visited bits
-                // while the batch is sorted and merged.  A wrong guess only
-                // wastes the reads.
-                bool go = false;
+                // minimum, when within range and no spilled key is smaller).
+                // Where it is next1 its reads are under way; else they start
+                // here, a dependent chain (offsets, adjacency, visited words)
+                // of which each step is issued one merge after the previous
+                // one, so that its latency overlaps the merge.  A wrong guess
+                // only wastes the reads.
                 int64_t spec_ofs = 0;
-                if (g0 + 2 * WAVE >= np) {
-                    uint64_t bmin = nk > 0 ? wave_min64(k0 < k1 ? k0 : k1) : KEY_MAX;
-                    uint64_t smin = head < size ? lds.S[head] : KEY_MAX;
-                    uint64_t cand = uni64(bmin < smin ? bmin : smin);
-                    go = cand != KEY_MAX && !(spill_n > 0 && spill_min < cand) &&
-                         key_dist<INT>(cand) <= threshold(rfull, r, f);
-                    if (go) {
+                if (last) {
+                    uint64_t cand = head < size ? uni64(lds.S[head]) : KEY_MAX;
+                    if (na > 0) {
+                        const uint64_t b0 = readlane64(k0, 0);
+                        cand = b0 < cand ? b0 : cand;
+                    }
+                    if (nb2 > 0) {
+                        const uint64_t b1 = readlane64(k1, 0);
+                        cand = b1 < cand ? b1 : cand;
+                    }
+                    if (cand != KEY_MAX && !(spill_n > 0 && spill_min < cand) &&
+                        key_dist<INT>(cand) <= threshold(rfull, r, f)) {
                         spec_id = (uint32_t)cand;
-                        // lanes 0 and 1 read the two offsets with a vector load,
-                        // which the sort's LDS traffic does not wait for
-                        spec_ofs = a.offsets[spec_id + (lane & 1)];
+                        if (spec_id != next1) {
+                            // lanes 0 and 1 read the two offsets with a vector load,
+                            // which the merges' LDS traffic does not wait for
+                            spec_ofs = a.offsets[spec_id + (lane & 1)];
+                            stage = 1;
+                        } else if (stage == 0) {
+                            const int64_t o = readlane64(ofs, 0);
+                            read_adjacency(o, (int)(readlane64(ofs, 1) - o));
+                        }
+                    } else {
+                        stage = 0;
                     }
                 }
-                if (na > 0) k0 = wave_sort(k0, pow2_at_least(na));
-                // The guess's reads form a dependent chain (offsets, then
-                // adjacency, then visited bits); each step is issued one
-                // merge after the previous one so that its latency overlaps it.
                 if (na > 0) absorb_pool(k0, na);
-                int nl0 = 0, nl1 = 0;
-                if (go) {
-                    spec_e0 = readlane64(spec_ofs, 0);
-                    spec_deg = readlane64(spec_ofs, 1) - spec_e0;
-                    nl0 = (int)(spec_deg < WAVE ? spec_deg : WAVE);
-                    nl1 = (int)(spec_deg < 2 * WAVE ? spec_deg - nl0 : WAVE);
-                    spec_nb = lane < nl0 ? (uint32_t)a.nbrs[spec_e0 + lane] : 0u;
-                    spec_nb1 = lane < nl1 ? (uint32_t)a.nbrs[spec_e0 + WAVE + lane] : 0u;
+                if (stage == 2) read_visited();
+                if (stage == 1) {
+                    const int64_t o = readlane64(spec_ofs, 0);
+                    read_adjacency(o, (int)(readlane64(spec_ofs, 1) - o));
                 }
                 if (na > 0) absorb_s(k0, na, true);
-                spec_vis = go;
-                if (spec_vis) {
-                    // the marks of this expansion are complete before the
-                    // visited words of the guess are read (those outside the
-                    // window: the others are on chip)
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                    uint32_t wd = 0u, wd1 = 0u;
-                    if (lane < nl0 && (int64_t)spec_nb < a.n_base && spec_nb - w0 >= W)
-                        wd = __hip_atomic_load(&gbits[spec_nb >> 5], __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-                    if (lane < nl1 && (int64_t)spec_nb1 < a.n_base && spec_nb1 - w0 >= W)
-                        wd1 = __hip_atomic_load(&gbits[spec_nb1 >> 5], __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-                    spec_bit = (wd >> (spec_nb & 31)) & 1u;
-                    spec_bit1 = (wd1 >> (spec_nb1 & 31)) & 1u;
-                    spec_wz = wd == 0u;
-                    spec_wz1 = wd1 == 0u;
-                }
-                if (nb2 > 0) {
-                    k1 = wave_sort(k1, pow2_at_least(nb2));
-                    absorb(k1, nb2, true);
-                }
+                if (stage == 2) read_visited();
+                spec_vis = stage == 3;
+                if (nb2 > 0) absorb(k1, nb2, true);
+                if (last) break;
             }
 
-            if (a.two_phase && hops == (int)a.probe_hops) {
+            if (probe_end > 0 && hops == probe_end) {
+                const SearchKArgs &ap = late_args();
                 // ---- state after the probe expansions -> search range ----
                 if (spill_n > 0) refill();   // the smallest keys of S on chip
                 int nseed = (int)lds.misc[64];
@@ -756,29 +827,30 @@ search_kernel(SearchKArgs a) {
                 else if (lane == 11) fv = m > 0 ? key_dist<INT>(lds.S[head + m - 1]) : rmax;
                 else if (lane == 12) fv = rmax;
                 else if (lane == 13) fv = (float)dc;
-                if (a.feat_out && lane < ONNG_NFEAT) a.feat_out[(size_t)qi * ONNG_NFEAT + lane] = fv;
-                if (a.has_pred) {
-                    eps = predict_eps(a.pred, fv, MT, qi, lane, lds.misc + 72, &cost);
+                if (ap.feat_out && lane < ONNG_NFEAT) ap.feat_out[(size_t)qi * ONNG_NFEAT + lane] = fv;
+                if (ap.has_pred) {
+                    eps = predict_eps(ap.pred, fv, MT, qi, lane, lds.misc + 72, &cost);
                     eps = unif(eps);
                     cost = unif(cost);
-                    if (a.pred.mode == ONNG_PRED_CURVE) cost_budget(cost);
-                    ep = a.pred.we >= 0.0f ? dynamic_ep(eps, a.pred.e0, a.pred.we)
-                                           : (a.ep_pq ? uniu(a.ep_pq[qi]) : a.ep);
+                    if (ap.pred.mode == ONNG_PRED_CURVE) cost_budget(cost);
+                    ep = ap.pred.we >= 0.0f ? dynamic_ep(eps, ap.pred.e0, ap.pred.we)
+                                           : (ap.ep_pq ? uniu(ap.ep_pq[qi]) : ap.ep);
                 } else {
-                    eps = a.eps_pq ? unif(a.eps_pq[qi]) : a.eps;
-                    ep = a.ep_pq ? uniu(a.ep_pq[qi]) : a.ep;
+                    eps = ap.eps_pq ? unif(ap.eps_pq[qi]) : ap.eps;
+                    ep = ap.ep_pq ? uniu(ap.ep_pq[qi]) : ap.ep;
                 }
                 f = range_factor(eps, MT);
                 s_prune(threshold(rfull, r, f));
-                if (a.predict_only) break;   // the range is all this pass reports
+                if (ap.predict_only) break;   // the range is all this pass reports
             }
         }
 
         // ---------------------------------------------- rerank, output ---
+        const SearchKArgs &ao = late_args();
         int nout = min(npool, k);
-        if (a.predict_only) {
+        if (ao.predict_only) {
             // no result rows in a predict-only pass
-        } else if (a.has_rr && npool > 0) {
+        } else if (ao.has_rr && npool > 0) {
             // exact f32 distances of the pool from the f32 rows
             for (int c0 = 0; c0 < npool; c0 += WAVE) {
                 if (c0 + lane < npool) lds.ids[lane] = (uint32_t)lds.pool[c0 + lane];
@@ -788,14 +860,14 @@ search_kernel(SearchKArgs a) {
                 // pieces pp, pp + 4, ... of its row, up to 8 at once, so that a
                 // pass waits for memory once (rows of up to 128 components)
                 const int pp = lane & 3;
-                const int n4 = (a.dim + 3) >> 2;
+                const int n4 = (ao.dim + 3) >> 2;
                 const float4 *qf4 = reinterpret_cast<const float4 *>(qrow);
                 for (int r0 = 0; r0 < u; r0 += 16) {
                     const int row = r0 + (lane >> 2);
                     const bool rv = row < u;
                     const uint32_t id = rv ? lds.ids[row] : 0u;
                     const float4 *xr4 =
-                        reinterpret_cast<const float4 *>(a.rr_base + (size_t)id * a.rr_pitch);
+                        reinterpret_cast<const float4 *>(ao.rr_base + (size_t)id * ao.rr_pitch);
                     float acc = 0.0f;
                     for (int j0 = 0; j0 < n4; j0 += 32) {
                         float4 xv[8], qv[8];
@@ -814,8 +886,8 @@ search_kernel(SearchKArgs a) {
 #pragma unroll
                             for (int e = 0; e < 4; e++) {
                                 // components past dim (a row's padding) count as zero
-                                const float xe = c + e < a.dim ? xs[e] : 0.0f;
-                                const float qe = c + e < a.dim ? qs[e] : 0.0f;
+                                const float xe = c + e < ao.dim ? xs[e] : 0.0f;
+                                const float qe = c + e < ao.dim ? qs[e] : 0.0f;
                                 if constexpr (MT == ONNG_L2SQ) {
                                     const float df = xe - qe;
                                     acc = fmaf(df, df, acc);
@@ -841,35 +913,35 @@ search_kernel(SearchKArgs a) {
                 merge_sorted(lds.S, 0, cur, key, u, k, lds.stage, NoSpill());
             }
             nout = min(npool, k);
-            for (int i = lane; i < a.k_stride; i += WAVE) {
+            for (int i = lane; i < ao.k_stride; i += WAVE) {
                 int32_t id = -1;
                 float d = F_INF;
                 if (i < nout) {
                     uint64_t key = lds.S[i];
                     id = (int32_t)(uint32_t)key;
                     d = unord_f32((uint32_t)(key >> 32));
-                    if (a.id_map) id = a.id_map[id];
+                    if (ao.id_map) id = ao.id_map[id];
                 }
-                a.out_ids[(size_t)qi * a.k_stride + i] = id;
-                reinterpret_cast<float *>(a.out_d)[(size_t)qi * a.k_stride + i] = d;
+                ao.out_ids[(size_t)qi * ao.k_stride + i] = id;
+                reinterpret_cast<float *>(ao.out_d)[(size_t)qi * ao.k_stride + i] = d;
             }
         } else {
-            for (int i = lane; i < a.k_stride; i += WAVE) {
+            for (int i = lane; i < ao.k_stride; i += WAVE) {
                 int32_t id = -1;
                 uint64_t key = i < nout ? lds.pool[i] : KEY_MAX;
                 if (i < nout) id = (int32_t)(uint32_t)key;
-                if (i < nout && a.id_map) id = a.id_map[id];
-                a.out_ids[(size_t)qi * a.k_stride + i] = id;
+                if (i < nout && ao.id_map) id = ao.id_map[id];
+                ao.out_ids[(size_t)qi * ao.k_stride + i] = id;
                 if constexpr (INT) {
-                    reinterpret_cast<int32_t *>(a.out_d)[(size_t)qi * a.k_stride + i] =
+                    reinterpret_cast<int32_t *>(ao.out_d)[(size_t)qi * ao.k_stride + i] =
                         i < nout ? (int32_t)(key >> 32) : INT32_MAX;
                 } else {
-                    reinterpret_cast<float *>(a.out_d)[(size_t)qi * a.k_stride + i] =
+                    reinterpret_cast<float *>(ao.out_d)[(size_t)qi * ao.k_stride + i] =
                         i < nout ? unord_f32((uint32_t)(key >> 32)) : F_INF;
                 }
             }
         }
-        if (nout < k && !a.predict_only) flags |= ONNG_QF_PADDED;
+        if (nout < k && !ao.predict_only) flags |= ONNG_QF_PADDED;
         if (lane == 0) {
             onng_query_stats st;
             st.dc = dc;
@@ -879,8 +951,8 @@ search_kernel(SearchKArgs a) {
             st.eps = eps;
             st.scanned = scanned;
             st.cost = cost;
-            st.us = (float)(wall_clock64() - t_start) * a.us_per_tick;
-            a.stats[qi] = st;
+            st.us = (float)(wall_clock64() - t_start) * ao.us_per_tick;
+            ao.stats[qi] = st;
         }
 
         // leave the global visited bitset clean for the next query
