@@ -70,7 +70,7 @@ struct Q<ONNG_U8, ONNG_L2SQ> {
     static constexpr bool INT = true;
     u32x4 q[PPL];
     uint32_t qq;
-    __device__ void load(const uint8_t *row, int p, int L, int n16) {
+    __device__ __forceinline__ void load(const uint8_t *row, int p, int L, int n16) {
         qq = 0;
 #pragma unroll
         for (int t = 0; t < PPL; t++) {
@@ -84,7 +84,7 @@ struct Q<ONNG_U8, ONNG_L2SQ> {
         }
     }
     // sum over this lane's pieces of (x - q)^2
-    __device__ uint32_t fold(const u32x4 *x, float) const {
+    __device__ __forceinline__ uint32_t fold(const u32x4 *x, float) const {
         uint32_t s = qq;
 #pragma unroll
         for (int t = 0; t < PPL; t++) s += u8_piece(x[t], q[t]);
@@ -101,7 +101,7 @@ struct Q {
     float q[PPL][N];
     // the query is always f32: its piece t of the stored layout covers
     // components [pc*N, pc*N + N)
-    __device__ void load_f32(const float *qrow, int dim, int p, int L, int n16) {
+    __device__ __forceinline__ void load_f32(const float *qrow, int dim, int p, int L, int n16) {
 #pragma unroll
         for (int t = 0; t < PPL; t++) {
             int pc = p + t * L;
@@ -113,7 +113,7 @@ struct Q {
         }
     }
     // this lane's part of sum (x - q)^2, or of <x, q> for cosine
-    __device__ float fold(const u32x4 *x, float sc) const {
+    __device__ __forceinline__ float fold(const u32x4 *x, float sc) const {
         // two accumulation chains (even / odd components) halve the
         // dependent-FMA latency
         float acc[2] = {0.0f, 0.0f};
@@ -217,6 +217,7 @@ search_kernel(SearchKArgs a0) {
     const int p = lane & (L - 1);
     const int grp = lane / L;
     const int rpp = WAVE / L;   // rows per pass
+    const uint32_t n_ids = (uint32_t)min(a.n_base, (int64_t)0xFFFFFFFF);
     // byte offsets of this lane's pieces of a row
     int piece[QT::PPL];
     bool has_piece[QT::PPL];
@@ -261,7 +262,7 @@ search_kernel(SearchKArgs a0) {
         int max_dc = as.max_dc_pq ? uni(as.max_dc_pq[qi]) : as.max_dc;
         if (max_dc <= 0) max_dc = INT32_MAX;
         // budget relative to the predicted cost of the chosen range
-        auto cost_budget = [&](float c) {
+        auto cost_budget = [&](float c) __attribute__((always_inline)) {
             const float factor = late_args().max_dc_factor;
             if (factor > 0.0f) {
                 float b = fminf(factor * c, 2.0e9f);
@@ -294,9 +295,9 @@ search_kernel(SearchKArgs a0) {
         int64_t spec_e0 = 0;
         int spec_deg = 0;
         uint32_t spec_nb = 0, spec_nb1 = 0;
-        bool spec_vis = false;
-        // offsets read ahead: lanes 0 and 1 those of next1, lanes 2 and 3 those
-        // of ofs_id (next2 of the latest expansion)
+        // offsets read ahead: lanes 0 and 1 those of the next pop, lanes 2 and 3
+        // those of ofs_id, which is likely to follow it (read with a vector load,
+        // which the LDS traffic of the merges does not wait for)
         int64_t ofs = 0;
         uint32_t ofs_id = NO_SPEC;
         // bitset words of the guessed ids, read ahead (first looked at by the
@@ -316,52 +317,48 @@ search_kernel(SearchKArgs a0) {
         wave_sync();
 
         // -------------------------------------------------- helpers ------
-        // Mark a batch of ids visited; returns whether this lane's id is new.
-        // known_ok: `known` is this id's bitset word, read after every earlier
-        // mark of the query; the mark then needs no reply, and *from_known tells
-        // the caller the answer came from that word (an id repeated in one
-        // list looks new in each copy: see dedupe_known).
-        auto visit = [&](bool valid, uint32_t id, bool known_ok = false, uint32_t known = 0u,
-                         bool *from_known = nullptr) -> bool {
+        // Mark a chunk of ids visited; returns whether this lane's id is new.
+        // `known` is the bitset word of an id outside the window, read after
+        // every earlier mark of the query, so that the mark needs no reply;
+        // *from_known tells that the answer came from that word (an id repeated
+        // in one list looks new in each copy: see dedupe_known).
+        auto visit = [&](bool valid, uint32_t id, uint32_t known, bool *from_known) __attribute__((always_inline)) -> bool {
             const uint32_t off = id - w0;   // wraps below the window
             const bool inw = valid && off < W;
             const bool outw = valid && !inw;
-            bool isnew = false, first = false;
+            bool isnew = false;
+            *from_known = false;
             if (inw) {
                 const uint32_t bit = 1u << (off & 31);
                 isnew = (atomicOr(&lds.vis[off >> 5], bit) & bit) == 0u;
             } else if (outw) {
                 const uint32_t bit = 1u << (id & 31);
-                if (known_ok) {
-                    isnew = (known & bit) == 0u;
-                    first = known == 0u;
-                    if (isnew)
-                        __hip_atomic_fetch_or(&gbits[id >> 5], bit, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT);
-                    if (from_known) *from_known = isnew;
-                } else {
-                    const uint32_t old = atomicOr(&gbits[id >> 5], bit);
-                    isnew = (old & bit) == 0u;
-                    first = old == 0u;
-                }
+                isnew = (known & bit) == 0u;
+                if (isnew)
+                    __hip_atomic_fetch_or(&gbits[id >> 5], bit, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+                *from_known = isnew;
             }
             // log each word when this query turns it non-zero
-            const bool logged = isnew && first;
+            const bool logged = *from_known && known == 0u;
             const uint64_t m = ballot(logged);
-            if (logged && log_n + mbcnt(m) < a.vlog_cap) vlog[log_n + mbcnt(m)] = (int32_t)(id >> 5);
-            log_n += __popcll(m);
+            if (m) {
+                if (logged && log_n + mbcnt(m) < a.vlog_cap)
+                    vlog[log_n + mbcnt(m)] = (int32_t)(id >> 5);
+                log_n += __popcll(m);
+            }
             return isnew;
         };
 
-        // Ids of chunk 0 and chunk 1 of a guessed expansion that were found new
-        // from words read before it (k0/k1 set) are new in every copy when the
+        // Ids of two chunks of a list that were found new
+        // from words read before them (k0/k1 set) are new in every copy when the
         // list repeats an id.  Keep the first copy in list order (chunk 0
         // before chunk 1, lower lane first), as Algorithm 1's visited set does:
         // a bitmap of 8192 id hashes in LDS finds the lanes whose hash was
         // already taken, and only for those the wave compares ids exactly.
         // The bitmap lives in the distance-key buffer, unused until the batch.
         auto dedupe_known = [&](uint32_t id0, bool &n0, bool k0, uint32_t id1, bool &n1,
-                                bool k1) {
+                                bool k1) __attribute__((always_inline)) {
             uint32_t *bm = reinterpret_cast<uint32_t *>(kbuf);   // 1 KiB
             reinterpret_cast<u32x4 *>(bm)[lane] = u32x4{0, 0, 0, 0};
             wave_sync();
@@ -453,14 +450,14 @@ search_kernel(SearchKArgs a0) {
         // spill a key that fell past the on-chip capacity of S; spilled keys
         // arrive in ascending order, so index 0 is the smallest of this merge
         uint64_t first_spilled = KEY_MAX;
-        auto spill_put = [&](int idx, uint64_t key) {
+        auto spill_put = [&](int idx, uint64_t key) __attribute__((always_inline)) {
             int pos = spill_n + idx;
             if (idx == 0) first_spilled = key;
             if (pos < a.spill_cap) spill0[(size_t)spill_sel * a.spill_cap + pos] = key;
         };
 
         // Merge sorted batch (lane j < nb holds j-th key) into S.
-        auto s_insert = [&](uint64_t key, int nb) {
+        auto s_insert = [&](uint64_t key, int nb) __attribute__((always_inline)) {
             if (nb == 0) return;
             if (size + nb > a.s_cap && head > 0) {
                 // compact the live part to the front
@@ -497,7 +494,7 @@ search_kernel(SearchKArgs a0) {
         };
 
         // Drop S entries beyond the range (a suffix of the sorted array).
-        auto s_prune = [&](float thr) {
+        auto s_prune = [&](float thr) __attribute__((always_inline)) {
             if (size == head || __builtin_isinf(thr)) return;
             if (key_dist<INT>(lds.S[size - 1]) <= thr) return;   // all within range
             // first index with d > thr: every stride-th entry first, then the
@@ -527,7 +524,7 @@ search_kernel(SearchKArgs a0) {
         };
 
         // Merge sorted keys into the pool (R and rerank candidates).
-        auto pool_insert = [&](uint64_t key, int nb) {
+        auto pool_insert = [&](uint64_t key, int nb) __attribute__((always_inline)) {
             // a full pool only takes keys below its last one (a sorted prefix)
             if (npool == pool_q) nb = __popcll(ballot(lane < nb && key < lds.pool[pool_q - 1]));
             if (nb == 0) return;
@@ -542,8 +539,8 @@ search_kernel(SearchKArgs a0) {
 
         // Process a sorted batch: R first (absorb_pool), then the range test
         // with the new r and the insertion into S (absorb_s).
-        auto absorb_pool = [&](uint64_t key, int u) { pool_insert(key, u); };
-        auto absorb_s = [&](uint64_t key, int u, bool to_s) {
+        auto absorb_pool = [&](uint64_t key, int u) __attribute__((always_inline)) { pool_insert(key, u); };
+        auto absorb_s = [&](uint64_t key, int u, bool to_s) __attribute__((always_inline)) {
             float thr = threshold(rfull, r, f);
             // the batch is sorted, so the keys within range are a prefix
             bool keep = lane < u && key_dist<INT>(key) <= thr;
@@ -553,14 +550,14 @@ search_kernel(SearchKArgs a0) {
             s_prune(thr);
             s_insert(ck, nk);
         };
-        auto absorb = [&](uint64_t key, int u, bool to_s) {
+        auto absorb = [&](uint64_t key, int u, bool to_s) __attribute__((always_inline)) {
             absorb_pool(key, u);
             absorb_s(key, u, to_s);
         };
 
         // Bring spilled keys back: merge every live spilled key into S, the
         // ones that do not fit go to the other spill buffer.
-        auto refill = [&]() {
+        auto refill = [&]() __attribute__((always_inline)) {
             __threadfence_block();   // spilled keys were stored by other lanes
             float thr = threshold(rfull, r, f);
             int n_old = spill_n;
@@ -592,7 +589,10 @@ search_kernel(SearchKArgs a0) {
                 valid = s >= 0 && (int64_t)s < a.n_base;
                 sid = valid ? (uint32_t)s : 0u;
             }
-            bool isnew = visit(valid, sid);
+            // nothing is marked yet: every word is known to be zero
+            bool from_known, no1 = false;
+            bool isnew = visit(valid, sid, 0u, &from_known);
+            dedupe_known(sid, isnew, from_known, 0u, no1, false);
             uint64_t m = ballot(isnew);
             int u = __popcll(m);
             if (isnew) lds.ids[mbcnt(m)] = sid;
@@ -609,41 +609,54 @@ search_kernel(SearchKArgs a0) {
         }
 
         // ------------------------------------------------- main loop -----
+        // One pass is up to two 64-edge chunks of the expanded node: their ids
+        // and visited marks, then one distance batch for the new nodes.  A
+        // longer list takes more passes (g0 is the pass's first edge).
+        int np = 0, g0 = 0;
+        int64_t e0 = 0;
         for (;;) {
-            if (head == size && spill_n == 0) break;                  // S empty
-            if (dc >= max_dc) {                                       // budget spent
-                flags |= ONNG_QF_BUDGET;
-                break;
-            }
-            if (spill_n > 0 && (head == size || uni64(lds.S[head]) > spill_min)) {
-                refill();
-                if (head == size) break;
+            const bool pop = g0 >= np;
+            if (pop) {
+                if (head == size && spill_n == 0) break;              // S empty
+                if (dc >= max_dc) {                                   // budget spent
+                    flags |= ONNG_QF_BUDGET;
+                    break;
+                }
+                if (spill_n > 0 && (head == size || uni64(lds.S[head]) > spill_min)) {
+                    refill();
+                    if (head == size) break;
+                }
             }
             // the pop and the two keys behind it in one read
-            const uint64_t front = lds.S[min(head + lane, size - 1)];
-            const uint64_t sk = readlane64(front, 0);
-            const uint32_t next1 = head + 1 < size ? (uint32_t)readlane64(front, 1) : NO_SPEC;
-            const uint32_t next2 = head + 2 < size ? (uint32_t)readlane64(front, 2) : NO_SPEC;
-            head++;
-            float thr = threshold(rfull, r, f);
-            if (key_dist<INT>(sk) > thr) break;                        // d(s,q) > r(1+eps)
-            hops++;
-            const uint32_t s = (uint32_t)sk;
-            // adjacency of s: read ahead when the previous expansion guessed
-            // this pop, else read now
-            const bool hit = s == spec_id;
-            spec_id = NO_SPEC;
-            int64_t e0;
-            int deg;
-            if (hit) {
-                e0 = spec_e0;
-                deg = spec_deg;
-            } else {
-                e0 = a.offsets[s];
-                deg = (int)(a.offsets[s + 1] - e0);
+            const uint64_t front = lds.S[max(min(head + lane, size - 1), 0)];
+            bool hit = false;
+            if (pop) {
+                const uint64_t sk = readlane64(front, 0);
+                head++;
+                if (key_dist<INT>(sk) > threshold(rfull, r, f)) break;   // d(s,q) > r(1+eps)
+                hops++;
+                const uint32_t s = (uint32_t)sk;
+                // adjacency of s: read ahead when the previous expansion
+                // guessed this pop, else read now
+                hit = s == spec_id;
+                int deg;
+                if (hit) {
+                    e0 = spec_e0;
+                    deg = spec_deg;
+                } else {
+                    e0 = a.offsets[s];
+                    deg = (int)(a.offsets[s + 1] - e0);
+                }
+                np = (int)min(ep, (uint32_t)deg);
+                g0 = 0;
+                scanned += np;
             }
-            const int np = (int)min(ep, (uint32_t)deg);
-            scanned += np;
+            spec_id = NO_SPEC;
+            const int left = np - g0;
+            const bool last = left <= 2 * WAVE;
+            const int at1 = pop ? 1 : 0;
+            const uint32_t next1 = head < size ? (uint32_t)readlane64(front, at1) : NO_SPEC;
+            const uint32_t next2 = head + 1 < size ? (uint32_t)readlane64(front, at1 + 1) : NO_SPEC;
             // The next pop is next1 unless this expansion finds a nearer node
             // (at the measured settings next1 it is in 62 to 94 % of the
             // expansions), so its reads start now: the offsets of next1 and of
@@ -651,164 +664,158 @@ search_kernel(SearchKArgs a0) {
             // expansion ago its offsets are known and the adjacency itself is
             // requested before this expansion's rows.
             const bool ahead = next1 != NO_SPEC && next1 == ofs_id;
-            int64_t n_e0 = 0;
-            int n_deg = 0;
-            if (ahead) {
-                n_e0 = readlane64(ofs, 2);
-                n_deg = (int)(readlane64(ofs, 3) - n_e0);
-            }
+            int64_t n_e0 = readlane64(ofs, 2);
+            int n_deg = (int)(readlane64(ofs, 3) - n_e0);
+            // What was read ahead has to be there from here on, a wrong guess
+            // too: else the compiler, which does not see that these loads are
+            // over, waits for all loads in flight where their registers are
+            // written next, in the middle of the expansion.
+            asm volatile("" ::"v"(spec_nb), "v"(spec_nb1), "v"(spec_wd), "v"(spec_wd1));
+            // The reads below are masked per lane and write their registers in
+            // place; lanes without a value keep an old one, which nothing looks
+            // at.  Under a branch of the whole wave (or with zeros for those
+            // lanes) the registers would be copied where the paths join, and a
+            // copy waits for the load.
+            int nl0 = 0, nl1 = 0;
+            auto read_adjacency = [&](bool go, int64_t first, int n) __attribute__((always_inline)) {
+                const int m0 = go ? min(n, WAVE) : 0;
+                const int m1 = go ? min(n - m0, WAVE) : 0;
+                if (lane < m0) spec_nb = (uint32_t)a.nbrs[first + lane];
+                if (lane < m1) spec_nb1 = (uint32_t)a.nbrs[first + WAVE + lane];
+                nl0 = go ? m0 : nl0;
+                nl1 = go ? m1 : nl1;
+            };
+            auto read_visited = [&](bool go) __attribute__((always_inline)) {
+                // every earlier mark is complete before the visited words are
+                // read (of ids outside the window: the others are on chip)
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                const bool c0 = (lane < (go ? nl0 : 0)) & (spec_nb < n_ids) & (spec_nb - w0 >= W);
+                const bool c1 = (lane < (go ? nl1 : 0)) & (spec_nb1 < n_ids) & (spec_nb1 - w0 >= W);
+                if (c0)
+                    spec_wd = __hip_atomic_load(&gbits[spec_nb >> 5], __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+                if (c1)
+                    spec_wd1 = __hip_atomic_load(&gbits[spec_nb1 >> 5], __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+            };
+            read_adjacency(!hit, e0 + g0, left);
+            read_visited(!hit);
             {
                 const uint32_t id = (lane & 2) ? next2 : next1;
                 ofs = a.offsets[(size_t)(id != NO_SPEC ? id : 0u) + (lane & 1)];
                 ofs_id = next2;
             }
-            // The edges in groups of up to two 64-edge chunks: ids and visited
-            // marks of the group, then one distance batch for its new nodes.
-            for (int g0 = 0;; g0 += 2 * WAVE) {
-                const bool last = g0 + 2 * WAVE >= np;
-                int u = 0;
-                const bool pre = hit && g0 == 0;
-                if (pre && spec_vis) {
-                    // both chunks read ahead, with their visited words
-                    const bool v0 = lane < np && (int64_t)spec_nb < a.n_base;
-                    const bool v1 = WAVE + lane < np && (int64_t)spec_nb1 < a.n_base;
-                    bool k0 = false, k1 = false;
-                    bool n0 = visit(v0, spec_nb, true, spec_wd, &k0);
-                    bool n1 = false;
-                    if (WAVE < np) n1 = visit(v1, spec_nb1, true, spec_wd1, &k1);
-                    if (ballot(k0 || k1)) dedupe_known(spec_nb, n0, k0, spec_nb1, n1, k1);
-                    uint64_t m = ballot(n0);
-                    if (n0) lds.ids[mbcnt(m)] = spec_nb;
-                    u = __popcll(m);
-                    m = ballot(n1);
-                    if (n1) lds.ids[u + mbcnt(m)] = spec_nb1;
-                    u += __popcll(m);
-                } else {
-#pragma unroll
-                    for (int cc = 0; cc < 2; cc++) {
-                        const int c0 = g0 + cc * WAVE;
-                        if (c0 >= np) break;
-                        const int j = c0 + lane;
-                        uint32_t id;
-                        if (pre) id = j < np ? (cc == 0 ? spec_nb : spec_nb1) : 0u;
-                        else id = j < np ? (uint32_t)a.nbrs[e0 + j] : 0u;
-                        bool valid = j < np && (int64_t)id < a.n_base;
-                        bool isnew = visit(valid, id);
-                        uint64_t m = ballot(isnew);
-                        if (isnew) lds.ids[u + mbcnt(m)] = id;
-                        u += __popcll(m);
-                    }
-                }
-                if (u == 0 && !last) continue;
-                // the guess's reads: 0 nothing usable, 1 offsets requested,
-                // 2 adjacency requested, 3 visited words requested
-                int stage = 0;
-                int nl0 = 0, nl1 = 0;
-                auto read_adjacency = [&](int64_t g_e0, int g_deg) {
-                    spec_e0 = g_e0;
-                    spec_deg = g_deg;
-                    nl0 = min(spec_deg, WAVE);
-                    nl1 = min(spec_deg - nl0, WAVE);
-                    spec_nb = lane < nl0 ? (uint32_t)a.nbrs[spec_e0 + lane] : 0u;
-                    spec_nb1 = lane < nl1 ? (uint32_t)a.nbrs[spec_e0 + WAVE + lane] : 0u;
-                    stage = 2;
-                };
-                auto read_visited = [&]() {
-                    // the marks of this expansion are complete before the
-                    // visited words of the guess are read (those outside the
-                    // window: the others are on chip)
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                    spec_wd = 0u;
-                    spec_wd1 = 0u;
-                    if (lane < nl0 && (int64_t)spec_nb < a.n_base && spec_nb - w0 >= W)
-                        spec_wd = __hip_atomic_load(&gbits[spec_nb >> 5], __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                    if (lane < nl1 && (int64_t)spec_nb1 < a.n_base && spec_nb1 - w0 >= W)
-                        spec_wd1 = __hip_atomic_load(&gbits[spec_nb1 >> 5], __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-                    stage = 3;
-                };
-                if (last && ahead) read_adjacency(n_e0, n_deg);
-                uint64_t k0 = KEY_MAX, k1 = KEY_MAX;
-                int nk = 0;
-                if (u > 0) {
-                    wave_sync();
-                    batch_keys(u);
-                    dc += u;
-                    k0 = lane < u ? kbuf[lane] : KEY_MAX;
-                    k1 = lane + WAVE < u ? kbuf[lane + WAVE] : KEY_MAX;
-                    wave_sync();
-                }
-                if (stage == 2) read_visited();
-                // Keys that can neither enter S (beyond the current range,
-                // which only shrinks) nor the pool (beyond its last key when
-                // full) are dropped before sorting.
-                if (u > 0) {
-                    const float thr0 = threshold(rfull, r, f);
-                    const uint64_t plast = npool == pool_q ? lds.pool[pool_q - 1] : KEY_MAX;
-                    bool keep0 = lane < u && (key_dist<INT>(k0) <= thr0 || k0 < plast);
-                    bool keep1 = lane + WAVE < u && (key_dist<INT>(k1) <= thr0 || k1 < plast);
-                    uint64_t m0 = ballot(keep0), m1 = ballot(keep1);
-                    const int n0 = __popcll(m0);
-                    nk = n0 + __popcll(m1);
-                    if (nk < u && nk > 0) {
-                        if (keep0) kbuf[mbcnt(m0)] = k0;
-                        if (keep1) kbuf[n0 + mbcnt(m1)] = k1;
-                        wave_sync();
-                        k0 = lane < nk ? kbuf[lane] : KEY_MAX;
-                        k1 = lane + WAVE < nk ? kbuf[lane + WAVE] : KEY_MAX;
-                        wave_sync();
-                    }
-                }
-                const int na = min(nk, WAVE), nb2 = nk - na;
-                if (na > 0) k0 = wave_sort(k0, pow2_at_least(na));
-                if (nb2 > 0) k1 = wave_sort(k1, pow2_at_least(nb2));
-                // Guess the next pop (the smaller of S's head and this group's
-                // minimum, when within range and no spilled key is smaller).
-                // Where it is next1 its reads are under way; else they start
-                // here, a dependent chain (offsets, adjacency, visited words)
-                // of which each step is issued one merge after the previous
-                // one, so that its latency overlaps the merge.  A wrong guess
-                // only wastes the reads.
-                int64_t spec_ofs = 0;
-                if (last) {
-                    uint64_t cand = head < size ? uni64(lds.S[head]) : KEY_MAX;
-                    if (na > 0) {
-                        const uint64_t b0 = readlane64(k0, 0);
-                        cand = b0 < cand ? b0 : cand;
-                    }
-                    if (nb2 > 0) {
-                        const uint64_t b1 = readlane64(k1, 0);
-                        cand = b1 < cand ? b1 : cand;
-                    }
-                    if (cand != KEY_MAX && !(spill_n > 0 && spill_min < cand) &&
-                        key_dist<INT>(cand) <= threshold(rfull, r, f)) {
-                        spec_id = (uint32_t)cand;
-                        if (spec_id != next1) {
-                            // lanes 0 and 1 read the two offsets with a vector load,
-                            // which the merges' LDS traffic does not wait for
-                            spec_ofs = a.offsets[spec_id + (lane & 1)];
-                            stage = 1;
-                        } else if (stage == 0) {
-                            const int64_t o = readlane64(ofs, 0);
-                            read_adjacency(o, (int)(readlane64(ofs, 1) - o));
-                        }
-                    } else {
-                        stage = 0;
-                    }
-                }
-                if (na > 0) absorb_pool(k0, na);
-                if (stage == 2) read_visited();
-                if (stage == 1) {
-                    const int64_t o = readlane64(spec_ofs, 0);
-                    read_adjacency(o, (int)(readlane64(spec_ofs, 1) - o));
-                }
-                if (na > 0) absorb_s(k0, na, true);
-                if (stage == 2) read_visited();
-                spec_vis = stage == 3;
-                if (nb2 > 0) absorb(k1, nb2, true);
-                if (last) break;
+            int u;
+            {
+                const bool v0 = lane < left && spec_nb < n_ids;
+                const bool v1 = WAVE + lane < left && spec_nb1 < n_ids;
+                bool k0, k1 = false;
+                bool n0 = visit(v0, spec_nb, spec_wd, &k0);
+                bool n1 = false;
+                if (WAVE < left) n1 = visit(v1, spec_nb1, spec_wd1, &k1);
+                if (ballot(k0 || k1)) dedupe_known(spec_nb, n0, k0, spec_nb1, n1, k1);
+                uint64_t m = ballot(n0);
+                if (n0) lds.ids[mbcnt(m)] = spec_nb;
+                u = __popcll(m);
+                m = ballot(n1);
+                if (n1) lds.ids[u + mbcnt(m)] = spec_nb1;
+                u += __popcll(m);
             }
+            // the guess's reads: 0 nothing usable, 1 offsets requested,
+            // 2 adjacency requested, 3 visited words requested
+            int stage = 0;
+            auto guess_adjacency = [&](bool go, int64_t first, int n) __attribute__((always_inline)) {
+                read_adjacency(go, first, n);
+                spec_e0 = go ? first : spec_e0;
+                spec_deg = go ? n : spec_deg;
+                stage = go ? 2 : stage;
+            };
+            auto guess_visited = [&]() __attribute__((always_inline)) {
+                read_visited(stage == 2);
+                stage = stage == 2 ? 3 : stage;
+            };
+            guess_adjacency(last && ahead, n_e0, n_deg);
+            uint64_t k0 = KEY_MAX, k1 = KEY_MAX;
+            int nk = 0;
+            if (u > 0) {
+                wave_sync();
+                batch_keys(u);
+                dc += u;
+                k0 = lane < u ? kbuf[lane] : KEY_MAX;
+                k1 = lane + WAVE < u ? kbuf[lane + WAVE] : KEY_MAX;
+                wave_sync();
+            }
+            guess_visited();
+            // Keys that can neither enter S (beyond the current range,
+            // which only shrinks) nor the pool (beyond its last key when
+            // full) are dropped before sorting.
+            if (u > 0) {
+                const float thr0 = threshold(rfull, r, f);
+                const uint64_t plast = npool == pool_q ? lds.pool[pool_q - 1] : KEY_MAX;
+                bool keep0 = lane < u && (key_dist<INT>(k0) <= thr0 || k0 < plast);
+                bool keep1 = lane + WAVE < u && (key_dist<INT>(k1) <= thr0 || k1 < plast);
+                uint64_t m0 = ballot(keep0), m1 = ballot(keep1);
+                const int n0 = __popcll(m0);
+                nk = n0 + __popcll(m1);
+                if (nk < u && nk > 0) {
+                    if (keep0) kbuf[mbcnt(m0)] = k0;
+                    if (keep1) kbuf[n0 + mbcnt(m1)] = k1;
+                    wave_sync();
+                    k0 = lane < nk ? kbuf[lane] : KEY_MAX;
+                    k1 = lane + WAVE < nk ? kbuf[lane + WAVE] : KEY_MAX;
+                    wave_sync();
+                }
+            }
+            const int na = min(nk, WAVE), nb2 = nk - na;
+            if (na > 0) k0 = wave_sort(k0, pow2_at_least(na));
+            if (nb2 > 0) k1 = wave_sort(k1, pow2_at_least(nb2));
+            // Guess the next pop (the smaller of S's head and this group's
+            // minimum, when within range and no spilled key is smaller).
+            // Where it is next1 its reads are under way; else they start
+            // here, a dependent chain (offsets, adjacency, visited words)
+            // of which each step is issued one merge after the previous
+            // one, so that its latency overlaps the merge.  A wrong guess
+            // only wastes the reads.
+            bool have_ofs = false;
+            if (last) {
+                uint64_t cand = head < size ? uni64(lds.S[head]) : KEY_MAX;
+                if (na > 0) {
+                    const uint64_t b0 = readlane64(k0, 0);
+                    cand = b0 < cand ? b0 : cand;
+                }
+                if (nb2 > 0) {
+                    const uint64_t b1 = readlane64(k1, 0);
+                    cand = b1 < cand ? b1 : cand;
+                }
+                if (cand != KEY_MAX && !(spill_n > 0 && spill_min < cand) &&
+                    key_dist<INT>(cand) <= threshold(rfull, r, f)) {
+                    spec_id = (uint32_t)cand;
+                    if (spec_id != next1) {
+                        stage = 1;
+                        ofs_id = next1;   // what then follows it
+                    } else if (stage == 0) {
+                        stage = 1;        // requested at the pop
+                        have_ofs = true;
+                    }
+                } else {
+                    stage = 0;
+                }
+            }
+            {
+                const uint32_t id = (lane & 2) && next1 != NO_SPEC ? next1 : spec_id;
+                if (lane < (stage == 1 && !have_ofs ? WAVE : 0)) ofs = a.offsets[(size_t)id + (lane & 1)];
+            }
+            if (na > 0) absorb_pool(k0, na);
+            if (stage == 1) {
+                n_e0 = readlane64(ofs, 0);
+                n_deg = (int)(readlane64(ofs, 1) - n_e0);
+            }
+            guess_adjacency(stage == 1, n_e0, n_deg);
+            if (na > 0) absorb_s(k0, na, true);
+            guess_visited();
+            if (nb2 > 0) absorb(k1, nb2, true);
+            g0 += 2 * WAVE;
+            if (!last) continue;
 
             if (probe_end > 0 && hops == probe_end) {
                 const SearchKArgs &ap = late_args();

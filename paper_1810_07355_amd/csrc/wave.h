@@ -138,15 +138,24 @@ __device__ __forceinline__ uint64_t wave_min64(uint64_t v) {
     return v;
 }
 
-// One compare-exchange step of the bitonic network: block size K, distance J.
+// Lanes that keep the smaller key in the step of block size K, distance J.
 template <int K, int J>
-__device__ __forceinline__ uint64_t bitonic_step(uint64_t key, int lane) {
-    uint64_t other = xor_lane64<J>(key);
-    bool up = (lane & K) == 0;
-    bool lower = (lane & J) == 0;
-    uint64_t mn = key < other ? key : other;
-    uint64_t mx = key < other ? other : key;
-    return (lower == up) ? mn : mx;
+constexpr uint64_t bitonic_lower_lanes() {
+    uint64_t m = 0;
+    for (int l = 0; l < WAVE; l++)
+        if (((l & K) == 0) == ((l & J) == 0)) m |= 1ull << l;
+    return m;
+}
+
+// One compare-exchange step of the bitonic network: block size K, distance J.
+// The lane pattern is a literal combined with the comparison in the scalar
+// unit: as a predicate per lane each of the 21 patterns was kept in a scalar
+// register pair across the caller's loops.
+template <int K, int J>
+__device__ __forceinline__ uint64_t bitonic_step(uint64_t key, int) {
+    const uint64_t other = xor_lane64<J>(key);
+    const uint64_t keep = ~(ballot(key < other) ^ bitonic_lower_lanes<K, J>());
+    return __builtin_amdgcn_inverse_ballot_w64(keep) ? key : other;
 }
 
 template <int K, int J>
@@ -176,16 +185,18 @@ __device__ __forceinline__ int pow2_at_least(int x) {
     return w;
 }
 
-// First index i in [0, n) with a[i] >= key (n if none).
+// First index i in [0, n) with a[i] >= key (n if none); n is wave-uniform, so
+// that the lanes take the same number of steps.
 template <typename P>
 __device__ __forceinline__ int lower_bound_u64(P a, int n, uint64_t key) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (a[mid] < key) lo = mid + 1;
-        else hi = mid;
+    int at = 0;
+    while (n > 1) {
+        const int half = n >> 1;
+        at += a[at + half - 1] < key ? half : 0;
+        n -= half;
     }
-    return lo;
+    if (n == 1) at += a[at] < key ? 1 : 0;
+    return at;
 }
 
 // Merge a batch into a sorted array, in place.
@@ -197,9 +208,62 @@ __device__ __forceinline__ int lower_bound_u64(P a, int n, uint64_t key) {
 // A's elements move to higher indices only, so they are moved top chunk
 // first, each chunk read completely before it is written; batch keys are
 // written last.
+// A batch of at most 4 keys (what an expansion of a search mostly adds) is
+// ranked by comparing A's chunks with the keys in scalar registers: the binary
+// searches of the general path are chains of 6 to 8 dependent LDS reads.
+template <typename PA, typename Spill>
+__device__ __forceinline__ int merge_few(PA A, int base, int na, uint64_t bkey, int nb, int cap,
+                                         Spill spill) {
+    const int lane = lane_id();
+    uint64_t k[4];
+    int rank[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        k[j] = j < nb ? (uint64_t)readlane64((int64_t)bkey, j) : ~0ull;
+        rank[j] = 0;
+    }
+    for (int c0 = ((na - 1) >> 6) << 6; c0 >= 0; c0 -= WAVE) {
+        const int i = c0 + lane;
+        const uint64_t a = A[base + min(i, na - 1)];
+        const int n = min(WAVE, na - c0);
+        int above = 0;   // batch keys below this element
+        uint64_t any = 0;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const bool gt = (i < na) & (a > k[j]);
+            const uint64_t m = ballot(gt);
+            above += gt;
+            rank[j] += n - (int)__popcll(m);
+            if (j == 0) any = m;
+        }
+        if (any == 0) {   // this chunk stays in place, and so do all below it
+#pragma unroll
+            for (int j = 0; j < 4; j++) rank[j] += c0;
+            break;
+        }
+        wave_sync();
+        if (above > 0) {
+            if (i + above < cap) A[base + i + above] = a;
+            else spill(i + above - cap, a);
+        }
+        wave_sync();
+    }
+    int pos = rank[0];
+#pragma unroll
+    for (int j = 1; j < 4; j++) pos = lane == j ? rank[j] : pos;
+    pos += lane;
+    if (lane < nb) {
+        if (pos < cap) A[base + pos] = bkey;
+        else spill(pos - cap, bkey);
+    }
+    wave_sync();
+    return na + nb;
+}
+
 template <typename PA, typename PS, typename Spill>
 __device__ __forceinline__ int merge_sorted(PA A, int base, int na, uint64_t bkey, int nb,
                                             int cap, PS stage, Spill spill) {
+    if (nb <= 4) return merge_few(A, base, na, bkey, nb, cap, spill);
     const int lane = lane_id();
     stage[lane] = bkey;
     wave_sync();
