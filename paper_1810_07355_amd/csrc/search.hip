@@ -438,9 +438,11 @@ search_kernel(SearchKArgs a0) {
             }
         };
         auto batch_keys = [&](int u) __attribute__((always_inline)) {
-            for (int r0 = 0; r0 < u; r0 += 4 * rpp) {
+            constexpr int MAXP = DT == ONNG_F32 ? 8 : 4;
+            for (int r0 = 0; r0 < u; r0 += MAXP * rpp) {
                 const int left = u - r0;
-                if (left > 2 * rpp) row_passes(std::integral_constant<int, 4>(), r0, u);
+                if (MAXP > 4 && left > 4 * rpp) row_passes(std::integral_constant<int, MAXP>(), r0, u);
+                else if (left > 2 * rpp) row_passes(std::integral_constant<int, 4>(), r0, u);
                 else if (left > rpp) row_passes(std::integral_constant<int, 2>(), r0, u);
                 else row_passes(std::integral_constant<int, 1>(), r0, u);
             }
