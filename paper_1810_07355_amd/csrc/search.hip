@@ -287,8 +287,17 @@ search_kernel(SearchKArgs a0) {
         const int probe_end = as.two_phase ? (int)as.probe_hops : 0;
         int scanned = 0;   // adjacency entries read (sum of min(deg, e_p) over expansions)
         int flags = 0;
-        bool rfull = false;
+        // search range: f * the k-th distance, infinite until k are known
+        float thr = F_INF;
         float r = F_INF;
+        bool rfull = false;
+        float pruned = __builtin_nanf("");   // range that S was last cut to
+        uint64_t plast = KEY_MAX;            // last key of a full pool
+        // the first keys of S, one a lane from index front_at on; read again
+        // after S has changed
+        uint64_t front = KEY_MAX;
+        int front_at = 0;
+        bool front_ok = false;
         // guessed next expansion (see the expansion loop)
         constexpr uint32_t NO_SPEC = 0xFFFFFFFFu;
         uint32_t spec_id = NO_SPEC;
@@ -317,39 +326,6 @@ search_kernel(SearchKArgs a0) {
         wave_sync();
 
         // -------------------------------------------------- helpers ------
-        // Mark a chunk of ids visited; returns whether this lane's id is new.
-        // `known` is the bitset word of an id outside the window, read after
-        // every earlier mark of the query, so that the mark needs no reply;
-        // *from_known tells that the answer came from that word (an id repeated
-        // in one list looks new in each copy: see dedupe_known).
-        auto visit = [&](bool valid, uint32_t id, uint32_t known, bool *from_known) __attribute__((always_inline)) -> bool {
-            const uint32_t off = id - w0;   // wraps below the window
-            const bool inw = valid && off < W;
-            const bool outw = valid && !inw;
-            bool isnew = false;
-            *from_known = false;
-            if (inw) {
-                const uint32_t bit = 1u << (off & 31);
-                isnew = (atomicOr(&lds.vis[off >> 5], bit) & bit) == 0u;
-            } else if (outw) {
-                const uint32_t bit = 1u << (id & 31);
-                isnew = (known & bit) == 0u;
-                if (isnew)
-                    __hip_atomic_fetch_or(&gbits[id >> 5], bit, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-                *from_known = isnew;
-            }
-            // log each word when this query turns it non-zero
-            const bool logged = *from_known && known == 0u;
-            const uint64_t m = ballot(logged);
-            if (m) {
-                if (logged && log_n + mbcnt(m) < a.vlog_cap)
-                    vlog[log_n + mbcnt(m)] = (int32_t)(id >> 5);
-                log_n += __popcll(m);
-            }
-            return isnew;
-        };
-
         // Ids of two chunks of a list that were found new
         // from words read before them (k0/k1 set) are new in every copy when the
         // list repeats an id.  Keep the first copy in list order (chunk 0
@@ -393,6 +369,51 @@ search_kernel(SearchKArgs a0) {
             n0 = n0 && !((drop0 >> lane) & 1u);
             n1 = n1 && !((drop1 >> lane) & 1u);
             wave_sync();
+        };
+
+        // Mark up to two chunks of ids visited (id1 where two) and list the new
+        // ones in lds.ids; returns their number.  `wd` is the bitset word of an
+        // id outside the window, read after every earlier mark of the query, so
+        // that the mark needs no reply.  Both chunks' marks are under way before
+        // either is looked at.
+        auto mark = [&](bool v0, uint32_t id0, uint32_t wd0, bool two, bool v1, uint32_t id1,
+                        uint32_t wd1) __attribute__((always_inline)) -> int {
+            const uint32_t off0 = id0 - w0, off1 = id1 - w0;   // wrap below the window
+            const bool in0 = v0 && off0 < W, in1 = v1 && off1 < W;
+            uint32_t old0 = 0u, old1 = 0u;
+            if (in0) old0 = atomicOr(&lds.vis[off0 >> 5], 1u << (off0 & 31));
+            if (in1) old1 = atomicOr(&lds.vis[off1 >> 5], 1u << (off1 & 31));
+            // out of the window: the answer came from the word (an id repeated
+            // in the list looks new in each copy: see dedupe_known)
+            const bool k0 = v0 && !in0 && !(wd0 >> (id0 & 31) & 1u);
+            const bool k1 = v1 && !in1 && !(wd1 >> (id1 & 31) & 1u);
+            bool n0 = k0 || (in0 && !(old0 >> (off0 & 31) & 1u));
+            bool n1 = k1 || (in1 && !(old1 >> (off1 & 31) & 1u));
+            if (ballot(k0 || k1)) {
+                // set the bits, and log each word that this query turns non-zero
+                if (k0)
+                    __hip_atomic_fetch_or(&gbits[id0 >> 5], 1u << (id0 & 31), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+                if (k1)
+                    __hip_atomic_fetch_or(&gbits[id1 >> 5], 1u << (id1 & 31), __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT);
+                const bool g0 = k0 && wd0 == 0u, g1 = k1 && wd1 == 0u;
+                const uint64_t m0 = ballot(g0), m1 = ballot(g1);
+                const int at1 = log_n + __popcll(m0);
+                if (g0 && log_n + mbcnt(m0) < a.vlog_cap) vlog[log_n + mbcnt(m0)] = (int32_t)(id0 >> 5);
+                if (g1 && at1 + mbcnt(m1) < a.vlog_cap) vlog[at1 + mbcnt(m1)] = (int32_t)(id1 >> 5);
+                log_n = at1 + __popcll(m1);
+                dedupe_known(id0, n0, k0, id1, n1, k1);
+            }
+            uint64_t m = ballot(n0);
+            if (n0) lds.ids[mbcnt(m)] = id0;
+            int u = __popcll(m);
+            if (two) {
+                m = ballot(n1);
+                if (n1) lds.ids[u + mbcnt(m)] = id1;
+                u += __popcll(m);
+            }
+            return u;
         };
 
         // Distances of rows lds.ids[0..u) -> kbuf[i] as keys (u <= 128).  A lane
@@ -461,6 +482,7 @@ search_kernel(SearchKArgs a0) {
         // Merge sorted batch (lane j < nb holds j-th key) into S.
         auto s_insert = [&](uint64_t key, int nb) __attribute__((always_inline)) {
             if (nb == 0) return;
+            front_ok = false;
             if (size + nb > a.s_cap && head > 0) {
                 // compact the live part to the front
                 int live = size - head;
@@ -496,8 +518,9 @@ search_kernel(SearchKArgs a0) {
         };
 
         // Drop S entries beyond the range (a suffix of the sorted array).
-        auto s_prune = [&](float thr) __attribute__((always_inline)) {
-            if (size == head || __builtin_isinf(thr)) return;
+        auto s_prune = [&]() __attribute__((always_inline)) {
+            if (thr == pruned || size == head || __builtin_isinf(thr)) return;
+            pruned = thr;
             if (key_dist<INT>(lds.S[size - 1]) <= thr) return;   // all within range
             // first index with d > thr: every stride-th entry first, then the
             // entries between the last sample within range and the next one
@@ -528,28 +551,30 @@ search_kernel(SearchKArgs a0) {
         // Merge sorted keys into the pool (R and rerank candidates).
         auto pool_insert = [&](uint64_t key, int nb) __attribute__((always_inline)) {
             // a full pool only takes keys below its last one (a sorted prefix)
-            if (npool == pool_q) nb = __popcll(ballot(lane < nb && key < lds.pool[pool_q - 1]));
+            nb = __popcll(ballot(lane < nb && key < plast));
             if (nb == 0) return;
             int total = merge_sorted(lds.pool, 0, npool, key, nb, pool_q, lds.stage, NoSpill());
             npool = min(total, pool_q);
+            const uint64_t pk = lds.pool[k - 1], pl = lds.pool[pool_q - 1];
             if (npool >= k) {
                 rfull = true;
-                r = key_dist<INT>(lds.pool[k - 1]);
-                r = unif(r);
+                r = unif(key_dist<INT>(pk));
+                thr = unif(threshold(true, r, f));
             }
+            if (npool == pool_q) plast = uni64(pl);
         };
 
         // Process a sorted batch: R first (absorb_pool), then the range test
         // with the new r and the insertion into S (absorb_s).
         auto absorb_pool = [&](uint64_t key, int u) __attribute__((always_inline)) { pool_insert(key, u); };
         auto absorb_s = [&](uint64_t key, int u, bool to_s) __attribute__((always_inline)) {
-            float thr = threshold(rfull, r, f);
             // the batch is sorted, so the keys within range are a prefix
             bool keep = lane < u && key_dist<INT>(key) <= thr;
             if (!to_s) keep = lane < u;
             const int nk = __popcll(ballot(keep));
             const uint64_t ck = lane < nk ? key : KEY_MAX;
-            s_prune(thr);
+            s_prune();
+            if (!to_s) pruned = __builtin_nanf("");   // taken without the range test
             s_insert(ck, nk);
         };
         auto absorb = [&](uint64_t key, int u, bool to_s) __attribute__((always_inline)) {
@@ -561,7 +586,7 @@ search_kernel(SearchKArgs a0) {
         // ones that do not fit go to the other spill buffer.
         auto refill = [&]() __attribute__((always_inline)) {
             __threadfence_block();   // spilled keys were stored by other lanes
-            float thr = threshold(rfull, r, f);
+            front_ok = false;
             int n_old = spill_n;
             int sel_old = spill_sel;
             spill_sel ^= 1;
@@ -577,7 +602,7 @@ search_kernel(SearchKArgs a0) {
                 int nb = __popcll(m);
                 if (nb == 0) continue;
                 v = wave_sort(v, WAVE);
-                s_prune(thr);
+                s_prune();
                 s_insert(v, nb);
             }
         };
@@ -592,12 +617,7 @@ search_kernel(SearchKArgs a0) {
                 sid = valid ? (uint32_t)s : 0u;
             }
             // nothing is marked yet: every word is known to be zero
-            bool from_known, no1 = false;
-            bool isnew = visit(valid, sid, 0u, &from_known);
-            dedupe_known(sid, isnew, from_known, 0u, no1, false);
-            uint64_t m = ballot(isnew);
-            int u = __popcll(m);
-            if (isnew) lds.ids[mbcnt(m)] = sid;
+            const int u = mark(valid, sid, 0u, false, false, 0u, 0u);
             wave_sync();
             batch_keys(u);
             dc += u;
@@ -629,13 +649,17 @@ search_kernel(SearchKArgs a0) {
                     if (head == size) break;
                 }
             }
-            // the pop and the two keys behind it in one read
-            const uint64_t front = lds.S[max(min(head + lane, size - 1), 0)];
+            // the pop and the two keys behind it
+            if (!front_ok || head - front_at > WAVE - 4) {
+                front = lds.S[max(min(head + lane, size - 1), 0)];
+                front_at = head;
+                front_ok = true;
+            }
             bool hit = false;
             if (pop) {
-                const uint64_t sk = readlane64(front, 0);
+                const uint64_t sk = readlane64(front, head - front_at);
                 head++;
-                if (key_dist<INT>(sk) > threshold(rfull, r, f)) break;   // d(s,q) > r(1+eps)
+                if (key_dist<INT>(sk) > thr) break;                   // d(s,q) > r(1+eps)
                 hops++;
                 const uint32_t s = (uint32_t)sk;
                 // adjacency of s: read ahead when the previous expansion
@@ -656,9 +680,10 @@ search_kernel(SearchKArgs a0) {
             spec_id = NO_SPEC;
             const int left = np - g0;
             const bool last = left <= 2 * WAVE;
-            const int at1 = pop ? 1 : 0;
-            const uint32_t next1 = head < size ? (uint32_t)readlane64(front, at1) : NO_SPEC;
-            const uint32_t next2 = head + 1 < size ? (uint32_t)readlane64(front, at1 + 1) : NO_SPEC;
+            const uint64_t head_key = head < size ? readlane64(front, head - front_at) : KEY_MAX;
+            const uint32_t next1 = (uint32_t)head_key;   // NO_SPEC where S is empty
+            const uint32_t next2 = head + 1 < size ? (uint32_t)readlane64(front, head + 1 - front_at)
+                                                   : NO_SPEC;
             // The next pop is next1 unless this expansion finds a nearer node
             // (at the measured settings next1 it is in 62 to 94 % of the
             // expansions), so its reads start now: the offsets of next1 and of
@@ -707,22 +732,8 @@ search_kernel(SearchKArgs a0) {
                 ofs = a.offsets[(size_t)(id != NO_SPEC ? id : 0u) + (lane & 1)];
                 ofs_id = next2;
             }
-            int u;
-            {
-                const bool v0 = lane < left && spec_nb < n_ids;
-                const bool v1 = WAVE + lane < left && spec_nb1 < n_ids;
-                bool k0, k1 = false;
-                bool n0 = visit(v0, spec_nb, spec_wd, &k0);
-                bool n1 = false;
-                if (WAVE < left) n1 = visit(v1, spec_nb1, spec_wd1, &k1);
-                if (ballot(k0 || k1)) dedupe_known(spec_nb, n0, k0, spec_nb1, n1, k1);
-                uint64_t m = ballot(n0);
-                if (n0) lds.ids[mbcnt(m)] = spec_nb;
-                u = __popcll(m);
-                m = ballot(n1);
-                if (n1) lds.ids[u + mbcnt(m)] = spec_nb1;
-                u += __popcll(m);
-            }
+            const int u = mark(lane < left && spec_nb < n_ids, spec_nb, spec_wd, WAVE < left,
+                               WAVE + lane < left && spec_nb1 < n_ids, spec_nb1, spec_wd1);
             // the guess's reads: 0 nothing usable, 1 offsets requested,
             // 2 adjacency requested, 3 visited words requested
             int stage = 0;
@@ -752,10 +763,8 @@ search_kernel(SearchKArgs a0) {
             // which only shrinks) nor the pool (beyond its last key when
             // full) are dropped before sorting.
             if (u > 0) {
-                const float thr0 = threshold(rfull, r, f);
-                const uint64_t plast = npool == pool_q ? lds.pool[pool_q - 1] : KEY_MAX;
-                bool keep0 = lane < u && (key_dist<INT>(k0) <= thr0 || k0 < plast);
-                bool keep1 = lane + WAVE < u && (key_dist<INT>(k1) <= thr0 || k1 < plast);
+                bool keep0 = lane < u && (key_dist<INT>(k0) <= thr || k0 < plast);
+                bool keep1 = lane + WAVE < u && (key_dist<INT>(k1) <= thr || k1 < plast);
                 uint64_t m0 = ballot(keep0), m1 = ballot(keep1);
                 const int n0 = __popcll(m0);
                 nk = n0 + __popcll(m1);
@@ -780,7 +789,7 @@ search_kernel(SearchKArgs a0) {
             // only wastes the reads.
             bool have_ofs = false;
             if (last) {
-                uint64_t cand = head < size ? uni64(lds.S[head]) : KEY_MAX;
+                uint64_t cand = head_key;
                 if (na > 0) {
                     const uint64_t b0 = readlane64(k0, 0);
                     cand = b0 < cand ? b0 : cand;
@@ -790,7 +799,7 @@ search_kernel(SearchKArgs a0) {
                     cand = b1 < cand ? b1 : cand;
                 }
                 if (cand != KEY_MAX && !(spill_n > 0 && spill_min < cand) &&
-                    key_dist<INT>(cand) <= threshold(rfull, r, f)) {
+                    key_dist<INT>(cand) <= thr) {
                     spec_id = (uint32_t)cand;
                     if (spec_id != next1) {
                         stage = 1;
@@ -849,7 +858,8 @@ search_kernel(SearchKArgs a0) {
                     ep = ap.ep_pq ? uniu(ap.ep_pq[qi]) : ap.ep;
                 }
                 f = range_factor(eps, MT);
-                s_prune(threshold(rfull, r, f));
+                thr = unif(threshold(rfull, r, f));
+                s_prune();
                 if (ap.predict_only) break;   // the range is all this pass reports
             }
         }
