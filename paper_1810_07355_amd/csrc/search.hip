@@ -697,7 +697,7 @@ search_kernel(SearchKArgs a0) {
             // too: else the compiler, which does not see that these loads are
             // over, waits for all loads in flight where their registers are
             // written next, in the middle of the expansion.
-            asm volatile("" ::"v"(spec_nb), "v"(spec_nb1), "v"(spec_wd), "v"(spec_wd1));
+            asm volatile("" : "+v"(spec_nb), "+v"(spec_nb1), "+v"(spec_wd), "+v"(spec_wd1));
             // The reads below are masked per lane and write their registers in
             // place; lanes without a value keep an old one, which nothing looks
             // at.  Under a branch of the whole wave (or with zeros for those
@@ -705,19 +705,19 @@ search_kernel(SearchKArgs a0) {
             // copy waits for the load.
             int nl0 = 0, nl1 = 0;
             auto read_adjacency = [&](bool go, int64_t first, int n) __attribute__((always_inline)) {
-                const int m0 = go ? min(n, WAVE) : 0;
-                const int m1 = go ? min(n - m0, WAVE) : 0;
-                if (lane < m0) spec_nb = (uint32_t)a.nbrs[first + lane];
-                if (lane < m1) spec_nb1 = (uint32_t)a.nbrs[first + WAVE + lane];
-                nl0 = go ? m0 : nl0;
-                nl1 = go ? m1 : nl1;
+                if (!go) return;
+                nl0 = min(n, WAVE);
+                nl1 = min(n - nl0, WAVE);
+                if (lane < nl0) spec_nb = (uint32_t)a.nbrs[first + lane];
+                if (lane < nl1) spec_nb1 = (uint32_t)a.nbrs[first + WAVE + lane];
             };
             auto read_visited = [&](bool go) __attribute__((always_inline)) {
+                if (!go) return;
                 // every earlier mark is complete before the visited words are
                 // read (of ids outside the window: the others are on chip)
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                const bool c0 = (lane < (go ? nl0 : 0)) & (spec_nb < n_ids) & (spec_nb - w0 >= W);
-                const bool c1 = (lane < (go ? nl1 : 0)) & (spec_nb1 < n_ids) & (spec_nb1 - w0 >= W);
+                const bool c0 = (lane < nl0) & (spec_nb < n_ids) & (spec_nb - w0 >= W);
+                const bool c1 = (lane < nl1) & (spec_nb1 < n_ids) & (spec_nb1 - w0 >= W);
                 if (c0)
                     spec_wd = __hip_atomic_load(&gbits[spec_nb >> 5], __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT);
