@@ -210,21 +210,45 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
         set_error("onng_search: waves_per_block must be in [1, 8]");
         return ONNG_ERR_INVALID_ARG;
     }
-    int o = 0;
-    P.off_pool = o; o = align16(o + P.pool_cap * 8);
-    P.off_s = o; o = align16(o + P.s_cap * 8);
-    P.off_stage = o; o = align16(o + 64 * 8);
-    P.off_stage2 = o; o = align16(o + 64 * 8);
-    P.off_ids = o; o = align16(o + 128 * 4);
-    P.off_vis = o; o = align16(o + (P.vis_log2 ? (4 << P.vis_log2) : 0));
-    P.off_misc = o; o = align16(o + 168 * 4);
-    P.lds_per_wave = o;
+    auto layout = [](SearchPlan *q) {
+        int o = 0;
+        q->off_pool = o; o = align16(o + q->pool_cap * 8);
+        q->off_s = o; o = align16(o + q->s_cap * 8);
+        q->off_stage = o; o = align16(o + 64 * 8);
+        q->off_stage2 = o; o = align16(o + 64 * 8);
+        q->off_ids = o; o = align16(o + 128 * 4);
+        q->off_vis = o; o = align16(o + (q->vis_log2 ? (4 << q->vis_log2) : 0));
+        q->off_misc = o; o = align16(o + 168 * 4);
+        q->lds_per_wave = o;
+    };
+    layout(&P);
+    // A batch of at most one wave per SIMD (4 a CU) leaves most of the LDS idle:
+    // a wave takes a block of its own (the queries then spread over all CUs) and
+    // the window grows to up to 2^18 ids while the batch stays resident at once
+    // and rows lie outside it.  Measured, before -> so: f32, 200k rows, 16 / 256
+    // / 1000 queries 302 -> 268, 473 -> 435, 636 -> 599 us; u8, 100k rows, k 100,
+    // the same batches 584 -> 558, 639 -> 609, 674 -> 654 us; fp8, 1M rows, 1000
+    // queries 1342 -> 1341 us.  From 2048 queries on the larger window costs
+    // waves: f32 663 -> 804, fp8 1618 -> 2023 us.
+    const int64_t cus = device_cu_count();
+    if ((!cfg || (!cfg->visited_log2 && !cfg->waves_per_block && !cfg->blocks)) && nq <= 4 * cus) {
+        P.wpb = 1;
+        for (int v = 13; v > P.vis_log2; v--) {
+            SearchPlan q = P;
+            q.vis_log2 = v;
+            layout(&q);
+            if ((16LL << v) < base->n && (160 * 1024 / q.lds_per_wave) * cus >= nq) {
+                P = q;
+                break;
+            }
+        }
+    }
     // the kernel uses the two stages as one 128-key buffer
     if (P.off_stage2 != P.off_stage + 64 * 8) {
         set_error("onng_search: internal LDS layout");
         return ONNG_ERR_UNSUPPORTED;
     }
-    size_t lds = (size_t)o * P.wpb;
+    size_t lds = (size_t)P.lds_per_wave * P.wpb;
     if (lds > 160 * 1024) {
         set_error("onng_search: on-chip state above 160 KiB per block");
         return ONNG_ERR_UNSUPPORTED;
