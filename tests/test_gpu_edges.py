@@ -271,3 +271,62 @@ def test_topk_wide_bound_and_filter(kind, n, dim, k):
     ids, d = A.build_knn(gpu_vectors(x, metric), k)
     assert np.array_equal(host(ids)[rows], rid)
     assert np.array_equal(host(d)[rows].astype(np.float64), rd)
+
+
+def _random_lists(n, degs, seed):
+    """Lists of the given lengths in turn; ids at random, so that some repeat."""
+    g = np.random.default_rng(seed)
+    off = np.zeros(n + 1, np.int64)
+    off[1:] = np.cumsum(np.resize(degs, n))
+    return off, g.integers(0, n, off[-1]).astype(np.int32)
+
+
+@pytest.mark.parametrize("kind,dim", [("u8", 16), ("u8", 128), ("f32", 17), ("f32", 100), ("f32", 128)])
+@pytest.mark.parametrize("shape", [None, dict(visited_log2=-1, s_capacity=64)])
+def test_search_batch_and_list_sizes(kind, dim, shape):
+    """List lengths around the 64-edge chunks and the two of a pass, batches of
+    every number of row passes, merges of few and of many keys.  The components
+    are whole numbers, so that float distances are exact in any order: ids,
+    distances and counts equal the oracle's."""
+    n, nq = 2500, 6
+    g = np.random.default_rng(dim)
+    hi = 256 if kind == "u8" else 40
+    x, q = (g.integers(0, hi, (m, dim)).astype(np.uint8 if kind == "u8" else np.float32) for m in (n, nq))
+    off, nb = _random_lists(n, [0, 1, 3, 63, 64, 65, 127, 128, 129, 191, 257, 20, 33], 5)
+    seeds = g.integers(0, n, (nq, 8)).astype(np.int32)
+    seeds[:, 5] = seeds[:, 2]
+    bv, qv = orc.Vectors.from_array(x, orc.L2SQ), orc.Vectors.from_array(q, orc.L2SQ)
+    A = api()
+    cfg = A.launch_config(**shape) if shape else None
+    B, Q, G = gpu_vectors(x, orc.L2SQ), gpu_vectors(q, orc.L2SQ), gpu_graph(off, nb)
+    for k, eps, ep in ((1, 0.0, orc.INF_EP), (4, 0.05, 65), (64, 0.1, orc.INF_EP), (100, 0.02, 130)):
+        say("search sizes", kind, dim, shape, k, eps, ep)
+        ref = orc.search(bv, off, nb, qv, seeds, k, eps, ep)
+        r = A.search(B, G, Q, to_dev(seeds), k=k, eps=eps, ep=ep, launch=cfg)
+        assert np.array_equal(host(r.ids), ref["ids"])
+        d = host(r.dists).astype(np.float64)
+        if kind == "u8":
+            d[d == 2 ** 31 - 1] = np.inf
+        assert np.array_equal(d, ref["dists"])
+        assert np.array_equal(host(r.dc), ref["dc"])
+        assert np.array_equal(host(r.hops), ref["hops"])
+
+
+@pytest.mark.parametrize("nq", [1, 5, 1024, 1025])
+def test_search_small_batch_window(nq):
+    """The launch of a batch that leaves the chip idle (window of 2^18 ids, a
+    block a wave) against the general one and the off-chip bitset."""
+    n, dim = 140_000, 16
+    g = np.random.default_rng(9)
+    x, q = (g.integers(0, 256, (m, dim)).astype(np.uint8) for m in (n, nq))
+    off, nb = _random_lists(n, [12, 70, 24], 6)
+    A = api()
+    B, Q, G = gpu_vectors(x, orc.L2SQ), gpu_vectors(q, orc.L2SQ), gpu_graph(off, nb)
+    seeds = to_dev(g.integers(0, n, (nq, 8)).astype(np.int32))
+    say("search window", nq)
+    out = [A.search(B, G, Q, seeds, k=10, eps=0.1, ep=orc.INF_EP, launch=c)
+           for c in (None, A.launch_config(visited_log2=11, waves_per_block=4),
+                     A.launch_config(visited_log2=-1))]
+    for r in out[1:]:
+        for name in ("ids", "dists", "dc", "hops", "scanned"):
+            assert np.array_equal(host(getattr(r, name)), host(getattr(out[0], name))), name
