@@ -447,14 +447,15 @@ __global__ void __launch_bounds__(256) sac_select_kernel(
 //
 // A work item is up to CAP consecutive targets of one node's list: its
 // undecided targets go into a hash table in LDS, and the lists of the node's
-// not yet removed neighbours stream past it, coalesced, the next one's load in
-// flight.  Lists of at most 128 are one item of one wave, in rank order, so an
+// not yet removed neighbours stream past it, coalesced, in pieces of 64 entries
+// of which four are in flight.  Lists of at most 128 are one item of one wave, in rank order, so an
 // edge kept by this very pass already serves as a witness; longer lists are
 // cut into items of 512 targets, each taken by four waves in no order, which
-// count only edges decided before.  What bounds it is the LDS probing and the
-// chain of one list per step, not the bytes (those 13.5M edges: 11.7 ms; with
-// one table and one block size per class of list length, in three launches
-// a pass, 15.2 ms).  The earlier form ran one round per rank (as many as the
+// count only edges decided before.  Three quarters of a wave's time it waits for
+// list pieces, scattered runs of some 270 bytes: 20 GB over all passes, at
+// 2 TB/s.  Those 13.5M edges take 10.4 ms (11.7 with one list in flight; with a
+// table whose buckets of four ids are one 16-byte LDS read 13.8; with one block
+// size per class of list length, in three launches a pass, 15.2).  The earlier form ran one round per rank (as many as the
 // longest list, each with a same-round settling pass and a host
 // synchronisation) with a binary search per kept neighbour: 458 ms.
 
@@ -462,6 +463,7 @@ constexpr int8_t ST_UNDECIDED = 0, ST_KEPT = 1, ST_REMOVED = 2;
 constexpr int64_t PA_MAX_DEGREE = (1 << 20) - 1;   // longer lists are refused
 constexpr int PA_SMALL = 128;          // longest list that one wave takes
 constexpr int PA_CHUNK = 512;          // targets per item of a longer list
+constexpr int PA_AHEAD = 4;            // pieces of 64 list entries in flight per wave
 constexpr uint32_t PA_EMPTY = 0xFFFFFFFFu;   // no node id (ids are below 2^31)
 
 // The hash table has four slots per target, so that probe runs stay short; a
@@ -554,67 +556,68 @@ __device__ void pa_item(const PaGraph<LenT> &g, PaTable<LenT, CAP, RankT> &T, in
                 cnl = (int32_t)min<int64_t>(g.off[cl + 1] - cbl, lim);
             }
         }
-        uint64_t todo = ballot(cnl > 0);
-        int32_t x = 0;
-        LenT lx = 0;
-        int sx = ST_REMOVED;
-        auto fetch = [&](int64_t at, int cnt) {
-            sx = ST_REMOVED;
-            if (lane < cnt) {
-                x = g.nbrs[at + lane];
-                lx = g.lens[at + lane];
-                sx = ld_relaxed(&g.st[at + lane]);
-            }
-        };
-        if (todo) {
-            const int src = (int)__builtin_ctzll(todo);
-            fetch(readlane64(cbl, src), __builtin_amdgcn_readlane(cnl, src));
-        }
-        while (todo) {
-            const int src = (int)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            const int i = ib + src;
-            int si = __builtin_amdgcn_readlane(sl, src);
-            const int32_t c = __builtin_amdgcn_readlane(cl, src);
-            const int64_t cb = readlane64(cbl, src);
+        // A unit is 64 entries of one list.  PA_AHEAD of them are in flight; the
+        // loads are unconditional (lanes past the end read the last entry, past
+        // the last unit the item's own list), so that the wait for one unit
+        // leaves the later ones in flight.
+        uint64_t todo = ballot(cnl > 0), ask = todo;
+        int todo_j = 0, ask_j = 0;   // first entry of the unit to take, to request
+        if (!todo) continue;
+        int32_t x[PA_AHEAD];
+        LenT lx[PA_AHEAD];
+        uint32_t sx[PA_AHEAD];   // the word of the status (extending a byte would wait for it)
+        auto request = [&](int d) __attribute__((always_inline)) {
+            const int src = (int)__builtin_ctzll(ask | 1ull << 63);
             const int cn = __builtin_amdgcn_readlane(cnl, src);
-            int32_t y = x;
-            LenT ly = lx;
-            int sy = sx;
-            if (todo) {
-                const int nx = (int)__builtin_ctzll(todo);
-                fetch(readlane64(cbl, nx), __builtin_amdgcn_readlane(cnl, nx));
-            }
-            if (si == ST_UNDECIDED && i >= t0) {
-                if (uni((int)T.rem[i - t0])) continue;
-                // one wave, in rank order: all that could hold it back has run
-                if (WAVES == 1 && !uni((int)T.pend[i - t0])) si = ST_KEPT;
-            }
-            for (int jc0 = 0;;) {
-                if (sy != ST_REMOVED) {
-                    const int jc = jc0 + lane;
-                    uint32_t h = Table::slot((uint32_t)y);
+            const int cnt = ask ? min(cn - ask_j, WAVE) : 1;
+            const int64_t at = (ask ? readlane64(cbl, src) + ask_j : b) + min(lane, cnt - 1);
+            x[d] = g.nbrs[at];
+            lx[d] = g.lens[at];
+            sx[d] = ld_relaxed(reinterpret_cast<const uint32_t *>(g.st) + (at >> 2));
+            const bool more = ask && ask_j + WAVE < cn;
+            ask = more ? ask : ask & (ask - 1);
+            ask_j = more ? ask_j + WAVE : 0;
+        };
+#pragma unroll
+        for (int d = 0; d < PA_AHEAD; d++) request(d);
+        while (todo) {
+#pragma unroll
+            for (int d = 0; d < PA_AHEAD; d++) {
+                if (!todo) break;
+                const int src = (int)__builtin_ctzll(todo);
+                const int i = ib + src;
+                int si = __builtin_amdgcn_readlane(sl, src);
+                const int32_t c = __builtin_amdgcn_readlane(cl, src);
+                const int cn = __builtin_amdgcn_readlane(cnl, src);
+                const int jc = todo_j + lane;
+                bool look = jc < cn;
+                if (si == ST_UNDECIDED && i >= t0) {
+                    const int rem = T.rem[i - t0], pend = T.pend[i - t0];
+                    look = look && !rem;
+                    // one wave, in rank order: all that could hold it back has run
+                    if (WAVES == 1 && !uni(pend)) si = ST_KEPT;
+                }
+                const int sy = (int)(sx[d] >> (((__builtin_amdgcn_readlane((int)cbl, src) + lane) & 3) * 8)) & 0xff;
+                if (look && sy != ST_REMOVED) {
+                    const uint32_t y = (uint32_t)x[d];
+                    uint32_t h = Table::slot(y);
                     for (uint32_t id; (id = T.hid[h]) != PA_EMPTY; h = Table::next(h)) {
-                        if (id != (uint32_t)y) continue;
+                        if (id != y) continue;
                         const int k = T.hrank[h];
                         const int j = t0 + k;
-                        if (j > i && (jc < j || (jc == j && c < v)) && ly < T.len[k]) {
+                        if (j > i && (jc < j || (jc == j && c < v)) && lx[d] < T.len[k]) {
                             if (si == ST_KEPT && sy == ST_KEPT) T.rem[k] = 1;
                             else T.pend[k] = 1;
                         }
                         if (!dup) break;
                     }
                 }
-                jc0 += WAVE;
-                if (jc0 >= cn) break;
-                sy = ST_REMOVED;
-                if (jc0 + lane < cn) {
-                    y = g.nbrs[cb + jc0 + lane];
-                    ly = g.lens[cb + jc0 + lane];
-                    sy = ld_relaxed(&g.st[cb + jc0 + lane]);
-                }
+                const bool more = todo_j + WAVE < cn;
+                todo = more ? todo : todo & (todo - 1);
+                todo_j = more ? todo_j + WAVE : 0;
+                request(d);
+                if constexpr (WAVES == 1) wave_sync();   // this unit's flags before the next status
             }
-            if constexpr (WAVES == 1) wave_sync();   // this step's flags before the next status
         }
     }
     sync();
