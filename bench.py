@@ -1189,17 +1189,18 @@ def build_only(args, torch, A, dg, cfg, xt, metric, dev):
     n = cfg.n_base
     ops = 2.0 * n * n * cfg.dim
     u8 = cfg.kind == "u8"
-    # float rows of at most 128 components at this size take the bf16 screen
-    # (exact f32 recompute of the survivors); its MFMAs run over 128 components
-    bf16 = not u8 and cfg.dim <= 128 and n >= 32768
-    peak = 5000.0 if u8 else 2500.0 if bf16 else 157.3   # dense int8 / bf16 / f32, x 1e12
+    # float rows of at most 128 components at this size take the f16 screen
+    # (exact f32 recompute of the survivors); its MFMAs run over 128 components,
+    # once over all columns and once over a sample of them
+    screen = not u8 and cfg.dim <= 128 and n >= 32768
+    peak = 5000.0 if u8 else 2500.0 if screen else 157.3   # dense int8 / f16 / f32, x 1e12
     achieved = ops / (ms * 1e-3) / 1e12
     out = {"build": "exact kNN table", "workload": cfg.name, "n": n, "dim": cfg.dim,
            "k": cfg.knn_k,
-           "dtype": "u8 (int8 MFMA)" if u8 else ("f32 (bf16 MFMA screen, f32 recompute)" if bf16
+           "dtype": "u8 (int8 MFMA)" if u8 else ("f32 (f16 MFMA screen, f32 recompute)" if screen
                                                  else "f32 (f32 MFMA)"),
            "ms_per_build": round(ms, 3), "ops_per_build": ops,
-           "mfma_ops_per_build": 2.0 * n * n * (128 if bf16 else cfg.dim),
+           "mfma_ops_per_build": 2.0 * n * n * (128 if screen else cfg.dim),
            "achieved": round(achieved, 2), "peak": peak,
            "unit": "TOP/s" if u8 else "TFLOP/s", "frac": round(achieved / peak, 4),
            "reps": args.build_reps}

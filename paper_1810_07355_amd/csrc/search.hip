@@ -28,6 +28,20 @@
 // larger r but the batch rejects is beyond every later range and could only
 // end the search when popped, at a pop where the batch's next candidate ends
 // it too.
+//
+// An expansion is one dependent chain, and a query's expansions follow each
+// other, so the kernel's time is the sum of these chains over the waves that a
+// CU holds (12: registers and LDS), and for a batch that fits the chip, or the
+// last queries of a larger one, the longest query's chain itself.  What an
+// expansion waits for is kept to one trip to memory, its rows: the offsets,
+// adjacency and visited words of the next pop are read ahead (a pop hits them in
+// 97 % of the expansions and more).  The rest is instructions: about 600 of
+// u8 rows with 4 new rows per expansion, 1,300 of fp8 rows with 68, at 4 cycles
+// and more each; so reads are kept in registers or scalars where that saves an
+// LDS trip, and a merge of few keys does without searches.
+// Kernel alone, before and after that work: u8, 100k x 128, 1000 queries, k 100:
+// 935 -> 654 us; f32, 200k x 100, 10k queries: 1511 -> 1254 us; fp8 + rerank,
+// 1M x 100, 10k queries: 4300 -> 3232 us.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -632,7 +632,7 @@ int topk_bm(int32_t k, int dtype, int32_t dim, int side_words) {
 
 // The wide u8 kernel takes over when its 256-row blocks alone fill the chip
 // (one per compute unit at least) and the rows fit two 64-byte k-steps.
-// The bf16-screened f32 kernel: f32 rows of at most 128 components, its
+// The f16-screened passes (and the bf16-screened kernel behind them): f32 rows of at most 128 components, its
 // 128-row blocks filling the chip.
 bool topk_use_wide_f32(const onng_vectors *Q, int64_t nb, int32_t k) {
     return Q->dtype == ONNG_F32 && Q->dim <= FW_NCH * 32 && nb >= 16 * FW_BN &&

@@ -193,7 +193,7 @@ onng_status launch_topk_wide_f32(const TopkArgs &a, const onng_vectors *Q, bool 
                                  uint8_t *qh, uint8_t *bh, uint32_t *ymax, uint64_t *glist,
                                  uint32_t *gcand, hipStream_t st);
 
-// ---- many query rows by a bound and a filter (topk_wide.hip) -------------
+// ---- many query rows by a bound and a filter (topk_wide_bound.hip) -------
 // The two passes of topk_bound.h for many query rows: a wave holds 64 of them
 // (four 16-row blocks), whose operands stay in registers for the sweep, so each
 // operand read from LDS feeds four matrix instructions.

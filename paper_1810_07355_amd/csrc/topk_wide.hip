@@ -1,5 +1,7 @@
-// Exact top-k of u8 rows (squared L2, at most 128 components) for many query
-// rows: the wide form of the top-k kernel.  Built with MFMA results in
+// Exact top-k of u8 rows (squared L2, at most 128 components) and of f32 rows
+// (a bf16 screen, exact recompute) for many query rows, with a kept list per
+// row: for rows whose candidates overflow the bound-and-filter passes
+// (topk_wide_bound.hip), and for u8 bases too large for these.  Built with MFMA results in
 // ordinary VGPRs (see build.py), which the one-comparison epilogue reads
 // directly.
 #include <hip/hip_runtime.h>
