@@ -222,6 +222,16 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
         q->lds_per_wave = o;
     };
     layout(&P);
+    // the kernel uses the two stages as one 128-key buffer
+    if (P.off_stage2 != P.off_stage + 64 * 8) {
+        set_error("onng_search: internal LDS layout");
+        return ONNG_ERR_UNSUPPORTED;
+    }
+    size_t lds = (size_t)P.lds_per_wave * P.wpb;
+    if (lds > 160 * 1024) {
+        set_error("onng_search: on-chip state above 160 KiB per block");
+        return ONNG_ERR_UNSUPPORTED;
+    }
     // A batch of at most one wave per SIMD (4 a CU) leaves most of the LDS idle:
     // a wave takes a block of its own (the queries then spread over all CUs) and
     // the window grows to up to 2^18 ids while the batch stays resident at once
@@ -231,7 +241,9 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
     // queries 1342 -> 1341 us.  From 2048 queries on the larger window costs
     // waves: f32 663 -> 804, fp8 1618 -> 2023 us.
     const int64_t cus = device_cu_count();
-    if ((!cfg || (!cfg->visited_log2 && !cfg->waves_per_block && !cfg->blocks)) && nq <= 4 * cus) {
+    const bool few = (!cfg || (!cfg->visited_log2 && !cfg->waves_per_block && !cfg->blocks)) &&
+                     nq <= 4 * cus;
+    if (few) {
         P.wpb = 1;
         for (int v = 13; v > P.vis_log2; v--) {
             SearchPlan q = P;
@@ -242,16 +254,7 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
                 break;
             }
         }
-    }
-    // the kernel uses the two stages as one 128-key buffer
-    if (P.off_stage2 != P.off_stage + 64 * 8) {
-        set_error("onng_search: internal LDS layout");
-        return ONNG_ERR_UNSUPPORTED;
-    }
-    size_t lds = (size_t)P.lds_per_wave * P.wpb;
-    if (lds > 160 * 1024) {
-        set_error("onng_search: on-chip state above 160 KiB per block");
-        return ONNG_ERR_UNSUPPORTED;
+        lds = (size_t)P.lds_per_wave * P.wpb;
     }
     if (hipFuncSetAttribute(P.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
         hipSuccess) {
@@ -271,9 +274,11 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
     P.gbits_words = ((base->n + 31) / 32 + 31) / 32 * 32;
     Carver c(nullptr);
     c.take<int32_t>(64);
-    c.take<uint32_t>((size_t)P.slots * P.gbits_words);
-    c.take<int32_t>((size_t)P.slots * P.vlog_cap);
-    c.take<uint64_t>((size_t)P.slots * 2 * P.spill_cap);
+    // (a small batch's workspace also serves the same batch in blocks of four)
+    const size_t slots = few ? (size_t)(P.slots + 3) / 4 * 4 : (size_t)P.slots;
+    c.take<uint32_t>(slots * P.gbits_words);
+    c.take<int32_t>(slots * P.vlog_cap);
+    c.take<uint64_t>(slots * 2 * P.spill_cap);
     P.ws = c.size() + 256;
     *plan = P;
     return ONNG_OK;
@@ -928,8 +933,14 @@ onng_status onng_search_static(const onng_vectors *base, const onng_graph *graph
     onng_launch_config tuned;
     const onng_launch_config *cfg0 = params->launch;
     if (!cfg0 && lookup_tuned(base, params, &tuned)) cfg0 = &tuned;
+    // The shape is fixed here, not chosen by the batch: the scratch is counted in
+    // blocks of this shape below, and whether a base fits must not depend on the
+    // number of queries.
+    onng_launch_config c = cfg0 ? *cfg0 : onng_launch_config{};
+    if (!c.waves_per_block) c.waves_per_block = 4;
+    if (!c.visited_log2) c.visited_log2 = 11;
     SearchPlan P;
-    ONNG_TRY(make_plan(base, queries->n, params, cfg0, &P));
+    ONNG_TRY(make_plan(base, queries->n, params, &c, &P));
     // the same shape with as many persistent blocks as the scratch holds; the
     // carve adds at most 256 bytes of alignment per region (five regions)
     const size_t per_slot = (size_t)P.gbits_words * 4 + (size_t)P.vlog_cap * 4 +
@@ -945,7 +956,6 @@ onng_status onng_search_static(const onng_vectors *base, const onng_graph *graph
                   std::to_string(cap) + " (use onng_search with a workspace)");
         return ONNG_ERR_CAPACITY;
     }
-    onng_launch_config c = cfg0 ? *cfg0 : onng_launch_config{};
     c.blocks = (int32_t)std::min<int64_t>(P.blocks, max_blocks);
     SearchPlan P2;
     ONNG_TRY(make_plan(base, queries->n, params, &c, &P2));

@@ -330,3 +330,30 @@ def test_search_small_batch_window(nq):
     for r in out[1:]:
         for name in ("ids", "dists", "dc", "hops", "scanned"):
             assert np.array_equal(host(getattr(r, name)), host(getattr(out[0], name))), name
+
+
+@pytest.mark.parametrize("nq", [5, 901, 1023])
+def test_search_small_batch_scratch(nq):
+    """Batches whose own launch is a block a wave: the static scratch (fewer
+    slots than queries) and the autotuner on the default workspace take them as
+    they take larger ones."""
+    n, dim = 12_000, 32
+    g = np.random.default_rng(nq)
+    x, q = (g.integers(0, 256, (m, dim)).astype(np.uint8) for m in (n, nq))
+    off, nb = _random_lists(n, [12, 70, 24], 6)
+    A = api()
+    B, Q, G = gpu_vectors(x, orc.L2SQ), gpu_vectors(q, orc.L2SQ), gpu_graph(off, nb)
+    seeds = to_dev(g.integers(0, n, (nq, 8)).astype(np.int32))
+    say("search scratch", nq)
+    kw = dict(k=10, eps=0.05, ep=40)
+    ref = A.search(B, G, Q, seeds, **kw)
+    ids, dc = host(ref.ids), host(ref.dc)
+    got = A.search(B, G, Q, seeds, static_scratch=True, **kw)
+    assert np.array_equal(host(got.ids), ids) and np.array_equal(host(got.dc), dc)
+    r = A.SearchRequest(B, G, Q, seeds, **kw)
+    ws = r.ws.numel()
+    best = r.autotune()
+    # the largest shape the tuner tries has the default one's slots
+    assert best.waves_per_block in (2, 4) and r.ws_bytes <= ws
+    r.run()
+    assert np.array_equal(host(r.ids), ids) and np.array_equal(host(r.dc), dc)
