@@ -97,7 +97,7 @@ __device__ __forceinline__ int64_t sample_row(uint32_t i, int ns_log2, int64_t n
 
 // Norms of a staged tile's BN rows (CPR 16-byte chunks each) by nthr threads,
 // sixteen lanes per row: int32 of the shifted u8 rows; f32 in the order of
-// norms_f32_kernel (one component per lane, chains 64 apart, then lanes 32, 16,
+// norms_kernel<float> (one component per lane, chains 64 apart, then lanes 32, 16,
 // .. 1 apart), four of its lanes in each of these, so the same bits.
 template <bool U8, int CPR>
 __device__ __forceinline__ void tile_norms(const uint8_t *tile, int lds_pitch, int nthr, uint32_t *out) {
