@@ -126,6 +126,19 @@ __device__ __forceinline__ T group_sum_rt(T x, int G) {
     return x;
 }
 
+// The same sum with masks for branches: g8 and g16 are all ones where G is at
+// least 8, 16, and a step that G does not have adds zero.  x is never -0 (it is
+// a sum that starts from +0), so that changes nothing.
+template <typename T>
+__device__ __forceinline__ T group_sum_masked(T x, int G, uint32_t g8, uint32_t g16) {
+    x += dpp<DPP_QP_1032>(x);
+    x += dpp<DPP_QP_2301>(x);
+    x += __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, dpp<DPP_HALF_MIRROR>(x)) & g8);
+    x += __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, dpp<DPP_ROW_ROR8>(x)) & g16);
+    if (G >= 32) x += swz_xor<16>(x);
+    return x;
+}
+
 // Minimum over all 64 lanes (every lane receives it).
 __device__ __forceinline__ uint64_t wave_min64(uint64_t v) {
     uint64_t o;
