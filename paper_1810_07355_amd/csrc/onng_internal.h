@@ -88,8 +88,8 @@ __device__ __host__ inline float unord_f32(uint32_t o) {
     return __uint_as_float(u);
 }
 
-// Sort key of (distance, id): distance in the high word (int distances are
-// < 2^24 and used as is), id in the low word.
+// Sort key of (distance, id): distance in the high word (int distances, at most
+// dim * 255^2, are used as is), id in the low word.
 __device__ __host__ inline uint64_t make_key(uint32_t dord, uint32_t id) {
     return (uint64_t(dord) << 32) | id;
 }

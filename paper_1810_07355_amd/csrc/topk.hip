@@ -970,9 +970,11 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
             void *bargs[] = {&ba};
             ONNG_HIP(hipLaunchKernel(fn, dim3((unsigned)((Q->n + bm - 1) / bm), (unsigned)bp.splits[m]),
                                      dim3((unsigned)bound_threads(bp.rw)), bargs, bp.lds[m], st));
-            // (f32 bounds need no more than 16 bits past the exponent's first)
+            // (u8: the bits of the largest distance, dim * 255^2, 25 of them at 512
+            // components; f32 bounds need no more than 16 bits past the exponent's first)
             if (m == 0)
-                launch_bound_select(mins, Q->n, bp.groups, rank, u8 ? 23 : 31, u8 ? 0 : 8, tau, cnt, redo, st);
+                launch_bound_select(mins, Q->n, bp.groups, rank, u8 ? 31 - __builtin_clz(Q->dim * 65025u) : 31,
+                                    u8 ? 0 : 8, tau, cnt, redo, st);
         }
         launch_bound_sort(u8, bcand, bp.cap, cnt, Q->n, k, ids, dists, redo, 0, st);
         // rows that overflowed, if any
