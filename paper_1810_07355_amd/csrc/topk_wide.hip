@@ -560,7 +560,7 @@ topk_f32_wide_kernel(TopkArgs a, FwRows h, uint64_t *glist, uint32_t *gcand) {
                     if (!(cok && acc[rb][r] >= tq[rb][r])) continue;
                     const int lr = wl0 + rb * 16 + ro + r;
                     const int64_t crow = row0 + lr;
-                    if (a.exclude_self && col == crow) continue;
+                    if (a.exclude_self && (a.b_ids ? (int64_t)a.b_ids[col] : col) == crow) continue;
                     const int slot = atomicAdd(&cnt[lr], 1);
                     gcand[(size_t)crow * FW_CB + slot] = (uint32_t)col;
                     added = true;

@@ -222,7 +222,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) t
 #pragma unroll 1
         for (int e = lane; e < held; e += WAVE) {
             const int r = q_row[e];
-            if (a.exclude_self && (int64_t)((uint32_t)q_key[e] & 0x7FFFFFFFu) == A.row0 + lrow0 + r) q_row[e] = Q_SELF;
+            bool self = false;
+            if (a.exclude_self) {   // the row's own id, not its place in a candidate list
+                const uint32_t col = (uint32_t)q_key[e] & 0x7FFFFFFFu;
+                self = (a.b_ids ? (int64_t)a.b_ids[col] : (int64_t)col) == A.row0 + lrow0 + r;
+            }
+            if (self) q_row[e] = Q_SELF;
             else q_num[e] = (uint8_t)atomicAdd(&q_cnt[r], 1);
         }
         wave_sync();

@@ -33,3 +33,30 @@ def test_topk_u8_distances_past_24_bits(dim, nq):
         assert (rd[::44, 24:] > 2 ** 24).all()
     assert np.array_equal(host(ids), rid)
     assert np.array_equal(host(d).astype(np.float64), rd)
+
+
+@pytest.mark.parametrize("kind,n,nq,nc,k", [
+    ("u8", 5000, 12, 1500, 8), ("u8", 5000, 60, 1024, 20), ("u8", 1700, 1700, 1600, 8), ("u8", 65536, 65536, 1100, 8),
+    ("u8", 900, 900, 500, 8), ("f32l2", 5000, 12, 1500, 8), ("f32cos", 1700, 1700, 1600, 20),
+    ("f32l2", 32768, 32768, 1100, 8), ("f32cos", 32768, 32768, 1500, 20)])
+def test_topk_candidates_without_self(kind, n, nq, nc, k):
+    """A candidate list (in no order) with self exclusion: the base id that
+    equals the query's row is left out, wherever it stands in the list.  Narrow
+    and wide forms, with f32 rows of small whole numbers, whose distances are
+    exact."""
+    say("topk candidates without self", kind, n, nq, nc)
+    A = api()
+    g = np.random.default_rng(n + nq + nc)
+    metric = orc.COS if kind == "f32cos" else orc.L2SQ
+    dim = 24
+    x = g.integers(0, 250 if kind == "u8" else 14, (n, dim)).astype(np.uint8 if kind == "u8" else np.float32)
+    cand = g.permutation(n)[:nc].astype(np.int32)
+    own = [1, nq // 2, nq - 1]
+    cand[g.permutation(nc)[:3]] = own
+    rows = np.unique(np.concatenate([own, g.choice(nq, min(nq, 150), replace=False),
+                                     [c for c in cand if c < nq][:60], np.arange(min(nq, 20))]))
+    bv = orc.Vectors.from_array(x, metric)
+    rid, rd = orc.topk(bv, bv, k, q_rows=rows, cand=cand, exclude_self=True)
+    ids, d = A.topk(gpu_vectors(x[:nq], metric), gpu_vectors(x, metric), k, cand=to_dev(cand), exclude_self=True)
+    assert np.array_equal(host(ids)[rows], rid)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
