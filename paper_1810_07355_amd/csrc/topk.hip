@@ -9,7 +9,7 @@
 //
 // From 1024 base rows on, topk_bound.h's two passes do the work; topk_kernel
 // here takes smaller bases, larger shapes than their LDS holds, and the rows
-// whose candidate buffer overflowed there.
+// whose candidate buffer overflowed there or fell short of k.
 // A block owns BM query rows (16 per wave) and sweeps the base rows in tiles
 // of 64 staged in LDS.  Each row keeps its current k best keys sorted in LDS
 // and a buffer of candidates that beat its k-th key; the buffer is sorted and
@@ -528,10 +528,12 @@ __global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins,
     }
 }
 
-// One block per row: its cnt[row] candidates in order, the k first written
-// (padded when there are fewer).  A row with more than `cap` is left to the
-// general kernel (redo[1 + row], and redo[0] for any).  Up to 64 candidates sort in registers, more by a
-// bitonic network in LDS; with few rows the block has four waves.
+// One block per row: its cnt[row] candidates in order, the k first written.
+// A row with more than `cap`, or with fewer than
+// k (there are at least 1024 base rows, but the bound allows for one copy of the
+// row itself and a candidate list may hold more), is left to the general kernel
+// (redo[1 + row], and redo[0] for any).  Up to 64 candidates sort in registers,
+// more by a bitonic network in LDS; with few rows the block has four waves.
 template <bool U8>
 __global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, int cap, const int32_t *cnt,
                                                          int k, int32_t *out_ids, void *out_d,
@@ -540,27 +542,24 @@ __global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, i
     const int64_t row = blockIdx.x;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int n = uni(cnt[row]);
-    if (tid == 0) redo[1 + row0 + row] = n > cap;
-    if (n > cap) {
+    const bool bad = n > cap || n < k;
+    if (tid == 0) redo[1 + row0 + row] = bad;
+    if (bad) {
         if (tid == 0) redo[0] = 1;
         return;
     }
     const uint64_t *src = cand + row * cap;
     auto put = [&](int i, uint64_t key) {
         const int64_t at = (row0 + row) * k + i;
-        out_ids[at] = i < n ? (int32_t)(uint32_t)key : -1;
-        if constexpr (U8)
-            reinterpret_cast<int32_t *>(out_d)[at] = i < n ? (int32_t)(key >> 32) : INT32_MAX;
-        else
-            reinterpret_cast<float *>(out_d)[at] =
-                i < n ? unord_f32((uint32_t)(key >> 32)) : __builtin_inff();
+        out_ids[at] = (int32_t)(uint32_t)key;
+        if constexpr (U8) reinterpret_cast<int32_t *>(out_d)[at] = (int32_t)(key >> 32);
+        else reinterpret_cast<float *>(out_d)[at] = unord_f32((uint32_t)(key >> 32));
     };
     if (n <= WAVE) {
         if (tid >= WAVE) return;
         uint64_t key = tid < n ? src[tid] : KEY_MAX;
-        key = wave_sort(key, pow2_at_least(max(n, 1)));
+        key = wave_sort(key, pow2_at_least(n));
         if (tid < k) put(tid, key);
-        for (int i = WAVE + tid; i < k; i += WAVE) put(i, KEY_MAX);
         return;
     }
     const int w = pow2_at_least(n);
@@ -575,7 +574,7 @@ __global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, i
             }
         }
     __syncthreads();
-    for (int i = tid; i < k; i += nt) put(i, i < w ? sk[i] : KEY_MAX);
+    for (int i = tid; i < k; i += nt) put(i, sk[i]);
 }
 
 // Parts per row block.  With one block per compute unit (the LDS holds one
@@ -927,7 +926,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         if (wp.use) {
             const onng_status s = launch_wide_bound(a, Q, same, wp, wb, st);
             if (s != ONNG_OK) return s;
-            a.only = wb.redo;   // rows that overflowed, if any
+            a.only = wb.redo;   // rows that overflowed or fell short, if any
         }
         return launch_topk_wide_f32(a, Q, same, fqh, fbh, fymax, flist, fcand, st);
     }
@@ -977,7 +976,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
                                     u8 ? 0 : 8, tau, cnt, redo, st);
         }
         launch_bound_sort(u8, bcand, bp.cap, cnt, Q->n, k, ids, dists, redo, 0, st);
-        // rows that overflowed, if any
+        // rows that overflowed or fell short, if any
         a.only = redo;
     }
     const int nch = nch_for(Q->dtype, Q->dim);

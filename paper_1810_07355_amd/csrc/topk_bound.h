@@ -13,7 +13,8 @@
 // share a compute unit instead of one, and the matrix instructions are what is
 // left to wait for.  The products are those of topk.hip, in the same order: the distances
 // are the same bit for bit.  A row whose buffer overflows (distances tied or
-// very unevenly spread) is left to topk_kernel, which redoes such rows only.
+// very unevenly spread), or holds fewer than k, is left to topk_kernel, which
+// redoes such rows only.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -39,12 +39,14 @@ def test_topk_u8_distances_past_24_bits(dim, nq):
     ("u8", 5000, 12, 1500, 8), ("u8", 5000, 60, 1024, 20), ("u8", 1700, 1700, 1600, 8), ("u8", 65536, 65536, 1100, 8),
     ("u8", 900, 900, 500, 8), ("f32l2", 5000, 12, 1500, 8), ("f32cos", 1700, 1700, 1600, 20),
     ("f32l2", 32768, 32768, 1100, 8), ("f32cos", 32768, 32768, 1500, 20)])
-def test_topk_candidates_without_self(kind, n, nq, nc, k):
+@pytest.mark.parametrize("repeat", [False, True])
+def test_topk_candidates_without_self(kind, n, nq, nc, k, repeat):
     """A candidate list (in no order) with self exclusion: the base id that
-    equals the query's row is left out, wherever it stands in the list.  Narrow
-    and wide forms, with f32 rows of small whole numbers, whose distances are
-    exact."""
-    say("topk candidates without self", kind, n, nq, nc)
+    equals the query's row is left out, wherever it stands in the list.  With
+    `repeat` the list also holds some rows' own ids many times over: all copies
+    are left out there and kept elsewhere.  Narrow and wide forms, with f32
+    rows of small whole numbers, whose distances are exact."""
+    say("topk candidates without self", kind, n, nq, nc, repeat)
     A = api()
     g = np.random.default_rng(n + nq + nc)
     metric = orc.COS if kind == "f32cos" else orc.L2SQ
@@ -53,6 +55,9 @@ def test_topk_candidates_without_self(kind, n, nq, nc, k):
     cand = g.permutation(n)[:nc].astype(np.int32)
     own = [1, nq // 2, nq - 1]
     cand[g.permutation(nc)[:3]] = own
+    if repeat:
+        at = g.permutation(nc)[:90]
+        cand[at] = np.repeat(own, 30)
     rows = np.unique(np.concatenate([own, g.choice(nq, min(nq, 150), replace=False),
                                      [c for c in cand if c < nq][:60], np.arange(min(nq, 20))]))
     bv = orc.Vectors.from_array(x, metric)
