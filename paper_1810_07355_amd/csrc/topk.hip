@@ -916,12 +916,12 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     a.lds_pitch = lds_pitch_for(Q->dtype, B->dim);
     a.out_ids = ids;
     a.out_d = dists;
+    // the queries are the base rows: their converted copies serve both
+    const bool same = !cand && Q->data == B->data && Q->n == B->n && Q->pitch_bytes == B->pitch_bytes;
     if (wide_f32) {
         a.splits = 1;
         a.tiles_per_split = (int)((nb + FW_BN - 1) / FW_BN);
         a.part = nullptr;
-        const bool same = !cand && Q->data == B->data && Q->n == B->n &&
-                          Q->pitch_bytes == B->pitch_bytes;
         a.rotate = same ? 1 : 0;
         if (wp.use) {
             const onng_status s = launch_wide_bound(a, Q, same, wp, wb, st);
@@ -934,9 +934,9 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         a.splits = 1;
         a.tiles_per_split = (int)((nb + BN - 1) / BN);
         a.part = nullptr;
-        a.rotate = (!cand && Q->data == B->data && Q->n == B->n) ? 1 : 0;
+        a.rotate = same ? 1 : 0;
         if (wp.use) {
-            const onng_status s = launch_wide_bound(a, Q, a.rotate != 0, wp, wb, st);
+            const onng_status s = launch_wide_bound(a, Q, same, wp, wb, st);
             if (s != ONNG_OK) return s;
             a.only = wb.redo;
         }
@@ -987,7 +987,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     ONNG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const int ntiles = (int)((nb + BN - 1) / BN);
     a.splits = sp;
-    a.rotate = (!cand && sp == 1 && Q->data == B->data && Q->n == B->n) ? 1 : 0;
+    a.rotate = same && sp == 1 ? 1 : 0;
     a.tiles_per_split = (ntiles + sp - 1) / sp;
     a.part = part;
     dim3 grid((unsigned)((Q->n + a.bm - 1) / a.bm), (unsigned)sp),

@@ -65,3 +65,24 @@ def test_topk_candidates_without_self(kind, n, nq, nc, k, repeat):
     ids, d = A.topk(gpu_vectors(x[:nq], metric), gpu_vectors(x, metric), k, cand=to_dev(cand), exclude_self=True)
     assert np.array_equal(host(ids)[rows], rid)
     assert np.array_equal(host(d)[rows].astype(np.float64), rd)
+
+
+@pytest.mark.parametrize("dtype", [torch.uint8, torch.float32])
+def test_topk_one_buffer_two_pitches(dtype):
+    """Queries and base over one buffer, the same number of rows, the base's
+    twice as far apart: the queries are the buffer's first rows, not the base's."""
+    say("topk two pitches", dtype)
+    A, Lb = api(), L()
+    n, k, dim = 65536, 8, 16 if dtype == torch.uint8 else 4
+    g = np.random.default_rng(4)
+    buf = g.integers(0, 250 if dtype == torch.uint8 else 30, (2 * n, dim)).astype(
+        np.uint8 if dtype == torch.uint8 else np.float32)
+    t = to_dev(buf)
+    Q = A.Vectors(t[:n], Lb.U8 if dtype == torch.uint8 else Lb.F32, Lb.L2SQ, dim)
+    B = A.Vectors(t.view(n, 2 * dim), Q.dtype, Lb.L2SQ, dim)
+    rows = np.unique(np.concatenate([np.arange(40), g.choice(n, 60, replace=False), [n - 1]]))
+    rid, rd = orc.topk(orc.Vectors.from_array(buf[:n], orc.L2SQ),
+                       orc.Vectors.from_array(np.ascontiguousarray(buf[::2]), orc.L2SQ), k, q_rows=rows)
+    ids, d = A.topk(Q, B, k)
+    assert np.array_equal(host(ids)[rows], rid)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
