@@ -48,10 +48,14 @@ struct WideArgs {
 
 // ---- f32 rows as f16 ------------------------------------------------------
 // Scale: the power of two that takes the longest row to at most 2^8, so that
-// components and products are far from f16's and f32's limits.
+// components and products are far from f16's and f32's limits.  A squared length
+// past f32's range leaves no such power: other rows may then overflow f16, whose
+// products say nothing, and every row is left to the list kernel.
+__device__ __forceinline__ bool wide_has_scale(const float *len) { return fmaxf(len[0], len[1]) < 1e30f; }
+
 __device__ __forceinline__ float wide_scale(const float *len) {
     const float m = fmaxf(len[0], len[1]);
-    if (!(m > 0.0f) || !(m < 1e30f)) return 1.0f;
+    if (!(m > 0.0f) || !wide_has_scale(len)) return 1.0f;
     int e;
     frexpf(m, &e);   // m <= 2^e
     return ldexpf(1.0f, min(max(8 - e, -90), 90));
@@ -347,7 +351,7 @@ __global__ void __launch_bounds__(64) wide_finish_kernel(WideArgs A, const uint8
     const int64_t row = A.row0 + lr;
     const int n = uni(A.cnt[lr]);
     const int64_t avail = a.nb - (a.exclude_self ? 1 : 0);
-    const bool bad = n > A.cap || n < (int)min<int64_t>(a.k, avail);
+    const bool bad = n > A.cap || n < (int)min<int64_t>(a.k, avail) || !wide_has_scale(A.len);
     if (lane == 0) {
         redo[1 + row] = bad;
         if (bad) redo[0] = 1;

@@ -86,3 +86,21 @@ def test_topk_one_buffer_two_pitches(dtype):
     ids, d = A.topk(Q, B, k)
     assert np.array_equal(host(ids)[rows], rid)
     assert np.array_equal(host(d)[rows].astype(np.float64), rd)
+
+
+def test_topk_rows_past_the_screen_scale():
+    """f32 rows whose components overflow f16, beside one row whose squared
+    length overflows f32, so that no power of two brings all into f16's range:
+    the other rows' neighbours are those of the f32 distances (odd multiples of
+    2^17, whose squared differences sum exactly)."""
+    say("topk past the screen's scale")
+    A = api()
+    g = np.random.default_rng(3)
+    n, dim, k = 33000, 9, 8
+    x = ((2 * g.integers(-4, 4, (n, dim)) + 1) * 2.0 ** 17).astype(np.float32)
+    x[n // 2] = 1e20
+    rows = np.setdiff1d(np.unique(np.concatenate([np.arange(40), g.choice(n, 80, replace=False)])), [n // 2])
+    rid, rd = orc.knn_graph(orc.Vectors.from_array(x, orc.L2SQ), k, rows=rows)
+    ids, d = A.build_knn(gpu_vectors(x, orc.L2SQ), k)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
+    assert np.array_equal(host(ids)[rows], rid)
