@@ -659,6 +659,7 @@ bool topk_use_wide(const onng_vectors *Q, int64_t nb, int32_t k) {
 struct BoundPlan {
     bool use = false;
     int rw = 0;                  // row waves per block: 1, 4 or 8
+    int64_t chunk = 0;           // query rows per launch
     int ns_log2 = 0, group_tiles = 0, quads = 0, groups = 0, cap = 0;
     int splits[2] = {1, 1}, per_split[2] = {0, 0};   // bound, filter
     size_t lds[2] = {0, 0};
@@ -690,8 +691,12 @@ BoundPlan topk_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k) {
     int want_groups = 512;
     while (want_groups < 8 * rank) want_groups *= 2;
     want_groups = std::min(want_groups, 2048);
+    // Query rows in equal chunks, so that candidates and group minima (at most
+    // 1024 and 2048 per row where there is more than one chunk) stay within 1 GiB.
     const int bm = P.rw * 16;
-    const int64_t row_blocks = (Q->n + bm - 1) / bm;
+    const int64_t chunks = (Q->n + BOUND_CHUNK - 1) / BOUND_CHUNK;
+    const int64_t row_blocks = ((Q->n + chunks - 1) / chunks + bm - 1) / bm;
+    P.chunk = row_blocks * bm;
     P.group_tiles = 1;
     while (tiles / P.group_tiles * 16 * cw > want_groups) P.group_tiles *= 2;
     // few row blocks: groups of fewer tiles, the minima of four lanes together,
@@ -794,11 +799,12 @@ size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand
     if (sp > 1) c.take<uint64_t>((size_t)Q->n * sp * k);
     const BoundPlan bp = topk_bound_plan(Q, nb, k);
     if (bp.use) {
-        c.take<uint32_t>((size_t)Q->n * bp.groups);
-        c.take<uint32_t>(Q->n);
-        c.take<int32_t>(Q->n);
+        const int64_t rows = std::min(Q->n, bp.chunk);
+        c.take<uint32_t>((size_t)rows * bp.groups);
+        c.take<uint32_t>(rows);
+        c.take<int32_t>(rows);
         c.take<int32_t>(Q->n + 1);
-        c.take<uint64_t>((size_t)Q->n * bp.cap);
+        c.take<uint64_t>((size_t)rows * bp.cap);
     }
     return c.size() + 256;
 }
@@ -852,11 +858,12 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     const WidePlan wp = wide || wide_f32 ? wide_bound_plan(Q, nb, k) : WidePlan();
     const WideBufs wb = carve_wide(c, Q, nb, wp);
     if (bp.use) {
-        mins = c.take<uint32_t>((size_t)Q->n * bp.groups);
-        tau = c.take<uint32_t>(Q->n);
-        cnt = c.take<int32_t>(Q->n);
+        const int64_t rows = std::min(Q->n, bp.chunk);
+        mins = c.take<uint32_t>((size_t)rows * bp.groups);
+        tau = c.take<uint32_t>(rows);
+        cnt = c.take<int32_t>(rows);
         redo = c.take<int32_t>(Q->n + 1);
-        bcand = c.take<uint64_t>((size_t)Q->n * bp.cap);
+        bcand = c.take<uint64_t>((size_t)rows * bp.cap);
     }
     auto norms = [&](const void *x, int64_t pitch, int64_t n, void *out) {
         if (n == 0) return;
@@ -962,20 +969,24 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
         auto fn_of = u8 ? topk_bound_fn_u8 : Q->metric == ONNG_L2SQ ? topk_bound_fn_l2 : topk_bound_fn_cosine;
         const int bm = bp.rw * 16;
         const int rank = k + (exclude_self ? 1 : 0);
-        for (int m = 0; m < 2; m++) {
-            const void *fn = fn_of(nch_for(Q->dtype, Q->dim), bp.rw, m == 0);
-            ONNG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bp.lds[m]));
-            ba.t.tiles_per_split = bp.per_split[m];
-            void *bargs[] = {&ba};
-            ONNG_HIP(hipLaunchKernel(fn, dim3((unsigned)((Q->n + bm - 1) / bm), (unsigned)bp.splits[m]),
-                                     dim3((unsigned)bound_threads(bp.rw)), bargs, bp.lds[m], st));
-            // (u8: the bits of the largest distance, dim * 255^2, 25 of them at 512
-            // components; f32 bounds need no more than 16 bits past the exponent's first)
-            if (m == 0)
-                launch_bound_select(mins, Q->n, bp.groups, rank, u8 ? 31 - __builtin_clz(Q->dim * 65025u) : 31,
-                                    u8 ? 0 : 8, tau, cnt, redo, st);
+        for (ba.row_first = 0; ba.row_first < Q->n; ba.row_first += bp.chunk) {
+            const int64_t rows = std::min(bp.chunk, Q->n - ba.row_first);
+            ba.t.nq = ba.row_first + rows;
+            for (int m = 0; m < 2; m++) {
+                const void *fn = fn_of(nch_for(Q->dtype, Q->dim), bp.rw, m == 0);
+                ONNG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bp.lds[m]));
+                ba.t.tiles_per_split = bp.per_split[m];
+                void *bargs[] = {&ba};
+                ONNG_HIP(hipLaunchKernel(fn, dim3((unsigned)((rows + bm - 1) / bm), (unsigned)bp.splits[m]),
+                                         dim3((unsigned)bound_threads(bp.rw)), bargs, bp.lds[m], st));
+                // (u8: the bits of the largest distance, dim * 255^2, 25 of them at 512
+                // components; f32 bounds need no more than 16 bits past the exponent's first)
+                if (m == 0)
+                    launch_bound_select(mins, rows, bp.groups, rank, u8 ? 31 - __builtin_clz(Q->dim * 65025u) : 31,
+                                        u8 ? 0 : 8, tau, cnt, ba.row_first == 0 ? redo : nullptr, st);
+            }
+            launch_bound_sort(u8, bcand, bp.cap, cnt, rows, k, ids, dists, redo, ba.row_first, st);
         }
-        launch_bound_sort(u8, bcand, bp.cap, cnt, Q->n, k, ids, dists, redo, 0, st);
         // rows that overflowed or fell short, if any
         a.only = redo;
     }

@@ -29,17 +29,19 @@ namespace onng {
 namespace topk_detail {
 
 constexpr int BOUND_QUEUE = 192;          // candidates a wave holds before it places them
+constexpr int64_t BOUND_CHUNK = 65536;    // query rows whose candidates are held at a time
 
 struct BoundArgs {
-    TopkArgs t;
+    TopkArgs t;               // nq: end of the chunk's query rows
+    int64_t row_first;        // first query row of the chunk; the buffers below are the chunk's
     int32_t ns_log2;          // sampled rows (bound)
     int32_t group_tiles;      // tiles a lane's minimum runs over (bound)
     int32_t quads;            // the minima of four lanes make one group (bound)
     int32_t groups;           // minima per query row
-    uint32_t *mins;           // [nq][groups]
-    const uint32_t *tau;      // [nq] largest distance that passes (filter)
-    int32_t *cnt;             // [nq] candidates found (may exceed cap)
-    uint64_t *cand;           // [nq][cap]
+    uint32_t *mins;           // [rows][groups]
+    const uint32_t *tau;      // [rows] largest distance that passes (filter)
+    int32_t *cnt;             // [rows] candidates found (may exceed cap)
+    uint64_t *cand;           // [rows][cap]
     int32_t cap;
 };
 
@@ -70,7 +72,8 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
     const int lane = lane_id();
     const int wv = uni(threadIdx.x / WAVE);
     const int rw = RW == 1 ? 0 : wv, cw = RW == 1 ? wv : 0;
-    const int64_t row0 = (int64_t)blockIdx.x * bm;
+    const int64_t lrow0 = (int64_t)blockIdx.x * bm;   // within the chunk
+    const int64_t row0 = A.row_first + lrow0;
     constexpr bool norms = U8 || MT == ONNG_L2SQ;
 
     // LDS: two of [B tile][norms BN][ids BN] (the next tile is stored while
@@ -109,14 +112,14 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
     float qnf[4] = {0, 0, 0, 0};
     uint32_t tau[4] = {0, 0, 0, 0};
     bool rok[4];
-    const int64_t crow0 = row0 + rw * 16 + 4 * kg;
+    const int64_t lcrow0 = lrow0 + rw * 16 + 4 * kg, crow0 = A.row_first + lcrow0;
 #pragma unroll
     for (int r = 0; r < 4; r++) {
         rok[r] = crow0 + r < a.nq;
         if (rok[r]) {
             if constexpr (U8) qn8[r] = reinterpret_cast<const int32_t *>(a.qn)[crow0 + r];
             else if constexpr (MT == ONNG_L2SQ) qnf[r] = reinterpret_cast<const float *>(a.qn)[crow0 + r];
-            if (!BOUND) tau[r] = A.tau[crow0 + r];
+            if (!BOUND) tau[r] = A.tau[lcrow0 + r];
         }
     }
     const bool live = row0 + rw * 16 < a.nq;
@@ -200,14 +203,14 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
         wave_sync();
         if (lane < 16) {
             const int n = q_cnt[lane];
-            if (n) q_cnt[lane] = atomicAdd(&A.cnt[row0 + rw * 16 + lane], n);
+            if (n) q_cnt[lane] = atomicAdd(&A.cnt[lrow0 + rw * 16 + lane], n);
         }
         wave_sync();
 #pragma unroll 1
         for (int e = lane; e < qn_held; e += WAVE) {
             const int r = q_row[e];
             const int slot = q_cnt[r] + q_num[e];
-            if (slot < A.cap) A.cand[(row0 + rw * 16 + r) * A.cap + slot] = q_key[e];
+            if (slot < A.cap) A.cand[(lrow0 + rw * 16 + r) * A.cap + slot] = q_key[e];
         }
         wave_sync();
         qn_held = 0;
@@ -307,7 +310,7 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
                     best[r] = min(best[r], dpp<DPP_QP_2301>(best[r]));
                 }
                 if (rok[r] && (!A.quads || (lane & 3) == 0))
-                    A.mins[(crow0 + r) * A.groups + (A.quads ? at / 4 : at)] = best[r];
+                    A.mins[(lcrow0 + r) * A.groups + (A.quads ? at / 4 : at)] = best[r];
                 best[r] = ~0u;
             }
         }

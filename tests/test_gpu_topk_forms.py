@@ -104,3 +104,25 @@ def test_topk_rows_past_the_screen_scale():
     ids, d = A.build_knn(gpu_vectors(x, orc.L2SQ), k)
     assert np.array_equal(host(d)[rows].astype(np.float64), rd)
     assert np.array_equal(host(ids)[rows], rid)
+
+
+@pytest.mark.parametrize("kind,nq", [("u8", 66000), ("f32l2", 65537)])
+def test_topk_query_chunks(kind, nq):
+    """More query rows of over 128 components than one pass holds candidates
+    for: rows around the cut, with a candidate list and self exclusion, some of
+    them redone (all components equal, so tied with many)."""
+    say("topk query chunks", kind, nq)
+    A = api()
+    g = np.random.default_rng(nq)
+    dim, k = 130, 8
+    x = g.integers(0, 250 if kind == "u8" else 5, (nq, dim)).astype(np.uint8 if kind == "u8" else np.float32)
+    x[g.permutation(nq)[:nq // 2]] = 2
+    cand = g.permutation(nq)[:1500].astype(np.int32)
+    cut = -(-(nq // 2) // 128) * 128
+    rows = np.unique(np.concatenate([np.arange(20), np.arange(cut - 140, cut + 140), [nq - 1], cand[:60]]))
+    bv = orc.Vectors.from_array(x, orc.L2SQ)
+    rid, rd = orc.topk(bv, bv, k, q_rows=rows, cand=cand, exclude_self=True)
+    V = gpu_vectors(x, orc.L2SQ)
+    ids, d = A.topk(V, V, k, cand=to_dev(cand), exclude_self=True)
+    assert np.array_equal(host(ids)[rows], rid)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
