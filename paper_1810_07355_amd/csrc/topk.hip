@@ -756,7 +756,10 @@ void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cn
 
 }  // namespace topk_detail
 
-static WideBufs carve_wide(Carver &c, const onng_vectors *Q, int64_t nb, const WidePlan &P) {
+// Converted rows lie where the list kernel behind the passes, which starts when
+// they are done, keeps its own: bh and qh are its bf16 copies of base and queries
+// (f32), qh its candidate slots (u8; the base's rows have a place of their own).
+static WideBufs carve_wide(Carver &c, const onng_vectors *Q, int64_t nb, const WidePlan &P, void *bh, void *qh) {
     WideBufs w{};
     if (!P.use) return w;
     const int64_t rows = std::min<int64_t>(Q->n, P.chunk);
@@ -765,9 +768,12 @@ static WideBufs carve_wide(Carver &c, const onng_vectors *Q, int64_t nb, const W
     w.cnt = c.take<int32_t>(rows);
     w.cand = c.take<uint64_t>((size_t)rows * P.cap);
     w.redo = c.take<int32_t>(Q->n + 1);
-    w.bh = c.take<uint8_t>((size_t)nb * P.nch * 64);
-    w.qh = c.take<uint8_t>((size_t)Q->n * P.nch * 64);
-    if (Q->dtype == ONNG_F32) {
+    static_assert(FW_NCH * 64 >= 4 * 64 && WIDE_CB * 8 >= 2 * 64, "room for a converted row");
+    w.qh = static_cast<uint8_t *>(qh);
+    if (Q->dtype == ONNG_U8) {
+        w.bh = c.take<uint8_t>((size_t)nb * P.nch * 64);
+    } else {
+        w.bh = static_cast<uint8_t *>(bh);
         w.side = c.take<float>(nb);
         w.len = c.take<float>(2);
     }
@@ -783,11 +789,11 @@ size_t topk_ws_size(const onng_vectors *Q, const onng_vectors *B, int64_t n_cand
     if (topk_use_wide(Q, nb, k)) {
         c.take<uint64_t>((size_t)Q->n * topk_kcap(k));
         c.take<uint64_t>((size_t)Q->n * WIDE_CB);
-        carve_wide(c, Q, nb, wide_bound_plan(Q, nb, k));
+        carve_wide(c, Q, nb, wide_bound_plan(Q, nb, k), nullptr, nullptr);
         return c.size() + 256;
     }
     if (topk_use_wide_f32(Q, nb, k)) {
-        carve_wide(c, Q, nb, wide_bound_plan(Q, nb, k));
+        carve_wide(c, Q, nb, wide_bound_plan(Q, nb, k), nullptr, nullptr);
         c.take<uint8_t>((size_t)nb * FW_NCH * 64);
         c.take<uint8_t>((size_t)Q->n * FW_NCH * 64);
         c.take<uint32_t>(1);
@@ -856,7 +862,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     int32_t *cnt = nullptr, *redo = nullptr;
     uint64_t *bcand = nullptr;
     const WidePlan wp = wide || wide_f32 ? wide_bound_plan(Q, nb, k) : WidePlan();
-    const WideBufs wb = carve_wide(c, Q, nb, wp);
+    const WideBufs wb = carve_wide(c, Q, nb, wp, fbh, wide ? static_cast<void *>(gcand) : fqh);
     if (bp.use) {
         const int64_t rows = std::min(Q->n, bp.chunk);
         mins = c.take<uint32_t>((size_t)rows * bp.groups);

@@ -23,3 +23,19 @@ def test_general_passes(dtype, n, k):
     stay within 1 GiB (and a few words per row)."""
     lists = 8 * n
     assert need(n, 200, dtype, k) <= lists + (1 << 30) + 16 * n + 4096
+
+
+@pytest.mark.parametrize("dtype,n,nb", [(L.F32, 10_000_000, None), (L.F32, 5_000_000, 200_000), (L.U8, 10_000_000, 400_000),
+                                        (L.U8, 400_000, None)])
+@pytest.mark.parametrize("k", [10, 100])
+def test_wide_passes(dtype, n, nb, k):
+    """Many rows of 96 components: the passes' converted queries (f32: their
+    converted base as well) share memory with what only the list kernel behind
+    them uses, so the size is that kernel's own (norms, lists, 256 candidate keys
+    or 128 ids per row; f32: two copies of the rows), and for 32,768 query rows
+    at most 2048 candidates and group minima, and 128 bytes per u8 base row."""
+    b = nb or n
+    lists = 4 * (n + b) + n * ((k + 7) // 8 * 8) * 8
+    lists += n * 256 * 8 if dtype == L.U8 else 256 * (n + b) + n * 128 * 4
+    extra = 32768 * (2048 * 12 + 8) + 4 * n + (128 * b if dtype == L.U8 else 4 * b)
+    assert need(n, 96, dtype, k, nb) <= lists + extra + 8192
