@@ -222,15 +222,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) t
     constexpr uint8_t Q_SELF = 255;   // the row itself, left out
     auto drain = [&]() {
         q_cnt[lane] = 0;
+        const bool by_place = a.exclude_self && !a.b_ids;
+        if (a.exclude_self && a.b_ids) {
+            // candidate ids, in a loop of their own: a load in the next one would wait
+            // there, in every call, for the tile that is being fetched (u8 70,000 rows,
+            // k 100: 2501 against 2491 us)
+#pragma unroll 1
+            for (int e = lane; e < held; e += WAVE)
+                if ((int64_t)a.b_ids[(uint32_t)q_key[e] & 0x7FFFFFFFu] == A.row0 + lrow0 + q_row[e]) q_row[e] = Q_SELF;
+        }
         wave_sync();
 #pragma unroll 1
         for (int e = lane; e < held; e += WAVE) {
             const int r = q_row[e];
-            bool self = false;
-            if (a.exclude_self) {   // the row's own id, not its place in a candidate list
-                const uint32_t col = (uint32_t)q_key[e] & 0x7FFFFFFFu;
-                self = (a.b_ids ? (int64_t)a.b_ids[col] : (int64_t)col) == A.row0 + lrow0 + r;
-            }
+            const bool self = by_place ? (int64_t)((uint32_t)q_key[e] & 0x7FFFFFFFu) == A.row0 + lrow0 + r : r == Q_SELF;
             if (self) q_row[e] = Q_SELF;
             else q_num[e] = (uint8_t)atomicAdd(&q_cnt[r], 1);
         }
