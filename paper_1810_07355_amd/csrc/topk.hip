@@ -534,21 +534,26 @@ __global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins,
 // row itself and a candidate list may hold more), is left to the general kernel
 // (redo[1 + row], and redo[0] for any).  Up to 64 candidates sort in registers,
 // more by a bitonic network in LDS; with few rows the block has four waves.
+// drop_own: candidates with the row's own id do not count.
 template <bool U8>
 __global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, int cap, const int32_t *cnt,
-                                                         int k, int32_t *out_ids, void *out_d,
+                                                         int k, int drop_own, int32_t *out_ids, void *out_d,
                                                          int32_t *redo, int64_t row0) {
     extern __shared__ __attribute__((aligned(16))) uint64_t sk[];
     const int64_t row = blockIdx.x;
     const int tid = threadIdx.x, nt = blockDim.x;
     const int n = uni(cnt[row]);
-    const bool bad = n > cap || n < k;
+    const uint64_t *src = cand + row * cap;
+    auto is_own = [&](uint64_t key) { return drop_own && (int64_t)(uint32_t)key == row0 + row; };
+    int own = 0;
+    if (drop_own && n <= cap)
+        for (int i0 = 0; i0 < n; i0 += nt) own += __syncthreads_count(i0 + tid < n && is_own(src[i0 + tid]));
+    const bool bad = n > cap || n - own < k;
     if (tid == 0) redo[1 + row0 + row] = bad;
     if (bad) {
         if (tid == 0) redo[0] = 1;
         return;
     }
-    const uint64_t *src = cand + row * cap;
     auto put = [&](int i, uint64_t key) {
         const int64_t at = (row0 + row) * k + i;
         out_ids[at] = (int32_t)(uint32_t)key;
@@ -558,12 +563,13 @@ __global__ void __launch_bounds__(256) bound_sort_kernel(const uint64_t *cand, i
     if (n <= WAVE) {
         if (tid >= WAVE) return;
         uint64_t key = tid < n ? src[tid] : KEY_MAX;
+        if (is_own(key)) key = KEY_MAX;
         key = wave_sort(key, pow2_at_least(n));
         if (tid < k) put(tid, key);
         return;
     }
     const int w = pow2_at_least(n);
-    for (int i = tid; i < w; i += nt) sk[i] = i < n ? src[i] : KEY_MAX;
+    for (int i = tid; i < w; i += nt) sk[i] = i < n && !is_own(src[i]) ? src[i] : KEY_MAX;
     for (int size = 2; size <= w; size <<= 1)
         for (int d = size >> 1; d > 0; d >>= 1) {
             __syncthreads();
@@ -748,10 +754,10 @@ void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank,
 }
 
 void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cnt, int64_t nq, int k,
-                       int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st) {
+                       bool drop_own, int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st) {
     auto fn = u8 ? bound_sort_kernel<true> : bound_sort_kernel<false>;
     hipLaunchKernelGGL(fn, dim3((unsigned)nq), dim3(nq < 1024 ? 256 : WAVE), (size_t)cap * 8, st, cand, cap,
-                       cnt, k, ids, dists, redo, row0);
+                       cnt, k, (int)drop_own, ids, dists, redo, row0);
 }
 
 }  // namespace topk_detail
@@ -991,7 +997,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
                     launch_bound_select(mins, rows, bp.groups, rank, u8 ? 31 - __builtin_clz(Q->dim * 65025u) : 31,
                                         u8 ? 0 : 8, tau, cnt, ba.row_first == 0 ? redo : nullptr, st);
             }
-            launch_bound_sort(u8, bcand, bp.cap, cnt, rows, k, ids, dists, redo, ba.row_first, st);
+            launch_bound_sort(u8, bcand, bp.cap, cnt, rows, k, false, ids, dists, redo, ba.row_first, st);
         }
         // rows that overflowed or fell short, if any
         a.only = redo;

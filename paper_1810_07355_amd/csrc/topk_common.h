@@ -225,12 +225,12 @@ onng_status launch_wide_bound(const TopkArgs &a, const onng_vectors *Q, bool sam
 
 // Per row an upper bound of the rank-th smallest of its group minima, its
 // counter cleared (and *clear, when given); per row its candidates sorted and
-// the k first written at row0 + row, or redo[1 + row0 + row] and redo[0] set
+// the k first (drop_own: without the row's own id) written at row0 + row, or redo[1 + row0 + row] and redo[0] set
 // (topk.hip).
 void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int top, int low,
                          uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st);
 void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cnt, int64_t nq, int k,
-                       int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st);
+                       bool drop_own, int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st);
 
 }  // namespace topk_detail
 }  // namespace onng

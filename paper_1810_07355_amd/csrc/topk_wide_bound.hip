@@ -44,6 +44,7 @@ struct WideArgs {
     uint64_t *cand;
     int32_t cap;
     const float *len;        // f32: largest |y| of the base, of the queries
+    int32_t drop_own;        // f32: the row's own id is left out at the end
 };
 
 // ---- f32 rows as f16 ------------------------------------------------------
@@ -222,21 +223,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) t
     constexpr uint8_t Q_SELF = 255;   // the row itself, left out
     auto drain = [&]() {
         q_cnt[lane] = 0;
-        const bool by_place = a.exclude_self && !a.b_ids;
-        if (a.exclude_self && a.b_ids) {
-            // candidate ids, in a loop of their own: a load in the next one would wait
-            // there, in every call, for the tile that is being fetched (u8 70,000 rows,
-            // k 100: 2501 against 2491 us)
-#pragma unroll 1
-            for (int e = lane; e < held; e += WAVE)
-                if ((int64_t)a.b_ids[(uint32_t)q_key[e] & 0x7FFFFFFFu] == A.row0 + lrow0 + q_row[e]) q_row[e] = Q_SELF;
-        }
         wave_sync();
 #pragma unroll 1
         for (int e = lane; e < held; e += WAVE) {
             const int r = q_row[e];
-            const bool self = by_place ? (int64_t)((uint32_t)q_key[e] & 0x7FFFFFFFu) == A.row0 + lrow0 + r : r == Q_SELF;
-            if (self) q_row[e] = Q_SELF;
+            if (a.exclude_self && (int64_t)((uint32_t)q_key[e] & 0x7FFFFFFFu) == A.row0 + lrow0 + r) q_row[e] = Q_SELF;
             else q_num[e] = (uint8_t)atomicAdd(&q_cnt[r], 1);
         }
         wave_sync();
@@ -355,17 +346,30 @@ __global__ void __launch_bounds__(64) wide_finish_kernel(WideArgs A, const uint8
     const int lr = blockIdx.x;
     const int64_t row = A.row0 + lr;
     const int n = uni(A.cnt[lr]);
-    const int64_t avail = a.nb - (a.exclude_self ? 1 : 0);
-    const bool bad = n > A.cap || n < (int)min<int64_t>(a.k, avail) || !wide_has_scale(A.len);
+    const int64_t avail = a.nb - (a.exclude_self || A.drop_own ? 1 : 0);
+    const int need = (int)min<int64_t>(a.k, avail);
+    bool bad = n > A.cap || n < need || !wide_has_scale(A.len);
+    const uint64_t *src = A.cand + (int64_t)lr * A.cap;
+    uint64_t key[VPL];
+    if (!bad) {
+#pragma unroll
+        for (int i = 0; i < VPL; i++) key[i] = i * WAVE + lane < n ? src[i * WAVE + lane] : KEY_MAX;
+        if (A.drop_own) {
+            int own = 0;
+#pragma unroll
+            for (int i = 0; i < VPL; i++) {
+                const bool is = i * WAVE + lane < n && (int64_t)a.b_ids[(uint32_t)key[i]] == row;
+                if (is) key[i] = KEY_MAX;
+                own += __popcll(ballot(is));
+            }
+            bad = n - own < need;
+        }
+    }
     if (lane == 0) {
         redo[1 + row] = bad;
         if (bad) redo[0] = 1;
     }
     if (bad) return;
-    const uint64_t *src = A.cand + (int64_t)lr * A.cap;
-    uint64_t key[VPL];
-#pragma unroll
-    for (int i = 0; i < VPL; i++) key[i] = i * WAVE + lane < n ? src[i * WAVE + lane] : KEY_MAX;
     const float *qf = reinterpret_cast<const float *>(q + row * q_pitch);
     for (int c = lane; c < 128; c += WAVE) qs[c] = c < a.dim ? qf[c] : 0.0f;
     // the k-th smallest of ~ord(D)
@@ -385,7 +389,7 @@ __global__ void __launch_bounds__(64) wide_finish_kernel(WideArgs A, const uint8
     int ns = 0;
 #pragma unroll
     for (int i = 0; i < VPL; i++) {
-        const bool in = i * WAVE + lane < n && !(unord_f32(~(uint32_t)(key[i] >> 32)) < dmin);
+        const bool in = key[i] != KEY_MAX && !(unord_f32(~(uint32_t)(key[i] >> 32)) < dmin);
         const uint64_t bal = ballot(in);
         if (in) keys[ns + mbcnt(bal)] = key[i];
         ns += __popcll(bal);
@@ -585,6 +589,13 @@ onng_status launch_wide_bound(const TopkArgs &t, const onng_vectors *Q, bool sam
     A.cap = P.cap;
     A.len = w.len;
     const int rank = t.k + (t.exclude_self ? 1 : 0);
+    // Self exclusion: the passes leave out the column that is the row's place, which
+    // in a candidate list is not its id.  There the own id goes at the end, from the
+    // few candidates (read and compared where the passes queue them it cost a table
+    // of 70,000 u8 rows, without a list, 25 of 2476 us).
+    const bool drop_own = t.exclude_self && t.b_ids;
+    if (drop_own) A.t.exclude_self = 0;
+    A.drop_own = drop_own;
     for (int64_t r0 = 0; r0 < t.nq; r0 += P.chunk) {
         A.row0 = r0;
         A.rows = (int32_t)std::min<int64_t>(P.chunk, t.nq - r0);
@@ -604,7 +615,7 @@ onng_status launch_wide_bound(const TopkArgs &t, const onng_vectors *Q, bool sam
                                     r0 == 0 ? w.redo : nullptr, st);
         }
         if (u8) {
-            launch_bound_sort(true, w.cand, P.cap, w.cnt, A.rows, t.k, t.out_ids, t.out_d, w.redo, r0, st);
+            launch_bound_sort(true, w.cand, P.cap, w.cnt, A.rows, t.k, drop_own, t.out_ids, t.out_d, w.redo, r0, st);
         } else {
             const void *ff = cosine ? finish_fn<ONNG_COSINE>(P.cap) : finish_fn<ONNG_L2SQ>(P.cap);
             const size_t fl = (size_t)P.cap * 8 + WAVE * FIN_PITCH + 512;
