@@ -497,12 +497,18 @@ __global__ void __launch_bounds__(256) merge_parts_kernel(const uint64_t *part, 
 
 // ---- between and after the passes of topk_bound.h ----
 // One wave per row: an upper bound of the rank-th smallest of its group minima
-// (the distances' low bits below `low` rounded up), and its counter cleared.
-// Bits are settled from `top` down by counting the minima at or below each
-// trial value, VPL minima per lane in registers.
+// (the distances' low bits below `low` rounded up; `past` is added), and its
+// counter cleared.  Bits are settled from `top` down by counting the minima at or
+// below each trial value, VPL minima per lane in registers.  Where more than
+// `most` minima are within the bound (equal distances; each minimum stands for
+// nb / sampled rows), the candidates would overflow: the counter starts past the
+// buffer, and with `none` for a bound nothing passes.  All rows equal, us: u8
+// 70,000 x 128, k 100: 29,140 -> 10,100, f32 10,000 x 10,000 x 100, k 8: 970 -> 467
+// (9,100 and 425 with the list kernel alone).
 template <int VPL>
 __global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins, int64_t nq, int groups,
-                                                           int rank, int top, int low, uint32_t *tau,
+                                                           int rank, int most, int top, int low, int cap,
+                                                           uint32_t past, uint32_t none, uint32_t *tau,
                                                            int32_t *cnt, int32_t *clear) {
     const int64_t row = (int64_t)blockIdx.x * 4 + uni(threadIdx.x / WAVE);
     const int lane = lane_id();
@@ -515,16 +521,18 @@ __global__ void __launch_bounds__(256) bound_select_kernel(const uint32_t *mins,
         x[i] = g < groups ? mins[row * groups + g] : ~0u;
     }
     uint32_t v = 0;
+    int within = groups;   // minima within the bound: those of the last trial that held rank
     for (int bit = top; bit >= low; bit--) {
         const uint32_t trial = v | ((1u << bit) - 1u);
         int c = 0;
 #pragma unroll
         for (int i = 0; i < VPL; i++) c += __popcll(ballot(x[i] <= trial));
         if (c < rank) v |= 1u << bit;
+        else within = c;
     }
     if (lane == 0) {
-        tau[row] = v | ((1u << low) - 1u);
-        cnt[row] = 0;
+        tau[row] = within > most ? none : (v | ((1u << low) - 1u)) + past;
+        cnt[row] = within > most ? cap + 1 : 0;
     }
 }
 
@@ -745,12 +753,12 @@ BoundPlan topk_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k) {
 
 namespace topk_detail {
 
-void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int top, int low,
-                         uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st) {
+void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int most, int top, int low,
+                         int cap, uint32_t past, uint32_t none, uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st) {
     auto sel = groups <= 512 ? bound_select_kernel<8> : groups <= 1024 ? bound_select_kernel<16>
                                                                        : bound_select_kernel<32>;
-    hipLaunchKernelGGL(sel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, mins, nq, groups, rank, top,
-                       low, tau, cnt, clear);
+    hipLaunchKernelGGL(sel, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, st, mins, nq, groups, rank, most,
+                       top, low, cap, past, none, tau, cnt, clear);
 }
 
 void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cnt, int64_t nq, int k,
@@ -994,8 +1002,9 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
                 // (u8: the bits of the largest distance, dim * 255^2, 25 of them at 512
                 // components; f32 bounds need no more than 16 bits past the exponent's first)
                 if (m == 0)
-                    launch_bound_select(mins, rows, bp.groups, rank, u8 ? 31 - __builtin_clz(Q->dim * 65025u) : 31,
-                                        u8 ? 0 : 8, tau, cnt, ba.row_first == 0 ? redo : nullptr, st);
+                    launch_bound_select(mins, rows, bp.groups, rank, bound_most(bp.cap, bp.ns_log2, nb),
+                                        u8 ? 31 - __builtin_clz(Q->dim * 65025u) : 31, u8 ? 0 : 8, bp.cap, 1, 0, tau,
+                                        cnt, ba.row_first == 0 ? redo : nullptr, st);
             }
             launch_bound_sort(u8, bcand, bp.cap, cnt, rows, k, false, ids, dists, redo, ba.row_first, st);
         }

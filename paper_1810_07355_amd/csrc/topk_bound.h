@@ -39,7 +39,7 @@ struct BoundArgs {
     int32_t quads;            // the minima of four lanes make one group (bound)
     int32_t groups;           // minima per query row
     uint32_t *mins;           // [rows][groups]
-    const uint32_t *tau;      // [rows] largest distance that passes (filter)
+    const uint32_t *tau;      // [rows] distances below it pass (filter)
     int32_t *cnt;             // [rows] candidates found (may exceed cap)
     uint64_t *cand;           // [rows][cap]
     int32_t cap;
@@ -123,6 +123,13 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
         }
     }
     const bool live = row0 + rw * 16 < a.nq;
+    bool any_passes = false;   // of the block's rows, the same in every wave
+    if constexpr (!BOUND) {
+        uint32_t t = 0;
+        for (int i = lane; i < bm; i += WAVE)
+            if (row0 + i < a.nq) t |= A.tau[lrow0 + i];
+        any_passes = ballot(t != 0) != 0;
+    }
 
     const int ntiles = BOUND ? (1 << A.ns_log2) / BN : (int)((a.nb + BN - 1) / BN);
     const int t_beg = blockIdx.y * a.tiles_per_split;
@@ -224,6 +231,8 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
     // the query operands are here: without this the loop's first product waits
     // for every load in flight, the next tile's among them, on each tile
     __builtin_amdgcn_s_waitcnt(0);
+    // (filter: a block none of whose rows lets anything pass has nothing to do)
+    if (!BOUND && !any_passes) return;
     for (int t = t_beg; t < t_end; t++) {
         uint8_t *const btile = reinterpret_cast<uint8_t *>(smem) + ((t - t_beg) & 1) * buf_bytes;
         uint32_t *const t_norm = reinterpret_cast<uint32_t *>(btile + BN * a.lds_pitch);
@@ -281,7 +290,7 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
                 else if constexpr (MT == ONNG_L2SQ) dd[r] = ord_f32(qnf[r] + bnf - 2.0f * accf[cb][r]);
                 else dd[r] = ord_f32(1.0f - accf[cb][r]);
                 if (BOUND) best[r] = min(best[r], dd[r]);
-                else hit |= ballot(dd[r] <= tau[r]);
+                else hit |= ballot(dd[r] < tau[r]);
             }
             if (BOUND || !hit) continue;
             const int64_t c = (int64_t)t * BN + col;
@@ -289,7 +298,7 @@ __global__ void __launch_bounds__(bound_threads(RW), NCH <= 8 ? (RW == 4 ? 3 : 4
             const uint32_t gid = a.b_ids ? t_gid[col] : (uint32_t)c;
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const bool in = cok && rok[r] && dd[r] <= tau[r] &&
+                const bool in = cok && rok[r] && dd[r] < tau[r] &&
                                 !(a.exclude_self && (int64_t)gid == crow0 + r);
                 const uint64_t m = ballot(in);
                 if (!m) continue;

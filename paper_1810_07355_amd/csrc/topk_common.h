@@ -223,12 +223,15 @@ WidePlan wide_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k);
 onng_status launch_wide_bound(const TopkArgs &a, const onng_vectors *Q, bool same_rows, const WidePlan &P,
                               const WideBufs &w, hipStream_t st);
 
-// Per row an upper bound of the rank-th smallest of its group minima, its
-// counter cleared (and *clear, when given); per row its candidates sorted and
+// Per row an upper bound of the rank-th smallest of its group minima plus `past`,
+// its counter cleared (and *clear, when given), or, where more than `most` minima
+// are within the bound, `none` and the counter past cap; its candidates sorted and
 // the k first (drop_own: without the row's own id) written at row0 + row, or redo[1 + row0 + row] and redo[0] set
 // (topk.hip).
-void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int top, int low,
-                         uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st);
+void launch_bound_select(const uint32_t *mins, int64_t nq, int groups, int rank, int most, int top, int low,
+                         int cap, uint32_t past, uint32_t none, uint32_t *tau, int32_t *cnt, int32_t *clear, hipStream_t st);
+// minima that stand for cap base rows
+inline int bound_most(int cap, int ns_log2, int64_t nb) { return (int)(((int64_t)cap << ns_log2) / nb); }
 void launch_bound_sort(bool u8, const uint64_t *cand, int cap, const int32_t *cnt, int64_t nq, int k,
                        bool drop_own, int32_t *ids, void *dists, int32_t *redo, int64_t row0, hipStream_t st);
 

@@ -596,6 +596,8 @@ onng_status launch_wide_bound(const TopkArgs &t, const onng_vectors *Q, bool sam
     const bool drop_own = t.exclude_self && t.b_ids;
     if (drop_own) A.t.exclude_self = 0;
     A.drop_own = drop_own;
+    // no D reaches this bound: u8 lim INT32_MAX - 1; f32 lim +inf (~ its sort key)
+    const uint32_t none = u8 ? 0u : ~0xFF800000u;
     for (int64_t r0 = 0; r0 < t.nq; r0 += P.chunk) {
         A.row0 = r0;
         A.rows = (int32_t)std::min<int64_t>(P.chunk, t.nq - r0);
@@ -611,8 +613,8 @@ onng_status launch_wide_bound(const TopkArgs &t, const onng_vectors *Q, bool sam
             ONNG_HIP(hipLaunchKernel(fn, dim3((unsigned)((A.rows + WB_ROWS - 1) / WB_ROWS), (unsigned)P.splits[m]),
                                      dim3(256), args, lds, st));
             if (bound)
-                launch_bound_select(w.mins, A.rows, P.groups, rank, 31, u8 ? 0 : 8, w.tau, w.cnt,
-                                    r0 == 0 ? w.redo : nullptr, st);
+                launch_bound_select(w.mins, A.rows, P.groups, rank, bound_most(P.cap, P.ns_log2, t.nb), 31, u8 ? 0 : 8,
+                                    P.cap, 0, none, w.tau, w.cnt, r0 == 0 ? w.redo : nullptr, st);
         }
         if (u8) {
             launch_bound_sort(true, w.cand, P.cap, w.cnt, A.rows, t.k, drop_own, t.out_ids, t.out_d, w.redo, r0, st);

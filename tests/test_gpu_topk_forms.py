@@ -126,3 +126,24 @@ def test_topk_query_chunks(kind, nq):
     ids, d = A.topk(V, V, k, cand=to_dev(cand), exclude_self=True)
     assert np.array_equal(host(ids)[rows], rid)
     assert np.array_equal(host(d)[rows].astype(np.float64), rd)
+
+
+@pytest.mark.parametrize("kind,n,dim,k,equal", [
+    ("u8", 1500, 20, 8, 1.0), ("u8", 6000, 300, 100, 0.4), ("f32l2", 20000, 33, 8, 0.5), ("f32cos", 1100, 12, 20, 1.0),
+    ("u8", 65536, 16, 20, 0.1), ("u8", 65600, 100, 100, 1.0), ("f32l2", 32768, 40, 30, 0.2), ("f32cos", 33000, 8, 10, 1.0)])
+def test_topk_many_equal_rows(kind, n, dim, k, equal):
+    """Rows of which a share are equal, so that their queries' bounds are tied
+    with far more rows than the candidate buffers hold: those are foreseen and
+    left to the list kernel, the others are not; whole numbers, so exact."""
+    say("topk equal rows", kind, n, dim, k, equal)
+    A = api()
+    g = np.random.default_rng(n + dim)
+    metric = orc.COS if kind == "f32cos" else orc.L2SQ
+    x = g.integers(0, 250 if kind == "u8" else 16, (n, dim)).astype(np.uint8 if kind == "u8" else np.float32)
+    same = g.random(n) < equal
+    x[same] = x[0]
+    rows = np.unique(np.concatenate([np.arange(60), np.arange(n - 60, n), g.choice(n, 80, replace=False)]))
+    rid, rd = orc.knn_graph(orc.Vectors.from_array(x, metric), k, rows=rows)
+    ids, d = A.build_knn(gpu_vectors(x, metric), k)
+    assert np.array_equal(host(ids)[rows], rid)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
