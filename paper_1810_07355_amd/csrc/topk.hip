@@ -218,14 +218,21 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
     constexpr int total = BN * CPR;
     const bool piped = total <= STG * (int)blockDim.x;
     uint4 stg[STG];
-    uint32_t side_g = 0;
+    uint32_t side_n = 0, side_g = 0;
     auto fetch_side = [&](int t) {
         const int64_t col = (int64_t)t * BN + threadIdx.x;
+        side_n = 0;
         side_g = 0;
-        if (threadIdx.x < BN && col < a.nb && a.b_ids) side_g = (uint32_t)a.b_ids[col];
+        if (threadIdx.x < BN && col < a.nb) {
+            if (a.bn) side_n = reinterpret_cast<const uint32_t *>(a.bn)[col];
+            if (a.b_ids) side_g = (uint32_t)a.b_ids[col];
+        }
     };
     auto put_side = [&]() {
-        if (threadIdx.x < BN && a.b_ids) t_gid[threadIdx.x] = side_g;
+        if (threadIdx.x < BN) {
+            if (a.bn) t_norm[threadIdx.x] = side_n;
+            if (a.b_ids) t_gid[threadIdx.x] = side_g;
+        }
     };
     // A thread's chunks sit at the same place in every tile; rows are read
     // with 32-bit offsets from the tile's first row.
@@ -325,7 +332,7 @@ __global__ void __launch_bounds__(256) topk_kernel(TopkArgs a) {
         }
         __syncthreads();
         if (piped && t + 1 < t_end) fetch_tile(tile_at(t + 1));
-        if (a.side_norms) {
+        if (a.side_norms && !a.bn) {
             tile_norms<U8, CPR>(btile, a.lds_pitch, blockDim.x, t_norm);
             __syncthreads();
         }
@@ -912,9 +919,13 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
                                static_cast<float *>(qn));
         brows = gathered;
     }
-    // the wide kernels read the base's norms; the others take them from the
-    // staged tiles, and cosine needs none
-    if (wide || wide_f32) norms(brows, B->pitch_bytes, nb, bn);
+    // Base norms: the wide kernels read them, and so does the list kernel where it
+    // sweeps at least 32 tiles by itself (norms from the staged tiles are 12 % of its
+    // time: 300,000 x 300 u8, k 10: 431 against 379 ms; a launch is 5 us).  The
+    // others take them from the staged tiles, and cosine needs none.
+    const bool list_norms = !wide && !wide_f32 && !bp.use && (u8 || Q->metric == ONNG_L2SQ) &&
+                            (nb + BN - 1) / BN >= 32 * sp;
+    if (wide || wide_f32 || list_norms) norms(brows, B->pitch_bytes, nb, bn);
     if (query_norms && !gathered) norms(Q->data, Q->pitch_bytes, Q->n, qn);
     ONNG_HIP(hipGetLastError());
     if (Q->n == 0) return ONNG_OK;
@@ -928,7 +939,7 @@ onng_status launch_topk(const onng_vectors *Q, const onng_vectors *B, const int3
     a.nb = nb;
     a.b_ids = cand;
     a.qn = qn;
-    a.bn = bn;
+    a.bn = wide || wide_f32 || list_norms ? bn : nullptr;
     a.dim = Q->dim;
     a.k = k;
     a.kcap = topk_kcap(k);

@@ -147,3 +147,28 @@ def test_topk_many_equal_rows(kind, n, dim, k, equal):
     ids, d = A.build_knn(gpu_vectors(x, metric), k)
     assert np.array_equal(host(ids)[rows], rid)
     assert np.array_equal(host(d)[rows].astype(np.float64), rd)
+
+
+@pytest.mark.parametrize("kind,nb,dim,k,cands", [("u8", 5000, 300, 256, False), ("u8", 5001, 150, 256, True),
+                                                 ("f32l2", 5000, 200, 132, False), ("f32l2", 5003, 131, 132, True),
+                                                 ("f32cos", 5000, 140, 132, False)])
+def test_topk_list_kernel_long_sweeps(kind, nb, dim, k, cands):
+    """Shapes that the list kernel takes by itself (k too large for a sample of
+    so few base rows) and sweeps in one part, long enough for base norms from a
+    launch of their own; a ragged last tile, candidate lists; whole numbers, so
+    exact."""
+    say("topk long sweeps", kind, nb, dim, k, cands)
+    A = api()
+    g = np.random.default_rng(nb + dim)
+    metric = orc.COS if kind == "f32cos" else orc.L2SQ
+    nq = 33000
+    x, q = (g.integers(0, 250 if kind == "u8" else 16, (n, dim)).astype(np.uint8 if kind == "u8" else np.float32)
+            for n in (nb + 700 * cands, nq))
+    cand = g.permutation(nb + 700)[:nb].astype(np.int32) if cands else None
+    rows = np.unique(np.concatenate([np.arange(40), np.arange(nq - 40, nq), g.choice(nq, 60, replace=False)]))
+    rid, rd = orc.topk(orc.Vectors.from_array(q, metric), orc.Vectors.from_array(x, metric), k, q_rows=rows,
+                       cand=cand, exclude_self=cands)
+    ids, d = A.topk(gpu_vectors(q, metric), gpu_vectors(x, metric), k, cand=to_dev(cand) if cands else None,
+                    exclude_self=cands)
+    assert np.array_equal(host(ids)[rows], rid)
+    assert np.array_equal(host(d)[rows].astype(np.float64), rd)
