@@ -4,6 +4,7 @@
 // results are deterministic.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -145,6 +146,9 @@ __global__ void __launch_bounds__(64) mlp_sample_kernel(const float *X, int batc
 // v + 16, ..., v + 240 in registers, so that it reads whole rows of dh or h; one
 // block per parameter and a thread per partial sum read each row's line for 4
 // bytes of it: 13.0 us at 1024 x (14 -> 64 -> 16), now 6.6 us.
+// A wave may put G partial sums beside each other and take 64 / G units (blockIdx.y
+// says which) over G times 256 samples at a time: see mlp_reduce_groups.
+template <int G>
 __global__ void __launch_bounds__(1024) mlp_reduce_kernel(const float *X, int batch, int F, int H,
                                                           int T, const float *hid, const float *dy,
                                                           const float *dh, const float *lossp,
@@ -166,29 +170,36 @@ __global__ void __launch_bounds__(1024) mlp_reduce_kernel(const float *X, int ba
     } else if (p == F + T + 2) {
         row = lossp; pitch = 1; lanes = 1; dst = loss;
     }
-    const int col = min(lane, lanes - 1);
-    float s[16];
+    // register u of lane group g: partial sum wave + 16 (u G + g)
+    constexpr int W = 64 / G, R = 16 / G;
+    if ((int)blockIdx.y * W >= lanes) return;
+    const int col = min((int)blockIdx.y * W + lane % W, lanes - 1);
+    const int first = G == 1 ? wave : wave + 16 * (lane / W);
+    float s[R];
 #pragma unroll
-    for (int q = 0; q < 16; q++) s[q] = 0.0f;
-    for (int n0 = wave; n0 < batch; n0 += 256) {
+    for (int u = 0; u < R; u++) s[u] = 0.0f;
+    for (int n0 = first; n0 < batch; n0 += 256 * G) {
         float v[16], f[16];
 #pragma unroll
-        for (int q = 0; q < 16; q++) {
-            const int64_t n = min(n0 + 16 * q, batch - 1);
-            v[q] = row[n * pitch + col];
-            f[q] = fac ? fac[n * fpitch] : 1.0f;
+        for (int i = 0; i < 16; i++) {
+            const int64_t n = min(n0 + 256 * (i / R) + 16 * G * (i % R), batch - 1);
+            v[i] = row[n * pitch + col];
+            f[i] = fac ? fac[n * fpitch] : 1.0f;
         }
 #pragma unroll
-        for (int q = 0; q < 16; q++)
-            if (n0 + 16 * q < batch) s[q] = fmaf(v[q], f[q], s[q]);
+        for (int i = 0; i < 16; i++)
+            if (n0 + 256 * (i / R) + 16 * G * (i % R) < batch) s[i % R] = fmaf(v[i], f[i], s[i % R]);
     }
 #pragma unroll
-    for (int m = 8; m >= 1; m >>= 1)
+    for (int m = R / 2; m >= 1; m >>= 1)
 #pragma unroll
-        for (int q = 0; q < m; q++) s[q] += s[q + m];
+        for (int u = 0; u < m; u++) s[u] += s[u + m];
+#pragma unroll
+    for (int m = G / 2; m >= 1; m >>= 1) s[0] += __shfl_down(s[0], m * W);
     red[wave][lane] = s[0];
     __syncthreads();
-    if (wave != 0 || lane >= lanes) return;
+    const int unit = blockIdx.y * W + lane;
+    if (wave != 0 || lane >= W || unit >= lanes) return;
     float r[16];
 #pragma unroll
     for (int v = 0; v < 16; v++) r[v] = red[v][lane];
@@ -196,7 +207,7 @@ __global__ void __launch_bounds__(1024) mlp_reduce_kernel(const float *X, int ba
     for (int m = 8; m >= 1; m >>= 1)
 #pragma unroll
         for (int v = 0; v < m; v++) r[v] += r[v + m];
-    dst[lane * step] = r[0];
+    dst[unit * step] = r[0];
 }
 
 __global__ void adam_kernel(float *p, const float *g, float *m, float *v, int64_t n, float lr,
@@ -331,6 +342,21 @@ onng_status mlp_forward_launch(const float *X, int32_t batch, int32_t F, const f
     return ONNG_OK;
 }
 
+// Partial sums beside each other in a wave of the gradient sums.  A wave takes 256 G
+// samples at a time, so up to 2048 samples one time or a few; from there on the few
+// blocks of whole rows leave the chip idle, and the units are split as far as the
+// blocks stay within one per compute unit.  Backward at 100,000 samples, us, with
+// G = 1, so, and with a block per parameter: 14 -> 16 -> 2: 539, 245, 214; 5 -> 33 ->
+// 2: 541, 268, 257; 14 -> 64 -> 16: 555, 303, 1761 (at 20,000: 114, 50, 73; 117, 57,
+// 91; 120, 67, 517).
+static int mlp_reduce_groups(int32_t batch, int32_t F, int32_t H, int32_t T) {
+    const int lanes = std::max(H, T);
+    int G = 1;
+    if (batch >= 2048)
+        while (G < 16 && (int64_t)(F + T + 3) * ((lanes + 32 / G - 1) / (32 / G)) <= device_cu_count()) G *= 2;
+    return G;
+}
+
 onng_status mlp_backward_launch(const float *X, const float *target, const float *w,
                                 int32_t batch, int32_t F, const float *W1, const float *b1,
                                 int32_t H, const float *W2, const float *b2, int32_t T,
@@ -343,8 +369,12 @@ onng_status mlp_backward_launch(const float *X, const float *target, const float
     float *lp = c.take<float>((size_t)batch);
     hipLaunchKernelGGL(mlp_sample_kernel, dim3((batch + MLP_S - 1) / MLP_S), dim3(64), 0, st, X, batch,
                        F, W1, b1, H, W2, b2, T, target, w, hid, nullptr, dy, dh, lp);
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3(F + T + 3), dim3(1024), 0, st, X, batch, F, H, T, hid,
-                       dy, dh, lp, gW1, gb1, gW2, gb2, loss);
+    const int G = mlp_reduce_groups(batch, F, H, T);
+    auto reduce = G == 16 ? mlp_reduce_kernel<16> : G == 8 ? mlp_reduce_kernel<8> : G == 4 ? mlp_reduce_kernel<4>
+                  : G == 2 ? mlp_reduce_kernel<2> : mlp_reduce_kernel<1>;
+    const int W = 64 / G;
+    hipLaunchKernelGGL(reduce, dim3(F + T + 3, (std::max(H, T) + W - 1) / W), dim3(1024), 0, st, X, batch, F,
+                       H, T, hid, dy, dh, lp, gW1, gb1, gW2, gb2, loss);
     ONNG_HIP(hipGetLastError());
     return ONNG_OK;
 }

@@ -1,0 +1,28 @@
+"""Shapes beside the usual ones of the training, encoding, rerank and list-sorting
+kernels, at the edges of the rules that split their work."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as orc
+from gpu_common import L, api, gpu_graph, gpu_vectors, host, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,F,H,T", [(2047, 14, 16, 2), (2048, 14, 16, 2), (4099, 1, 1, 1), (6001, 33, 33, 3),
+                                     (2050, 14, 64, 16), (5000, 110, 40, 16), (3000, 250, 64, 16), (2300, 60, 20, 9)])
+def test_mlp_large_batches(B, F, H, T):
+    """Gradient sums of batches whose units are split over blocks (1 to 16
+    partial sums beside each other in a wave); every result is an f32 sum in 256
+    partial sums and a tree, of terms of both signs: 1e-5 of its norm."""
+    say("mlp large", B, F, H, T)
+    A = api()
+    g = np.random.default_rng(B)
+    X, Y, W = (g.standard_normal(s).astype(np.float32) for s in ((B, F), (B, T), (B, T)))
+    W = np.abs(W)
+    W1, b1, W2, b2 = ((g.standard_normal(s) * 0.3).astype(np.float32) for s in ((H, F), (H,), (T, H), (T,)))
+    ref_loss, ref_g = orc.mlp_loss_grad(X, Y, W1, b1, W2, b2, W)
+    loss, grads = A.mlp_backward(to_dev(X), to_dev(Y), *(to_dev(a) for a in (W1, b1, W2, b2)), w=to_dev(W))
+    for got, ref in zip([loss, *grads], [np.array([ref_loss]), *ref_g]):
+        assert np.linalg.norm(host(got) - ref) <= 1e-5 * np.linalg.norm(ref) + 1e-7
