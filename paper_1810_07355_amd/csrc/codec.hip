@@ -111,29 +111,29 @@ __device__ __forceinline__ void put4(uint8_t *at, float4 v, float s) {
     }
 }
 
-// max over the 32 lanes of a half wave
-__device__ __forceinline__ float half_max(float x) {
+// max over the LPR lanes of a row
+template <int LPR>
+__device__ __forceinline__ float row_max(float x) {
     x = fmaxf(x, dpp<DPP_ROW_ROR8>(x));
     x = fmaxf(x, dpp<DPP_ROW_ROR4>(x));
     x = fmaxf(x, dpp<DPP_QP_2301>(x));
     x = fmaxf(x, dpp<DPP_QP_1032>(x));
-    return fmaxf(x, swz_xor<16>(x));
+    x = fmaxf(x, swz_xor<16>(x));
+    return LPR == 64 ? fmaxf(x, __shfl_xor(x, 32)) : x;
 }
 
-// Half a wave per row, four elements per lane and step; a half wave takes
-// ENC_ROWS rows, whose loads are in flight together.  Bound by memory: it
-// reads 4 dim bytes a row and writes the row.  Needs the destination aligned
-// for put4; SRC4: the source rows are 16-byte aligned (else element loads).
-// 1M x 100 to fp8 rows with the scale in the row: 106 us (512 MB, the rate of
-// a large copy); one element per lane and byte stores: 383 us.
-constexpr int ENC_ROWS = 4;
-
-template <int DT, bool SRC4>
+// LPR lanes per row, four elements per lane and step; they take ROWS rows, whose
+// loads are in flight together.  Bound by memory: it reads 4 dim bytes a row and
+// writes the row.  Needs the destination aligned for put4; SRC4: the source rows
+// are 16-byte aligned (else element loads).  Half a wave and four rows (1M x 100 to
+// fp8 rows with the scale in the row: 106 us, 512 MB, the rate of a large copy; one
+// element per lane and byte stores: 383 us); a wave a row for rows of more steps.
+template <int DT, bool SRC4, int LPR, int ROWS>
 __global__ void __launch_bounds__(256) encode4_kernel(const float *src, int64_t n, int dim,
                                                       uint8_t *dst, int64_t pitch, float *scale) {
     constexpr int ESZ = DT == ONNG_F32 ? 4 : DT == ONNG_FP8_E4M3 ? 1 : 2;
-    const int64_t row0 = ((int64_t)blockIdx.x * 8 + threadIdx.x / 32) * ENC_ROWS;
-    const int l = threadIdx.x & 31;
+    const int64_t row0 = ((int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR) * ROWS;
+    const int l = threadIdx.x & (LPR - 1);
     const int64_t fill = DT == ONNG_FP8_E4M3 && !scale ? pitch - 4 : pitch;
     auto load = [&](int64_t row, int c) {
         const float *x = src + row * dim + c;
@@ -146,21 +146,28 @@ __global__ void __launch_bounds__(256) encode4_kernel(const float *src, int64_t 
         if (c + 3 < dim) v.w = x[3];
         return v;
     };
-    float4 v[ENC_ROWS];
+    float4 v[ROWS];
 #pragma unroll
-    for (int r = 0; r < ENC_ROWS; r++) v[r] = load(row0 + r, 4 * l);
-    float s[ENC_ROWS];
+    for (int r = 0; r < ROWS; r++) v[r] = load(row0 + r, 4 * l);
+    float s[ROWS];
+    auto max4 = [](float4 u) { return fmaxf(fmaxf(fabsf(u.x), fabsf(u.y)), fmaxf(fabsf(u.z), fabsf(u.w))); };
+    if constexpr (DT == ONNG_FP8_E4M3) {
 #pragma unroll
-    for (int r = 0; r < ENC_ROWS; r++) {
-        s[r] = 1.0f;
-        if constexpr (DT == ONNG_FP8_E4M3) {
-            float mx = fmaxf(fmaxf(fabsf(v[r].x), fabsf(v[r].y)), fmaxf(fabsf(v[r].z), fabsf(v[r].w)));
-            mx = fmaxf(mx, 0.0f);   // NaN elements do not count
-            for (int c = 4 * (l + 32); c < dim; c += 128) {
-                const float4 u = load(row0 + r, c);
-                mx = fmaxf(mx, fmaxf(fmaxf(fabsf(u.x), fabsf(u.y)), fmaxf(fabsf(u.z), fabsf(u.w))));
-            }
-            mx = half_max(mx);
+        for (int r = 0; r < ROWS; r++) s[r] = fmaxf(max4(v[r]), 0.0f);   // NaN elements do not count
+        for (int c = 4 * (l + LPR); c < dim; c += 4 * LPR) {
+            float4 u[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; r++) u[r] = load(row0 + r, c);
+#pragma unroll
+            for (int r = 0; r < ROWS; r++) s[r] = fmaxf(s[r], max4(u[r]));
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; r++) {
+        if constexpr (DT != ONNG_FP8_E4M3) {
+            s[r] = 1.0f;
+        } else {
+            const float mx = row_max<LPR>(s[r]);
             s[r] = mx > 0.0f ? __fdiv_rn(mx, 448.0f) : 1.0f;
             if (l == 0 && row0 + r < n) {
                 if (scale) scale[row0 + r] = s[r];
@@ -170,12 +177,16 @@ __global__ void __launch_bounds__(256) encode4_kernel(const float *src, int64_t 
     }
     // elements at or past dim are zero: the code of 0 is 0 in every type
 #pragma unroll
-    for (int r = 0; r < ENC_ROWS; r++)
+    for (int r = 0; r < ROWS; r++)
         if (row0 + r < n && 4 * l * ESZ < fill) put4<DT>(dst + (row0 + r) * pitch + 4 * l * ESZ, v[r], s[r]);
-    for (int r = 0; r < ENC_ROWS; r++)
-        for (int64_t c = 4 * (l + 32); c * ESZ < fill; c += 128)
-            if (row0 + r < n)
-                put4<DT>(dst + (row0 + r) * pitch + c * ESZ, load(row0 + r, (int)min<int64_t>(c, dim)), s[r]);
+    for (int64_t c = 4 * (l + LPR); c * ESZ < fill; c += 4 * LPR) {
+        float4 u[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) u[r] = load(row0 + r, (int)min<int64_t>(c, dim));
+#pragma unroll
+        for (int r = 0; r < ROWS; r++)
+            if (row0 + r < n) put4<DT>(dst + (row0 + r) * pitch + c * ESZ, u[r], s[r]);
+    }
 }
 
 }  // namespace
@@ -187,13 +198,22 @@ onng_status encode_launch(const float *src, int64_t n, int32_t dim, int32_t dtyp
     const int unit = 4 * elem_bytes(dtype);
     if (reinterpret_cast<uintptr_t>(dst) % unit == 0 && pitch % unit == 0) {
         const bool s4 = reinterpret_cast<uintptr_t>(src) % 16 == 0 && dim % 4 == 0;
-        const dim3 grid((unsigned)((n + 8 * ENC_ROWS - 1) / (8 * ENC_ROWS))), block(256);
+        // Rows of more than one step of half a wave take a wave each: the rows side by
+        // side in the steps cost more than they hide.  us, half waves / so / one element
+        // per lane: f32, 300,000 x 300: 192 / 130 / 175; fp8, 300,000 x 300: 120 / 132 /
+        // 245, 93,750 x 960: 138 / 99 / 214, 1000 x 960: 16 / 9 / 11.  At 100 and 128
+        // components: fp8, 900,000 x 100: 92 / 189 / 347.
+        const bool wide = dim > 128;
+        const int64_t per = wide ? 4 : 32;
+        const dim3 grid((unsigned)((n + per - 1) / per)), block(256);
         uint8_t *d = static_cast<uint8_t *>(dst);
 #define ONNG_ENC(DT)                                                                             \
-    case DT:                                                                                     \
-        if (s4) hipLaunchKernelGGL((encode4_kernel<DT, true>), grid, block, 0, st, src, n, dim, d, pitch, scale); \
-        else hipLaunchKernelGGL((encode4_kernel<DT, false>), grid, block, 0, st, src, n, dim, d, pitch, scale);   \
-        break;
+    case DT: {                                                                                   \
+        auto fn = wide ? (s4 ? encode4_kernel<DT, true, 64, 1> : encode4_kernel<DT, false, 64, 1>)  \
+                       : (s4 ? encode4_kernel<DT, true, 32, 4> : encode4_kernel<DT, false, 32, 4>); \
+        hipLaunchKernelGGL(fn, grid, block, 0, st, src, n, dim, d, pitch, scale);                \
+        break;                                                                                   \
+    }
         switch (dtype) {
             ONNG_ENC(ONNG_F32)
             ONNG_ENC(ONNG_F16)

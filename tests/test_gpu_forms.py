@@ -26,3 +26,30 @@ def test_mlp_large_batches(B, F, H, T):
     loss, grads = A.mlp_backward(to_dev(X), to_dev(Y), *(to_dev(a) for a in (W1, b1, W2, b2)), w=to_dev(W))
     for got, ref in zip([loss, *grads], [np.array([ref_loss]), *ref_g]):
         assert np.linalg.norm(host(got) - ref) <= 1e-5 * np.linalg.norm(ref) + 1e-7
+
+
+@pytest.mark.parametrize("n", [1, 3, 130])
+@pytest.mark.parametrize("dim,pitch", [(128, None), (129, None), (132, None), (252, 384), (256, None), (257, None),
+                                       (300, 512), (515, None), (960, None)])
+def test_encode_wide_rows(n, dim, pitch):
+    """Rows of one and of several steps of a wave, ragged ends and wide padding,
+    the scale beside the rows and in them, byte for byte."""
+    A, Lb = api(), L()
+    g = np.random.default_rng(dim + n)
+    x = (g.standard_normal((n, dim)) * 10.0 ** g.integers(-6, 4, size=(n, 1))).astype(np.float32)
+    for dt, odt, esz, inrow in ((Lb.F32, orc.F32, 4, False), (Lb.F16, orc.F16, 2, False), (Lb.BF16, orc.BF16, 2, False),
+                                (Lb.FP8_E4M3, orc.FP8, 1, False), (Lb.FP8_E4M3, orc.FP8, 1, True)):
+        if pitch is not None and pitch < dim * esz + 16:
+            continue
+        say("encode wide", n, dim, pitch, dt, inrow)
+        v = A.encode(to_dev(x), dt, Lb.L2SQ, pitch=pitch, scale_in_row=inrow)
+        codes = host(v.data)
+        ref, rs = orc.encode_rows(x, odt, pitch=v.pitch)
+        codes = codes.view(np.uint8).reshape(n, -1)
+        ref = ref.view(np.uint8).reshape(n, -1)
+        if inrow:
+            assert np.array_equal(codes[:, -4:].copy().view(np.float32)[:, 0], rs)
+            codes, ref = codes[:, :-4], ref[:, :-4]
+        elif rs is not None:
+            assert np.array_equal(host(v.scale), rs)
+        assert np.array_equal(codes, ref)
