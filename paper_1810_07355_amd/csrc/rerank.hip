@@ -43,16 +43,17 @@ template <typename T>
 __device__ __forceinline__ T plus_xor1(T x) { return x + (sizeof(T) == 8 ? (T)dpp64<DPP_QP_1032>(x) : (T)dpp<DPP_QP_1032>((float)x)); }
 
 // One block per query.  Sixteen lanes share a pool row, four consecutive
-// components each per 64, and RR_ROWS rows of a lane group are in flight; then
+// components each per 64, and RR_ROWS rows of a lane group are in flight (RR_AHEAD,
+// or one where the lane groups hold the pool at once); then
 // every entry's place is the number of entries before it under (d, id).
 // Bound by the random row reads: the pool's rows once.  The sum of a row is
 // the tree of one component per lane (chains over components 64 apart, then
 // lanes 32, 16, .. 1 apart), kept as it was when one row at a time took the
 // whole wave, so f32 distances and their ties are unchanged.  10,000 queries
 // x 74 rows of 100 f32, f64 sums: 113 us; one row at a time 527 us.
-constexpr int RR_ROWS = 4;
+constexpr int RR_AHEAD = 4;
 
-template <bool F64, bool PLAIN_F32>
+template <bool F64, bool PLAIN_F32, int RR_ROWS>
 __global__ void __launch_bounds__(256) rerank_kernel(const uint8_t *q, int64_t qp, int qdt,
                                                      const float *qsc, const uint8_t *b,
                                                      int64_t bp, int bdt, const float *bsc,
@@ -177,13 +178,20 @@ onng_status rerank_launch(const onng_vectors *Q, const onng_vectors *B, const in
     }
     if (Q->n == 0) return ONNG_OK;
     const bool plain = Q->dtype == ONNG_F32 && B->dtype == ONNG_F32;
-    auto fn = use_f64 ? (plain ? rerank_kernel<true, true> : rerank_kernel<true, false>)
-                      : (plain ? rerank_kernel<false, true> : rerank_kernel<false, false>);
+    auto pick = [&](auto ahead) {
+        constexpr int R = decltype(ahead)::value;
+        return use_f64 ? (plain ? rerank_kernel<true, true, R> : rerank_kernel<true, false, R>)
+                       : (plain ? rerank_kernel<false, true, R> : rerank_kernel<false, false, R>);
+    };
+    // a pool of at most four rows fills no second row of a lane group (40,000 queries
+    // x 1 row of 8 f32, f64 sums: 27.7 us with four rows ahead, 14.4 with one; a
+    // wave to a row 25.0)
+    auto fn = psz <= 4 ? pick(std::integral_constant<int, 1>()) : pick(std::integral_constant<int, RR_AHEAD>());
     // one wave per query once the queries alone fill the chip (32 waves on each
     // compute unit), else up to four that share its rows
     int waves = 1;
     while (waves < 4 && Q->n * waves * 2 <= (int64_t)32 * device_cu_count() &&
-           psz > waves * 4 * RR_ROWS)
+           psz > waves * 4 * RR_AHEAD)
         waves *= 2;
     hipLaunchKernelGGL(fn, dim3((unsigned)Q->n), dim3(waves * WAVE), (size_t)psz * 12, st,
                        static_cast<const uint8_t *>(Q->data), Q->pitch_bytes, Q->dtype, Q->scale,

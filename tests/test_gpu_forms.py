@@ -53,3 +53,22 @@ def test_encode_wide_rows(n, dim, pitch):
         elif rs is not None:
             assert np.array_equal(host(v.scale), rs)
         assert np.array_equal(codes, ref)
+
+
+@pytest.mark.parametrize("pool", [1, 3, 4, 5])
+@pytest.mark.parametrize("nq,dim,metric", [(1, 8, orc.L2SQ), (700, 65, orc.COS), (40_000, 5, orc.L2SQ)])
+def test_rerank_small_pools(nq, pool, dim, metric):
+    """Pools that the four lane groups of a wave hold at once, and one row more;
+    whole numbers, so that f32 and f64 sums are exact; some places empty."""
+    say("rerank small pool", nq, pool, dim)
+    A = api()
+    g = np.random.default_rng(pool + nq)
+    x, q = (g.integers(-7, 8, (n, dim)).astype(np.float32) for n in (500, nq))
+    ids = np.argsort(g.random((nq, 500)), axis=1)[:, :pool].astype(np.int32)
+    ids[::3, pool // 2] = -1
+    k = min(3, pool)
+    rid, rd = orc.rerank(orc.Vectors.from_array(q, metric), orc.Vectors.from_array(x, metric), ids, k)
+    for f64 in (False, True):
+        gid, gd = A.rerank(gpu_vectors(q, metric), gpu_vectors(x, metric), to_dev(ids), k, use_f64=f64)
+        assert np.array_equal(host(gid), rid)
+        assert np.array_equal(host(gd).astype(np.float64), rd)
