@@ -206,7 +206,8 @@ __global__ void __launch_bounds__(256) sa_merge_kernel(const int32_t *knn, const
 // 256 take one wave (up to four keys a lane), four lists per block: the places
 // of a list of m keys cost m / 2 broadcasts and 2 m / 64 compares a lane, less
 // than a bitonic network's exchanges there.  Longer ones are queued for blocks
-// of their own, which sort up to 4096 keys in LDS by a bitonic network.
+// of their own, which sort up to 4096 keys in LDS by a bitonic network.  Up to 1024
+// lists in all go to such blocks directly, without a queue.
 // (13.5M edges in 200,003 lists, 5,000 of them long: 0.15 + 0.10 ms; the long
 // ones by counting 0.70 ms; one block of 256 threads per list, every place
 // counted, 2.0 ms.)
@@ -298,11 +299,11 @@ template <typename LenT>
 __global__ void __launch_bounds__(512) seg_sort_long_kernel(const int64_t *seg, const int64_t *off,
                                                             const uint64_t *keys, int32_t *nbrs,
                                                             LenT *lens, const int32_t *queue,
-                                                            const int32_t *n_queue) {
+                                                            const int32_t *n_queue, int n_lists) {
     __shared__ uint64_t sk[SEG_LDS];
-    const int total = *n_queue;
+    const int total = queue ? *n_queue : n_lists;
     for (int q = blockIdx.x; q < total; q += gridDim.x) {
-        const int64_t v = queue[q];
+        const int64_t v = queue ? queue[q] : q;
         const int64_t b = off[v], m = off[v + 1] - b;
         const uint64_t *src = keys + seg[v];
         __syncthreads();
@@ -873,30 +874,39 @@ __global__ void ae_new_kernel(int64_t n, const int32_t *src, const int32_t *dst,
 
 // ------------------------------------------------------------- host side --
 
-// Sorts every list (see seg_sort_kernel); queue: n + 1 ints, its first the
-// queue's length.
+// Sorts every list (see seg_sort_kernel); queue: n ints; n_queue: its length, zero.
 template <typename LenT>
 static void seg_sort(const int64_t *seg, const int64_t *off, int64_t n, const uint64_t *keys,
-                     int32_t *nbrs, LenT *lens, int32_t *queue, hipStream_t st) {
+                     int32_t *nbrs, LenT *lens, int32_t *queue, int32_t *n_queue, hipStream_t st) {
     if (n == 0) return;
-    (void)hipMemsetAsync(queue, 0, sizeof(int32_t), st);
+    if (n <= SEG_BLOCKS) {   // one launch for two: some 5 us of a call of 110 on 1000 nodes
+        hipLaunchKernelGGL((seg_sort_long_kernel<LenT>), dim3((unsigned)n), dim3(512), 0, st, seg, off, keys,
+                           nbrs, lens, nullptr, nullptr, (int)n);
+        return;
+    }
     hipLaunchKernelGGL((seg_sort_kernel<LenT>), dim3(blocks_for(n, 4)), dim3(256), 0, st, seg, off,
-                       n, keys, nbrs, lens, queue + 1, queue);
+                       n, keys, nbrs, lens, queue, n_queue);
     hipLaunchKernelGGL((seg_sort_long_kernel<LenT>),
-                       dim3((unsigned)std::min<int64_t>(n, SEG_BLOCKS)), dim3(512), 0, st, seg, off,
-                       keys, nbrs, lens, queue + 1, queue);
+                       dim3(SEG_BLOCKS), dim3(512), 0, st, seg, off, keys, nbrs, lens, queue,
+                       n_queue, 0);
+}
+
+// zeroes of consecutive regions of a workspace, first to end: one launch
+static hipError_t clear_range(void *first, void *end, hipStream_t st) {
+    return hipMemsetAsync(first, 0, (size_t)(static_cast<char *>(end) - static_cast<char *>(first)), st);
 }
 
 size_t adjust_degree_ws(int64_t n, int32_t k, int32_t e_o, int32_t e_i) {
     const int64_t eo = std::min(e_o, k), ei = std::min(e_i, k);
     Carver c(nullptr);
     c.take<int32_t>(n);                // reverse candidates per node
+    c.take<int32_t>(1);                // number of long lists
     c.take<int32_t>(n);                // forward edges per node
     c.take<int32_t>(n * ei);           // place of each reverse candidate
     c.take<int64_t>(n + 1);            // segment sizes, then edges per node
     c.take<int64_t>(n + 1);            // segment offsets
     c.take<uint64_t>(n * (eo + ei));   // keys
-    c.take<int32_t>(n + 1);            // long lists
+    c.take<int32_t>(n);                // long lists
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
 }
@@ -909,17 +919,18 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
     const int eo = std::min(e_o, k), ei = std::min(e_i, k);
     Carver c(ws);
     int32_t *rcnt = c.take<int32_t>(n);
+    int32_t *n_queue = c.take<int32_t>(1);
     int32_t *fcnt = c.take<int32_t>(n);
     int32_t *slot = c.take<int32_t>(n * (int64_t)ei);
     int64_t *cnt = c.take<int64_t>(n + 1);
     int64_t *seg = c.take<int64_t>(n + 1);
     uint64_t *keys = c.take<uint64_t>(n * (int64_t)(eo + ei));
-    int32_t *queue = c.take<int32_t>(n + 1);
+    int32_t *queue = c.take<int32_t>(n);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
     const unsigned wb = blocks_for(n, 4);
+    ONNG_HIP(clear_range(rcnt, n_queue + 1, st));
     if (n > 0) {
-        ONNG_HIP(hipMemsetAsync(rcnt, 0, sizeof(int32_t) * n, st));
         hipLaunchKernelGGL(sa_count_kernel, dim3(blocks_for(n, SA_ROWS)), dim3(SA_WAVES * WAVE), 0,
                            st, knn, n, k, eo, ei, rcnt, slot, fcnt);
     }
@@ -939,7 +950,7 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
         set_error("onng_adjust_degree: nnz_capacity too small");
         return ONNG_ERR_CAPACITY;
     }
-    seg_sort<LenT>(seg, offsets, n, keys, nbrs, lens, queue, st);
+    seg_sort<LenT>(seg, offsets, n, keys, nbrs, lens, queue, n_queue, st);
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
     return ONNG_OK;
@@ -962,15 +973,16 @@ size_t adjust_degree_constrained_ws(int64_t n, int32_t k, int32_t e_o, int32_t e
     const int64_t cap = nrev + n * (int64_t)std::min(e_o, k);
     Carver c(nullptr);
     c.take<int64_t>(n + 1);            // |N(G_t, o)|
-    c.take<int64_t>(n + 1);            // G_t offsets
+    c.take<int64_t>(n + 1);            // kept counts
     c.take<int32_t>(n);                // cursors
+    c.take<int32_t>(2);                // numbers of long lists
+    c.take<int64_t>(n + 1);            // G_t offsets
     c.take<int32_t>(n);                // first source per node
     c.take<uint64_t>(nrev);            // G_t keys
     c.take<int32_t>(nrev);             // G_t ids, sorted per node
     c.take<int32_t>(nrev);             // G_t lengths (4 bytes)
-    c.take<int64_t>(n + 1);            // kept counts
     c.take<uint64_t>(cap);             // kept keys
-    c.take<int32_t>(n + 1);            // long lists
+    c.take<int32_t>(n);                // long lists
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
 }
@@ -987,27 +999,26 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
     const int64_t cap = nrev + n * (int64_t)std::min(e_o, k);
     Carver c(ws);
     int64_t *cnt = c.take<int64_t>(n + 1);
-    int64_t *rev_off = c.take<int64_t>(n + 1);
+    int64_t *ocnt = c.take<int64_t>(n + 1);
     int32_t *cursor = c.take<int32_t>(n);
+    int32_t *n_queue = c.take<int32_t>(2);
+    int64_t *rev_off = c.take<int64_t>(n + 1);
     int32_t *first_src = c.take<int32_t>(n);
     uint64_t *rkeys = c.take<uint64_t>(nrev);
     int32_t *rv_nb = c.take<int32_t>(nrev);
     LenT *rv_len = reinterpret_cast<LenT *>(c.take<int32_t>(nrev));
-    int64_t *ocnt = c.take<int64_t>(n + 1);
     uint64_t *okeys = c.take<uint64_t>(cap);
-    int32_t *queue = c.take<int32_t>(n + 1);
+    int32_t *queue = c.take<int32_t>(n);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
-    ONNG_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * (n + 1), st));
-    ONNG_HIP(hipMemsetAsync(ocnt, 0, sizeof(int64_t) * (n + 1), st));
-    ONNG_HIP(hipMemsetAsync(cursor, 0, sizeof(int32_t) * n, st));
+    ONNG_HIP(clear_range(cnt, n_queue + 2, st));
     if (n > 0) {
         hipLaunchKernelGGL(sac_rcount_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, knn, n,
                            k, ei, cnt);
         ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, rev_off, (int)(n + 1), st));
         hipLaunchKernelGGL((sac_scatter_kernel<LenT>), dim3(blocks_for(n, 256)), dim3(256), 0, st,
                            knn, kd, n, k, ei, rev_off, cursor, rkeys, first_src);
-        seg_sort<LenT>(rev_off, rev_off, n, rkeys, rv_nb, rv_len, queue, st);
+        seg_sort<LenT>(rev_off, rev_off, n, rkeys, rv_nb, rv_len, queue, n_queue, st);
         hipLaunchKernelGGL((sac_select_kernel<LenT, false>), dim3(blocks_for(n * WAVE, 256)),
                            dim3(256), 0, st, rev_off, rv_nb, rv_len, first_src, knn, kd, n, k, eo,
                            ocnt, nullptr, nullptr);
@@ -1028,7 +1039,7 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
         hipLaunchKernelGGL((sac_select_kernel<LenT, true>), dim3(blocks_for(n * WAVE, 256)),
                            dim3(256), 0, st, rev_off, rv_nb, rv_len, first_src, knn, kd, n, k, eo,
                            nullptr, offsets, okeys);
-        seg_sort<LenT>(offsets, offsets, n, okeys, nbrs, lens, queue, st);
+        seg_sort<LenT>(offsets, offsets, n, okeys, nbrs, lens, queue, n_queue + 1, st);
     }
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
@@ -1187,8 +1198,9 @@ size_t add_edges_ws(int64_t n, int64_t nnz, int64_t m) {
     Carver c(nullptr);
     c.take<int64_t>(n + 1);
     c.take<int32_t>(n);
+    c.take<int32_t>(1);
     c.take<uint64_t>(nnz + m);
-    c.take<int32_t>(n + 1);
+    c.take<int32_t>(n);
     c.take<char>(scan_temp_bytes(n + 1));
     return c.size() + 256;
 }
@@ -1202,12 +1214,12 @@ static onng_status add_edges_impl(const onng_graph *g, const int32_t *src, const
     Carver c(ws);
     int64_t *cnt = c.take<int64_t>(n + 1);
     int32_t *cursor = c.take<int32_t>(n);
+    int32_t *n_queue = c.take<int32_t>(1);
     uint64_t *keys = c.take<uint64_t>(nnz + m);
-    int32_t *queue = c.take<int32_t>(n + 1);
+    int32_t *queue = c.take<int32_t>(n);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
-    ONNG_HIP(hipMemsetAsync(cnt, 0, sizeof(int64_t) * (n + 1), st));
-    ONNG_HIP(hipMemsetAsync(cursor, 0, sizeof(int32_t) * n, st));
+    ONNG_HIP(clear_range(cnt, n_queue + 1, st));
     const int64_t big = std::max(n, m);
     if (big > 0)
         hipLaunchKernelGGL(ae_count_kernel, dim3(blocks_for(big, 256)), dim3(256), 0, st,
@@ -1226,7 +1238,7 @@ static onng_status add_edges_impl(const onng_graph *g, const int32_t *src, const
         if (m > 0)
             hipLaunchKernelGGL((ae_new_kernel<LenT>), dim3(blocks_for(m, 256)), dim3(256), 0, st,
                                n, src, dst, len, m, out_off, cursor, keys);
-        seg_sort<LenT>(out_off, out_off, n, keys, out_nb, out_len, queue, st);
+        seg_sort<LenT>(out_off, out_off, n, keys, out_nb, out_len, queue, n_queue, st);
     }
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));

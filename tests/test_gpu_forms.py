@@ -72,3 +72,38 @@ def test_rerank_small_pools(nq, pool, dim, metric):
         gid, gd = A.rerank(gpu_vectors(q, metric), gpu_vectors(x, metric), to_dev(ids), k, use_f64=f64)
         assert np.array_equal(host(gid), rid)
         assert np.array_equal(host(gd).astype(np.float64), rd)
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025, 1500])
+def test_list_sorts_around_the_queue(n):
+    """Degree adjustments and edge insertion with as many lists as are sorted
+    without a queue, and one more: hubs of all lengths among short lists, empty
+    ones too; bit-exact."""
+    say("list sorts", n)
+    A, Lb = api(), L()
+    g = np.random.default_rng(n)
+    k = min(7, max(n - 1, 1))
+    ids = np.empty((n, k), dtype=np.int32)
+    d = np.empty((n, k), dtype=np.int32)
+    for v in range(n):
+        r = np.concatenate([g.permutation(min(n, 3)), 3 + g.permutation(max(n - 3, 0))])
+        r = r[r != v][:k]
+        o = np.lexsort((r, ln := np.sort(g.integers(1, 9, size=len(r)))))
+        ids[v], d[v] = -1, np.iinfo(np.int32).max
+        ids[v, :len(r)], d[v, :len(r)] = r[o], ln[o]
+    for eo, ei in ((k, k), (0, 2), (2, 0), (3, 5)):
+        for mine, ref in ((A.adjust_degree, orc.adjust_degree), (A.adjust_degree_constrained, orc.adjust_degree_constrained)):
+            off, nb, ln = ref(ids, d.astype(np.float64), eo, ei)
+            got = mine(to_dev(ids), to_dev(d), Lb.U8, Lb.L2SQ, eo, ei)
+            assert np.array_equal(host(got.offsets), off)
+            assert np.array_equal(host(got.nbrs), nb)
+            assert np.array_equal(host(got.lens), ln.astype(np.int32))
+    m = 5000
+    src = np.where(g.random(m) < 0.3, 0, g.integers(0, n, size=m)).astype(np.int32)
+    dst, ln = g.integers(0, n, size=m).astype(np.int32), g.integers(1, 50, size=m).astype(np.int32)
+    e = np.zeros(n + 1, dtype=np.int64)
+    out = A.graph_add_edges(gpu_graph(e, np.zeros(0, np.int32), np.zeros(0, np.int32)), to_dev(src), to_dev(dst),
+                            to_dev(ln), Lb.U8, Lb.L2SQ)
+    o = np.lexsort((dst, ln, src))
+    assert np.array_equal(host(out.nbrs), dst[o])
+    assert np.array_equal(host(out.lens), ln[o])
