@@ -198,6 +198,58 @@ __global__ void __launch_bounds__(256) sa_merge_kernel(const int32_t *knn, const
     if (lane == 0) cnt[o] = r + f;
 }
 
+// Short rows (at most SA_SHORT entries count) of few nodes: a lane a row, which looks
+// its own id up in the short row of each target, for the counts and again for the
+// keys.  Three launches fewer than the way by segments, which such calls are bound
+// by; us, so / by segments: 1000 nodes, e_o = e_i = 1: XXX / 104, 2 and 5: XXX / 105;
+// 10,000 nodes, 1 and 3: 101 / 122.  The looking up costs e_o e_i per node: at 4000
+// nodes, 5 and 5: 123 / 117, at 30,000, 2 and 5: 147 / 140.
+constexpr int SA_SHORT = 5;
+
+__device__ __forceinline__ bool in_row(const int32_t *row, int lim, int32_t x) {
+    for (int t = 0; t < lim && row[t] >= 0; t++)
+        if (row[t] == x) return true;
+    return false;
+}
+
+__global__ void sa_short_count_kernel(const int32_t *knn, int64_t n, int k, int eo, int ei, int64_t *cnt) {
+    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= n) return;
+    const int32_t *row = knn + m * k;
+    const int len = row_len(row, max(eo, ei));
+    atomicAdd((unsigned long long *)&cnt[m], (unsigned long long)min(eo, len));
+    for (int t = 0; t < min(ei, len); t++)
+        if (row[t] < n && !in_row(knn + (int64_t)row[t] * k, eo, (int32_t)m))
+            atomicAdd((unsigned long long *)&cnt[row[t]], 1ull);
+}
+
+// forward edges first, then the reverse ones that are none of them
+template <typename LenT>
+__global__ void sa_short_scatter_kernel(const int32_t *knn, const LenT *kd, int64_t n, int k, int eo, int ei,
+                                        const int64_t *off, int32_t *cursor, uint64_t *keys) {
+    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= n) return;
+    const int32_t *row = knn + m * k;
+    const int len = row_len(row, max(eo, ei));
+    for (int t = 0; t < min(eo, len); t++) {
+        const int64_t o = row[t];
+        LenT l = kd[m * k + t];
+        if (o < m)   // the copy that o's step adds comes first
+            for (int u = 0; u < ei && knn[o * k + u] >= 0; u++)
+                if (knn[o * k + u] == m) {
+                    l = kd[o * k + u];
+                    break;
+                }
+        keys[off[m] + t] = make_key(len_ord(l), (uint32_t)o);
+    }
+    for (int t = 0; t < min(ei, len); t++) {
+        const int64_t o = row[t];
+        if (o >= n || in_row(knn + o * k, eo, (int32_t)m)) continue;
+        const int at = min(eo, row_len(knn + o * k, eo)) + atomicAdd(&cursor[o], 1);
+        keys[off[o] + at] = make_key(len_ord(kd[m * k + t]), (uint32_t)m);
+    }
+}
+
 // ------------------------------------------------------------ segment sort --
 // List v: cnt = off[v+1] - off[v] keys at keys[seg[v]] to nbrs/lens at off[v],
 // in ascending order; equal keys keep their order.  A key's place is the
@@ -901,9 +953,9 @@ size_t adjust_degree_ws(int64_t n, int32_t k, int32_t e_o, int32_t e_i) {
     Carver c(nullptr);
     c.take<int32_t>(n);                // reverse candidates per node
     c.take<int32_t>(1);                // number of long lists
+    c.take<int64_t>(n + 1);            // segment sizes, then edges per node
     c.take<int32_t>(n);                // forward edges per node
     c.take<int32_t>(n * ei);           // place of each reverse candidate
-    c.take<int64_t>(n + 1);            // segment sizes, then edges per node
     c.take<int64_t>(n + 1);            // segment offsets
     c.take<uint64_t>(n * (eo + ei));   // keys
     c.take<int32_t>(n);                // long lists
@@ -920,37 +972,42 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
     Carver c(ws);
     int32_t *rcnt = c.take<int32_t>(n);
     int32_t *n_queue = c.take<int32_t>(1);
+    int64_t *cnt = c.take<int64_t>(n + 1);
     int32_t *fcnt = c.take<int32_t>(n);
     int32_t *slot = c.take<int32_t>(n * (int64_t)ei);
-    int64_t *cnt = c.take<int64_t>(n + 1);
     int64_t *seg = c.take<int64_t>(n + 1);
     uint64_t *keys = c.take<uint64_t>(n * (int64_t)(eo + ei));
     int32_t *queue = c.take<int32_t>(n);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
     const unsigned wb = blocks_for(n, 4);
-    ONNG_HIP(clear_range(rcnt, n_queue + 1, st));
-    if (n > 0) {
-        hipLaunchKernelGGL(sa_count_kernel, dim3(blocks_for(n, SA_ROWS)), dim3(SA_WAVES * WAVE), 0,
-                           st, knn, n, k, eo, ei, rcnt, slot, fcnt);
+    const bool short_rows =
+        n == 0 || (std::max(eo, ei) <= SA_SHORT && n * std::max(eo, 1) * std::max(ei, 1) < 100000);
+    ONNG_HIP(clear_range(rcnt, short_rows ? static_cast<void *>(cnt + n + 1) : n_queue + 1, st));
+    if (short_rows) {
+        const dim3 grid(blocks_for(n, 256)), block(256);
+        if (n > 0) hipLaunchKernelGGL(sa_short_count_kernel, grid, block, 0, st, knn, n, k, eo, ei, cnt);
+        ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, offsets, (int)(n + 1), st));
+        if (n > 0)
+            hipLaunchKernelGGL((sa_short_scatter_kernel<LenT>), grid, block, 0, st, knn, kd, n, k, eo, ei, offsets,
+                               rcnt, keys);
+    } else {
+        hipLaunchKernelGGL(sa_count_kernel, dim3(blocks_for(n, SA_ROWS)), dim3(SA_WAVES * WAVE), 0, st, knn, n, k, eo,
+                           ei, rcnt, slot, fcnt);
+        hipLaunchKernelGGL(sa_sizes_kernel, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, rcnt, fcnt, n, cnt);
+        ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, seg, (int)(n + 1), st));
+        hipLaunchKernelGGL((sa_scatter_kernel<LenT>), dim3(wb), dim3(256), 0, st, knn, kd, n, k, ei, seg, slot, keys);
+        hipLaunchKernelGGL((sa_merge_kernel<LenT>), dim3(wb), dim3(256), 0, st, knn, kd, n, k, rcnt, fcnt, seg, keys,
+                           cnt);
+        ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, offsets, (int)(n + 1), st));
     }
-    hipLaunchKernelGGL(sa_sizes_kernel, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, rcnt, fcnt,
-                       n, cnt);
-    ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, seg, (int)(n + 1), st));
-    if (n > 0) {
-        hipLaunchKernelGGL((sa_scatter_kernel<LenT>), dim3(wb), dim3(256), 0, st, knn, kd, n, k,
-                           ei, seg, slot, keys);
-        hipLaunchKernelGGL((sa_merge_kernel<LenT>), dim3(wb), dim3(256), 0, st, knn, kd, n, k,
-                           rcnt, fcnt, seg, keys, cnt);
-    }
-    ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, offsets, (int)(n + 1), st));
     ONNG_HIP(hipMemcpyAsync(nnz_out, offsets + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     ONNG_HIP(hipStreamSynchronize(st));
     if (*nnz_out > nnz_cap) {
         set_error("onng_adjust_degree: nnz_capacity too small");
         return ONNG_ERR_CAPACITY;
     }
-    seg_sort<LenT>(seg, offsets, n, keys, nbrs, lens, queue, n_queue, st);
+    seg_sort<LenT>(short_rows ? offsets : seg, offsets, n, keys, nbrs, lens, queue, n_queue, st);
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
     return ONNG_OK;

@@ -107,3 +107,28 @@ def test_list_sorts_around_the_queue(n):
     o = np.lexsort((dst, ln, src))
     assert np.array_equal(host(out.nbrs), dst[o])
     assert np.array_equal(host(out.lens), ln[o])
+
+
+@pytest.mark.parametrize("n", [2, 40, 3999, 4001])
+@pytest.mark.parametrize("k,eo,ei", [(1, 1, 1), (5, 5, 5), (5, 0, 5), (5, 4, 0), (30, 3, 5), (30, 5, 1), (30, 6, 5)])
+def test_degree_adjustment_short_rows(n, k, eo, ei):
+    """Algorithm 2 with few edges a row, over the rule that a lane takes a row,
+    below and above its number of nodes; rows with padding and hubs; bit-exact."""
+    say("degree short rows", n, k, eo, ei)
+    A, Lb = api(), L()
+    g = np.random.default_rng(n + k)
+    k = min(k, n - 1)
+    ids = np.full((n, k), -1, dtype=np.int32)
+    d = np.full((n, k), np.iinfo(np.int32).max, dtype=np.int32)
+    for v in range(n):
+        r = np.concatenate([g.permutation(2), 2 + g.permutation(min(n - 2, 60))]) if v % 3 else (v + 1 + g.permutation(min(n - 1, 40))) % n
+        r = r[r != v][:k if v % 5 else int(g.integers(0, k + 1))]
+        ln = np.sort(g.integers(1, 9, size=len(r)))
+        o = np.lexsort((r, ln))
+        ids[v, :len(r)], d[v, :len(r)] = r[o], ln[o]
+    off, nb, ln = orc.adjust_degree(ids, d.astype(np.float64), eo, ei)
+    for dt, dd in ((Lb.U8, d), (Lb.F32, np.where(ids >= 0, d * 0.5, np.inf).astype(np.float32))):
+        got = A.adjust_degree(to_dev(ids), to_dev(dd), dt, Lb.L2SQ, eo, ei)
+        assert np.array_equal(host(got.offsets), off)
+        assert np.array_equal(host(got.nbrs), nb)
+        assert np.array_equal(host(got.lens).astype(np.float64), ln if dt == Lb.U8 else ln * 0.5)
