@@ -234,12 +234,16 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
     }
     // A batch of at most one wave per SIMD (4 a CU) leaves most of the LDS idle:
     // a wave takes a block of its own (the queries then spread over all CUs) and
-    // the window grows to up to 2^18 ids while the batch stays resident at once
-    // and rows lie outside it.  Measured, before -> so: f32, 200k rows, 16 / 256
-    // / 1000 queries 302 -> 268, 473 -> 435, 636 -> 599 us; u8, 100k rows, k 100,
-    // the same batches 584 -> 558, 639 -> 609, 674 -> 654 us; fp8, 1M rows, 1000
-    // queries 1342 -> 1341 us.  From 2048 queries on the larger window costs
-    // waves: f32 663 -> 804, fp8 1618 -> 2023 us.
+    // the window grows to up to 2^18 ids while rows lie outside it and the chip
+    // holds the batch and three quarters of another one at once: without room for a
+    // second batch, batches on several streams ran one after the other (u8, 400k
+    // rows, 1000 queries, us per batch on 1 / 4 / 8 streams: 2^18 ids 140 / 92 / 91,
+    // so 138 / 61 / 59; blocks of four waves and 2^16 ids 143 / 56 / 70).  Blocks of
+    // four waves and 2^16 ids -> so, a lone batch: f32, 200k rows, 256 / 512 / 1000
+    // queries 475 -> 436, 630 -> 586, 635 -> 625 us; u8, 100k rows, k 100, 625 -> 600,
+    // 651 -> 621, 658 -> 642; fp8, 1M rows, 1215 -> 1177, 1233 -> 1215, 1300 -> 1297.
+    // From 2048 queries on the larger window costs waves: f32 663 -> 804, fp8
+    // 1618 -> 2023 us.
     const int64_t cus = device_cu_count();
     const bool few = (!cfg || (!cfg->visited_log2 && !cfg->waves_per_block && !cfg->blocks)) &&
                      nq <= 4 * cus;
@@ -249,7 +253,7 @@ static onng_status make_plan(const onng_vectors *base, int64_t nq, const onng_se
             SearchPlan q = P;
             q.vis_log2 = v;
             layout(&q);
-            if ((16LL << v) < base->n && (160 * 1024 / q.lds_per_wave) * cus >= nq) {
+            if ((16LL << v) < base->n && (160 * 1024 / q.lds_per_wave) * cus * 4 >= nq * 7) {
                 P = q;
                 break;
             }
