@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(256) sa_merge_kernel(const int32_t *knn, const
 // Short rows (at most SA_SHORT entries count) of few nodes: a lane a row, which looks
 // its own id up in the short row of each target, for the counts and again for the
 // keys.  Three launches fewer than the way by segments, which such calls are bound
-// by; us, so / by segments: 1000 nodes, e_o = e_i = 1: XXX / 104, 2 and 5: XXX / 105;
+// by; us, so / by segments: 1000 nodes, e_o = e_i = 1: 65 / 104, 2 and 5: 77 / 105;
 // 10,000 nodes, 1 and 3: 101 / 122.  The looking up costs e_o e_i per node: at 4000
 // nodes, 5 and 5: 123 / 117, at 30,000, 2 and 5: 147 / 140.
 constexpr int SA_SHORT = 5;

@@ -40,8 +40,8 @@
 // and more each; so reads are kept in registers or scalars where that saves an
 // LDS trip, and a merge of few keys does without searches.
 // Kernel alone, before and after that work: u8, 100k x 128, 1000 queries, k 100:
-// 935 -> 654 us; f32, 200k x 100, 10k queries: 1511 -> 1254 us; fp8 + rerank,
-// 1M x 100, 10k queries: 4300 -> 3232 us.
+// 935 -> 642 us; f32, 200k x 100, 10k queries: 1511 -> 1253 us; fp8 + rerank,
+// 1M x 100, 10k queries: 4300 -> 3177 us.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

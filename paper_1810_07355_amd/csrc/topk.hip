@@ -8,8 +8,8 @@
 // for float data.  Cosine distance on unit vectors is 1 - <x, y>.
 //
 // From 1024 base rows on, topk_bound.h's two passes do the work; topk_kernel
-// here takes smaller bases, larger shapes than their LDS holds, and the rows
-// whose candidate buffer overflowed there or fell short of k.
+// here takes smaller bases, shapes whose sample or buffers would not fit, and the
+// rows whose candidate buffer overflowed there or fell short of k.
 // A block owns BM query rows (16 per wave) and sweeps the base rows in tiles
 // of 64 staged in LDS.  Each row keeps its current k best keys sorted in LDS
 // and a buffer of candidates that beat its k-th key; the buffer is sorted and
@@ -660,15 +660,18 @@ int topk_bm(int32_t k, int dtype, int32_t dim, int side_words) {
                                                                                             : 32;
 }
 
-// The wide u8 kernel takes over when its 256-row blocks alone fill the chip
-// (one per compute unit at least) and the rows fit two 64-byte k-steps.
-// The f16-screened passes (and the bf16-screened kernel behind them): f32 rows of at most 128 components, its
-// 128-row blocks filling the chip.
+// The f16-screened passes (and the bf16-screened list kernel behind them): f32 rows
+// of at most 128 components, and so many queries that the list kernel's 128-row
+// blocks fill the chip.  The line is the list kernel's; the passes, which split the
+// columns among blocks, are faster below it too (kNN, 100 components, k 100, ms, the
+// narrow passes / these: 9,000 rows 0.44 / 0.23, 32,000 rows 3.39 / 1.02).
 bool topk_use_wide_f32(const onng_vectors *Q, int64_t nb, int32_t k) {
     return Q->dtype == ONNG_F32 && Q->dim <= FW_NCH * 32 && nb >= 16 * FW_BN &&
            Q->n >= (int64_t)FW_ROWS * device_cu_count() && fw_lds_bytes(topk_kcap(k)) <= 64 * 1024;
 }
 
+// The wide u8 passes and list kernel: the list kernel's 256-row blocks alone fill
+// the chip (one per compute unit at least) and the rows fit two 64-byte k-steps.
 bool topk_use_wide(const onng_vectors *Q, int64_t nb, int32_t k) {
     return Q->dtype == ONNG_U8 && nch_for(ONNG_U8, Q->dim) <= 2 && nb >= 16 * BN &&
            Q->n >= (int64_t)WIDE_ROWS * device_cu_count() &&
@@ -689,14 +692,21 @@ struct BoundPlan {
 BoundPlan topk_bound_plan(const onng_vectors *Q, int64_t nb, int32_t k) {
     BoundPlan P;
     const int rank = k + 1;      // one more, as the row itself may be a minimum
+    // us at 1024 base rows, these passes / the list kernel: u8, k 8: 1 query 28 / 35,
+    // 1000 queries 37 / 112; f32, k 100, 1 query 31 / 62 (from 17 queries on a sample of
+    // so few rows does not serve k 100).  Below 1024 they would still win for small k
+    // (u8, k 8, 1000 queries: 512 rows 35 / 104, 256 rows 36 / 82).
     if (Q->n < 1 || nb < 1024) return P;
     const int cw = Q->n <= 16 ? 4 : 1;
     P.rw = Q->n <= 16 ? 1 : Q->n <= 64 ? 4 : 8;
     // One row in f is sampled: the bound costs 1 / f of the filter's products
-    // and lets about k f candidates through.  Measured (us) at f = 2, 4, 8: u8
-    // 10,007 x 10,007 x 128, k 20: 180, 199, -, k 100: 284, 382, -; f32 10,000 x
-    // 10,000 x 100, k 8: 388, 362, -; f32 100 x 1M x 96, k 100: -, 369, 351;
-    // f32 10,000 x 200,000 x 100, k 74: -, 5746, 5313.
+    // and lets about k f candidates through.  Measured (us) at f = 2, 4, 8: kNN of u8
+    // rows, 128 components, k 10: 3000 rows 64, 66, 65; 10,007 154, 168, 184; 16,000 257,
+    // 266, 297; 25,000 548, 528, 569; 50,000 1707, 1598, 1685 (k 100: f = 2 is ahead
+    // throughout, 10,007 rows 261, 357, 815; 50,000 2459, 2727, 3369); of f32 rows, 100
+    // components, k 10: 3000 rows 82, 78, 78; 10,007 388, 366, 366; 25,000 2253, 1876,
+    // 1739 (k 100: 10,007 491, 554, 997; 25,000 2474, 2263, 2377); f32 100 x 1M x 96,
+    // k 100: -, 369, 351; f32 10,000 x 200,000 x 100, k 74: -, 5746, 5313.
     int f = nb >= 65536 ? 8 : Q->dtype == ONNG_U8 && nb < 16384 ? 2 : 4;
     for (; f >= 1; f /= 2) {
         const int64_t want = nb * 181 / 128 / f;         // pow2 within sqrt 2 of nb / f

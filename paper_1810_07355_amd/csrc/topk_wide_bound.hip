@@ -13,8 +13,11 @@
 //
 // Bound by instruction issue: the matrix cores and the vector ALU (compares,
 // maxima, candidates) each take about 30% of the cycles.  kNN of 100,003 x 100
-// f32, cosine, k 100: 23.9 -> 6.2 ms against the kernel that keeps lists; 70,000
-// x 128 u8, k 100: 10.5 -> 2.6; 1M x 100 f32: 513 -> 370.
+// f32, cosine, k 100: 24.6 -> 5.7 ms against the kernel that keeps lists (rows in
+// locality order); 70,000 x 128 u8, k 100: 14.0 -> 2.5; 1M x 100 f32: 506 -> 387.
+// Rows that are left to that kernel cost its whole sweep besides: 3000 equal rows
+// among the 70,000 14.0 -> 15.2 ms, among 100,003 f32 rows (in no order) 46.3 -> 35.9;
+// 70,000 rows of 100 distinct ones 10.2 -> 13.1.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
