@@ -948,11 +948,14 @@ static hipError_t clear_range(void *first, void *end, hipStream_t st) {
     return hipMemsetAsync(first, 0, (size_t)(static_cast<char *>(end) - static_cast<char *>(first)), st);
 }
 
+// The place behind the counts of n lists, zero for the scan, is the counter of the
+// lists' sort afterwards.
+static int32_t *zero_after_scan(int64_t *last) { return reinterpret_cast<int32_t *>(last); }
+
 size_t adjust_degree_ws(int64_t n, int32_t k, int32_t e_o, int32_t e_i) {
     const int64_t eo = std::min(e_o, k), ei = std::min(e_i, k);
     Carver c(nullptr);
     c.take<int32_t>(n);                // reverse candidates per node
-    c.take<int32_t>(1);                // number of long lists
     c.take<int64_t>(n + 1);            // segment sizes, then edges per node
     c.take<int32_t>(n);                // forward edges per node
     c.take<int32_t>(n * ei);           // place of each reverse candidate
@@ -971,7 +974,6 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
     const int eo = std::min(e_o, k), ei = std::min(e_i, k);
     Carver c(ws);
     int32_t *rcnt = c.take<int32_t>(n);
-    int32_t *n_queue = c.take<int32_t>(1);
     int64_t *cnt = c.take<int64_t>(n + 1);
     int32_t *fcnt = c.take<int32_t>(n);
     int32_t *slot = c.take<int32_t>(n * (int64_t)ei);
@@ -983,7 +985,7 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
     const unsigned wb = blocks_for(n, 4);
     const bool short_rows =
         n == 0 || (std::max(eo, ei) <= SA_SHORT && n * std::max(eo, 1) * std::max(ei, 1) < 100000);
-    ONNG_HIP(clear_range(rcnt, short_rows ? static_cast<void *>(cnt + n + 1) : n_queue + 1, st));
+    ONNG_HIP(clear_range(rcnt, short_rows ? static_cast<void *>(cnt + n + 1) : rcnt + n, st));
     if (short_rows) {
         const dim3 grid(blocks_for(n, 256)), block(256);
         if (n > 0) hipLaunchKernelGGL(sa_short_count_kernel, grid, block, 0, st, knn, n, k, eo, ei, cnt);
@@ -1007,7 +1009,7 @@ static onng_status adjust_degree_impl(const int32_t *knn, const LenT *kd, int64_
         set_error("onng_adjust_degree: nnz_capacity too small");
         return ONNG_ERR_CAPACITY;
     }
-    seg_sort<LenT>(short_rows ? offsets : seg, offsets, n, keys, nbrs, lens, queue, n_queue, st);
+    seg_sort<LenT>(short_rows ? offsets : seg, offsets, n, keys, nbrs, lens, queue, zero_after_scan(cnt + n), st);
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
     return ONNG_OK;
@@ -1032,7 +1034,6 @@ size_t adjust_degree_constrained_ws(int64_t n, int32_t k, int32_t e_o, int32_t e
     c.take<int64_t>(n + 1);            // |N(G_t, o)|
     c.take<int64_t>(n + 1);            // kept counts
     c.take<int32_t>(n);                // cursors
-    c.take<int32_t>(2);                // numbers of long lists
     c.take<int64_t>(n + 1);            // G_t offsets
     c.take<int32_t>(n);                // first source per node
     c.take<uint64_t>(nrev);            // G_t keys
@@ -1058,7 +1059,6 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
     int64_t *cnt = c.take<int64_t>(n + 1);
     int64_t *ocnt = c.take<int64_t>(n + 1);
     int32_t *cursor = c.take<int32_t>(n);
-    int32_t *n_queue = c.take<int32_t>(2);
     int64_t *rev_off = c.take<int64_t>(n + 1);
     int32_t *first_src = c.take<int32_t>(n);
     uint64_t *rkeys = c.take<uint64_t>(nrev);
@@ -1068,14 +1068,14 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
     int32_t *queue = c.take<int32_t>(n);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
-    ONNG_HIP(clear_range(cnt, n_queue + 2, st));
+    ONNG_HIP(clear_range(cnt, cursor + n, st));
     if (n > 0) {
         hipLaunchKernelGGL(sac_rcount_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, knn, n,
                            k, ei, cnt);
         ONNG_HIP(hipcub::DeviceScan::ExclusiveSum(tmp, tb, cnt, rev_off, (int)(n + 1), st));
         hipLaunchKernelGGL((sac_scatter_kernel<LenT>), dim3(blocks_for(n, 256)), dim3(256), 0, st,
                            knn, kd, n, k, ei, rev_off, cursor, rkeys, first_src);
-        seg_sort<LenT>(rev_off, rev_off, n, rkeys, rv_nb, rv_len, queue, n_queue, st);
+        seg_sort<LenT>(rev_off, rev_off, n, rkeys, rv_nb, rv_len, queue, zero_after_scan(cnt + n), st);
         hipLaunchKernelGGL((sac_select_kernel<LenT, false>), dim3(blocks_for(n * WAVE, 256)),
                            dim3(256), 0, st, rev_off, rv_nb, rv_len, first_src, knn, kd, n, k, eo,
                            ocnt, nullptr, nullptr);
@@ -1096,7 +1096,7 @@ static onng_status adjust_degree_constrained_impl(const int32_t *knn, const LenT
         hipLaunchKernelGGL((sac_select_kernel<LenT, true>), dim3(blocks_for(n * WAVE, 256)),
                            dim3(256), 0, st, rev_off, rv_nb, rv_len, first_src, knn, kd, n, k, eo,
                            nullptr, offsets, okeys);
-        seg_sort<LenT>(offsets, offsets, n, okeys, nbrs, lens, queue, n_queue + 1, st);
+        seg_sort<LenT>(offsets, offsets, n, okeys, nbrs, lens, queue, zero_after_scan(ocnt + n), st);
     }
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
@@ -1255,7 +1255,6 @@ size_t add_edges_ws(int64_t n, int64_t nnz, int64_t m) {
     Carver c(nullptr);
     c.take<int64_t>(n + 1);
     c.take<int32_t>(n);
-    c.take<int32_t>(1);
     c.take<uint64_t>(nnz + m);
     c.take<int32_t>(n);
     c.take<char>(scan_temp_bytes(n + 1));
@@ -1271,12 +1270,11 @@ static onng_status add_edges_impl(const onng_graph *g, const int32_t *src, const
     Carver c(ws);
     int64_t *cnt = c.take<int64_t>(n + 1);
     int32_t *cursor = c.take<int32_t>(n);
-    int32_t *n_queue = c.take<int32_t>(1);
     uint64_t *keys = c.take<uint64_t>(nnz + m);
     int32_t *queue = c.take<int32_t>(n);
     size_t tb = scan_temp_bytes(n + 1);
     void *tmp = c.take<char>(tb);
-    ONNG_HIP(clear_range(cnt, n_queue + 1, st));
+    ONNG_HIP(clear_range(cnt, cursor + n, st));
     const int64_t big = std::max(n, m);
     if (big > 0)
         hipLaunchKernelGGL(ae_count_kernel, dim3(blocks_for(big, 256)), dim3(256), 0, st,
@@ -1295,7 +1293,7 @@ static onng_status add_edges_impl(const onng_graph *g, const int32_t *src, const
         if (m > 0)
             hipLaunchKernelGGL((ae_new_kernel<LenT>), dim3(blocks_for(m, 256)), dim3(256), 0, st,
                                n, src, dst, len, m, out_off, cursor, keys);
-        seg_sort<LenT>(out_off, out_off, n, keys, out_nb, out_len, queue, n_queue, st);
+        seg_sort<LenT>(out_off, out_off, n, keys, out_nb, out_len, queue, zero_after_scan(cnt + n), st);
     }
     ONNG_HIP(hipGetLastError());
     ONNG_HIP(hipStreamSynchronize(st));
